@@ -170,7 +170,7 @@ enum {
  * Needs 1 <= K <= r (K <= 128, else NLR_EUNSUPPORTED), seed rows in [0, n);
  * NLR_EDEGENERATE if the K-th eigenvalue of U^T U is not above 1e-14 of the
  * largest.  Call between iterations (it uses the context's workspace) on the
- * context's stream; synchronises once per pass. */
+ * context's stream; synchronises once every few passes. */
 nlr_status nlr_labels_spectral(nlr_ctx* ctx, int32_t K, const int64_t* seed_rows, int32_t max_iter,
                                int32_t* labels, int32_t* passes_done);
 

@@ -107,9 +107,9 @@ __global__ __launch_bounds__(kThreads) void k_colmean(Geometry g, Bufs B) {
 // their mirror).
 typedef double f64x4_t __attribute__((ext_vector_type(4)));
 static_assert(kThreads == 256, "k_gram stages a 32 x 64 operand as 8 elements per thread of 4 waves");
-__global__ __launch_bounds__(kThreads) void k_gram(Geometry g, Bufs B) {
+__global__ __launch_bounds__(kThreads) void k_gram(const float* __restrict__ M, int64_t n, int d,
+                                                   const double* __restrict__ mean, double* __restrict__ part) {
   const int tid = threadIdx.x;
-  const int d = g.d;
   const int nb = (d + 63) / 64;
   int bp = blockIdx.y, bi = 0;
   while (bp >= nb - bi) {
@@ -117,9 +117,8 @@ __global__ __launch_bounds__(kThreads) void k_gram(Geometry g, Bufs B) {
     ++bi;
   }
   const int bj = bi + bp;
-  const int64_t n = g.n;
-  const int64_t r0 = (int64_t)blockIdx.x * n / g.GG;
-  const int64_t r1 = (int64_t)(blockIdx.x + 1) * n / g.GG;
+  const int64_t r0 = (int64_t)blockIdx.x * n / gridDim.x;
+  const int64_t r1 = (int64_t)(blockIdx.x + 1) * n / gridDim.x;
   const int lane = tid & 63, w = tid >> 6;
   const int kq = lane >> 4, cl = lane & 15;
   f64x4_t acc[4];
@@ -136,15 +135,15 @@ __global__ __launch_bounds__(kThreads) void k_gram(Geometry g, Bufs B) {
   const int sf = tid & 63, sr = tid >> 6;  // feature, first row (rows sr + 4 q)
   const int fsa = 64 * bi + sf, fsb = 64 * bj + sf;
   const bool oksa = fsa < d, oksb = fsb < d;
-  const double msa = oksa ? B.i_xbar[fsa] : 0.0, msb = oksb ? B.i_xbar[fsb] : 0.0;
+  const double msa = (oksa && mean) ? mean[fsa] : 0.0, msb = (oksb && mean) ? mean[fsb] : 0.0;
   float ra[8], rb[8];
   auto load_round = [&](int64_t t0) {
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
       const int64_t row = t0 + sr + 4 * q;
       const int64_t rb0 = (row < r1 ? row : r0) * (int64_t)d;
-      ra[q] = B.X[rb0 + (oksa ? fsa : 0)];
-      rb[q] = same ? 0.f : B.X[rb0 + (oksb ? fsb : 0)];
+      ra[q] = M[rb0 + (oksa ? fsa : 0)];
+      rb[q] = same ? 0.f : M[rb0 + (oksb ? fsb : 0)];
     }
   };
   if (r0 < r1) load_round(r0);
@@ -170,7 +169,7 @@ __global__ __launch_bounds__(kThreads) void k_gram(Geometry g, Bufs B) {
       }
     }
   }
-  double* out = B.i_gram + (int64_t)blockIdx.x * d * d;
+  double* out = part + (int64_t)blockIdx.x * d * d;
 #pragma unroll
   for (int J = 0; J < 4; ++J)
 #pragma unroll
@@ -580,10 +579,15 @@ hipError_t launch_colsum(const Geometry& g, const Bufs& b, hipStream_t st) {
   return hipGetLastError();
 }
 
+hipError_t launch_gram_partials(const float* M, int64_t n, int d, const double* mean, double* part, int chunks,
+                                hipStream_t st) {
+  const int nb = (d + 63) / 64;
+  hipLaunchKernelGGL(k_gram, dim3(chunks, nb * (nb + 1) / 2), dim3(kThreads), 0, st, M, n, d, mean, part);
+  return hipGetLastError();
+}
+
 hipError_t launch_gram(const Geometry& g, const Bufs& b, hipStream_t st) {
-  const int nb = (g.d + 63) / 64;
-  hipLaunchKernelGGL(k_gram, dim3(g.GG, nb * (nb + 1) / 2), dim3(kThreads), 0, st, g, b);
-  hipError_t e = hipGetLastError();
+  hipError_t e = launch_gram_partials(b.X, g.n, g.d, b.i_xbar, b.i_gram, g.GG, st);
   if (e != hipSuccess) return e;
   const int64_t dd = (int64_t)g.d * g.d;
   hipLaunchKernelGGL(k_gram_reduce, dim3((unsigned)((dd + kThreads - 1) / kThreads)), dim3(kThreads), 0, st, g, b);

@@ -185,23 +185,36 @@ Geometry make_geometry(int64_t n, int32_t d, int32_t r, int32_t K, bool aligned1
   return g;
 }
 
-static int32_t lab_gu(int64_t n, int32_t r) {
-  int64_t gu = (n + 4095) / 4096;
-  const int64_t cap = ((int64_t)16 << 20) / ((int64_t)r * r * 8);  // partials within 16 MiB
+// The label recovery's partial sums: the Gram partials of U, then the cluster sums of the
+// passes, in one region.  It is as large as 64 row chunks of r x r FP64 (16 MiB at most) and 256
+// of K x K, less what the r64 x r64 arrays take beyond r x r ones, so that the whole scratch stays
+// within what those would take (nlr_solve_static's fixed scratch also holds it); never under one
+// chunk of either kind.
+static size_t lab_fixed_bytes(int32_t r, int32_t K) {
+  const size_t r64 = (size_t)round_up(r, 64), r16 = (size_t)round_up(r, 16), k16 = (size_t)round_up(K, 16);
+  return 2 * align256(r64 * r64 * 8) + align256(r64 / 64 * 4096 * 8) + align256(2 * kLabJacParts * 8) +
+         2 * align256((size_t)r * K * 8) + align256(r16 * k16 * 8) + align256((size_t)K * K * 8) +
+         align256((size_t)K * 8) + 2 * align256((size_t)r * 8) + align256(16) + align256((size_t)K * 8) + align256(64);
+}
+static size_t lab_part_bytes(int64_t n, int32_t r) {
+  const size_t rr = (size_t)r * r * 8, kmax = r < kLabMaxK ? r : kLabMaxK;
+  size_t gu = (size_t)((n + 4095) / 4096);
+  const size_t cap = ((size_t)16 << 20) / rr;
   if (gu > cap) gu = cap;
   if (gu > 64) gu = 64;
-  return (int32_t)(gu < 1 ? 1 : gu);
-}
-static int32_t lab_ga2(int64_t n) {
-  int64_t ga = (n + 63) / 64;
-  return (int32_t)(ga > 256 ? 256 : (ga < 1 ? 1 : ga));
+  if (gu < 1) gu = 1;
+  size_t ga = (size_t)((n + 63) / 64);
+  if (ga > 256) ga = 256;
+  size_t bytes = gu * rr + ga * (kmax * kmax + kmax + 1) * 8;
+  const size_t fixed = lab_fixed_bytes(r, (int32_t)kmax), plain = 2 * rr + (size_t)r * kmax * 8 + kmax * kmax * 8;
+  bytes -= fixed > plain ? (fixed - plain < bytes ? fixed - plain : bytes) : 0;
+  const size_t least = kmax * (size_t)r * 8 + kmax * 4;
+  if (bytes < rr) bytes = rr;
+  return bytes < least ? least : bytes;
 }
 
 size_t lab_scratch_bytes(int64_t n, int32_t r, int32_t K) {
-  const size_t rr = (size_t)r * r * 8;
-  return align256((size_t)lab_gu(n, r) * rr) + 2 * align256(rr) + align256((size_t)r * K * 8) +
-         align256((size_t)K * K * 8) + align256((size_t)lab_ga2(n) * ((size_t)K * K + K + 1) * 8) +
-         align256((size_t)K * 8) + align256(64);
+  return lab_fixed_bytes(r, K) + align256(lab_part_bytes(n, r));
 }
 
 LabScratch carve_lab_scratch(int64_t n, int32_t r, int32_t K, char* base) {
@@ -212,15 +225,42 @@ LabScratch carve_lab_scratch(int64_t n, int32_t r, int32_t K, char* base) {
     off += align256(bytes);
     return p;
   };
-  const size_t rr = (size_t)r * r * 8;
-  L.GU = lab_gu(n, r);
-  L.GA2 = lab_ga2(n);
-  L.gpart = reinterpret_cast<double*>(take((size_t)L.GU * rr));
-  L.A = reinterpret_cast<double*>(take(rr));
-  L.V = reinterpret_cast<double*>(take(rr));
+  const size_t bytes = lab_part_bytes(n, r), rr = (size_t)r * r * 8;
+  const int32_t kmax = r < kLabMaxK ? r : kLabMaxK;
+  // Gram chunks: at most 256 rows' worth each, four workgroups a compute unit over all block
+  // pairs (as the initialisation's), within the region
+  const int64_t nbk = (r + 63) / 64;
+  int64_t gu = 1024 / (nbk * (nbk + 1) / 2);
+  if (gu > 256) gu = 256;
+  if (gu > (n + 255) / 256) gu = (n + 255) / 256;
+  if (gu > (int64_t)(bytes / rr)) gu = (int64_t)(bytes / rr);
+  L.GU = (int32_t)(gu < 1 ? 1 : gu);
+  // sum chunks: two workgroups a compute unit over the 64-column groups (their 64 KiB of LDS)
+  int64_t w = 512 / nbk;
+  const size_t chunk = (size_t)kmax * r * 8 + (size_t)kmax * 4;
+  if (w > (n + 255) / 256) w = (n + 255) / 256;
+  if (w > (int64_t)(bytes / chunk)) w = (int64_t)(bytes / chunk);
+  L.W = (int32_t)(w < 1 ? 1 : w);
+  L.r64 = round_up(r, 64);
+  const size_t r64 = (size_t)L.r64, r16 = (size_t)round_up(r, 16), k16 = (size_t)round_up(K, 16);
+  char* part = take(bytes);
+  L.gpart = reinterpret_cast<double*>(part);
+  L.spart = reinterpret_cast<long long*>(part);
+  L.cpart = reinterpret_cast<int32_t*>(part + (size_t)L.W * K * r * 8);
+  L.A = reinterpret_cast<double*>(take(r64 * r64 * 8));
+  L.V = reinterpret_cast<double*>(take(r64 * r64 * 8));
+  L.Q = reinterpret_cast<double*>(take(r64 / 64 * 4096 * 8));
+  L.jpart = reinterpret_cast<double*>(take(2 * kLabJacParts * 8));
   L.P = reinterpret_cast<double*>(take((size_t)r * K * 8));
-  L.cent = reinterpret_cast<double*>(take((size_t)K * K * 8));
-  L.apart = reinterpret_cast<double*>(take((size_t)L.GA2 * ((size_t)K * K + K + 1) * 8));
+  L.Pt = reinterpret_cast<double*>(take((size_t)r * K * 8));
+  L.Mimg = reinterpret_cast<double*>(take(r16 * k16 * 8));
+  L.centT = reinterpret_cast<double*>(take((size_t)K * K * 8));
+  L.cn = reinterpret_cast<double*>(take((size_t)K * 8));
+  L.cscale = reinterpret_cast<double*>(take((size_t)r * 8));
+  L.cinv = reinterpret_cast<double*>(take((size_t)r * 8));
+  char* two = take(16);
+  L.pmax = reinterpret_cast<double*>(two);
+  L.changed = reinterpret_cast<unsigned long long*>(two + 8);
   L.seeds = reinterpret_cast<int64_t*>(take((size_t)K * 8));
   L.flag = reinterpret_cast<int32_t*>(take(64));
   return L;
@@ -910,25 +950,38 @@ nlr_status nlr_labels_spectral(nlr_ctx* c, int32_t K, const int64_t* seed_rows, 
   if (c->failed) return NLR_ESTATE;
   const Geometry& g = c->g;
   LabScratch L = carve_lab_scratch(g.n, g.r, K, reinterpret_cast<char*>(c->b.theta_part));
-  int32_t flags[2] = {0, 0};
+  int32_t flags[4] = {0, 0, 0, 0};  // degenerate, done, passes, Jacobi converged
+  auto read_flags = [&]() {
+    return hipMemcpyAsync(flags, L.flag, sizeof(flags), hipMemcpyDeviceToHost, c->stream) == hipSuccess &&
+           hipStreamSynchronize(c->stream) == hipSuccess;
+  };
   if (hipMemcpyAsync(L.seeds, seed_rows, (size_t)K * sizeof(int64_t), hipMemcpyHostToDevice, c->stream) !=
       hipSuccess)
     return hip_fail(c);
-  if (launch_lab_embed(g, c->b, L, K, c->stream) != hipSuccess) return hip_fail(c);
-  if (hipMemcpyAsync(flags, L.flag, sizeof(flags), hipMemcpyDeviceToHost, c->stream) != hipSuccess)
-    return hip_fail(c);
-  if (hipStreamSynchronize(c->stream) != hipSuccess) return hip_fail(c);
-  if (flags[0]) return NLR_EDEGENERATE;
-  int32_t pass = 0;
-  while (pass < max_iter) {
-    ++pass;
-    if (launch_lab_pass(g, c->b, L, K, labels, pass == 1 ? 1 : 0, c->stream) != hipSuccess) return hip_fail(c);
-    if (hipMemcpyAsync(flags, L.flag, sizeof(flags), hipMemcpyDeviceToHost, c->stream) != hipSuccess)
-      return hip_fail(c);
-    if (hipStreamSynchronize(c->stream) != hipSuccess) return hip_fail(c);
-    if (pass > 1 && flags[1] == 0) break;
+  if (launch_lab_gram(g, c->b, L, c->stream) != hipSuccess) return hip_fail(c);
+  // sweeps past convergence return at entry: a dozen at first (most factors take eight to
+  // eleven), then a few at a time
+  for (int32_t sweep = 0; sweep < kLabMaxSweeps;) {
+    const int32_t count = sweep == 0 ? 12 : 6;
+    if (launch_lab_sweeps(L, g.r, sweep, count, c->stream) != hipSuccess) return hip_fail(c);
+    sweep += count;
+    if (L.r64 == 64) break;  // one workgroup runs to the end
+    if (!read_flags()) return hip_fail(c);
+    if (flags[3]) break;
   }
-  if (passes_done) *passes_done = pass;
+  if (launch_lab_embed(g, c->b, L, K, c->stream) != hipSuccess) return hip_fail(c);
+  // the device ends the iteration; the host looks every eighth pass (the kernels of a pass after
+  // the last, or on a degenerate spectrum, return at entry)
+  for (int32_t done = 0; done < max_iter;) {
+    const int32_t count = max_iter - done < 8 ? max_iter - done : 8;
+    for (int32_t k = 0; k < count; ++k)
+      if (launch_lab_pass(g, c->b, L, K, labels, c->stream) != hipSuccess) return hip_fail(c);
+    done += count;
+    if (!read_flags()) return hip_fail(c);
+    if (flags[0]) return NLR_EDEGENERATE;
+    if (flags[1]) break;
+  }
+  if (passes_done) *passes_done = flags[2];
   return NLR_OK;
 }
 

@@ -154,19 +154,32 @@ struct Bufs {
 
 // Scratch of the spectral label recovery (carved from the Theta-partial region,
 // which is free between host calls).
+constexpr int kLabMaxK = 128;
+constexpr int kLabMaxSweeps = 60;   // Jacobi sweeps at most
+constexpr int kLabJacParts = 32;    // partial sums of the off-diagonal mass (7 pivot + 21 other blocks at most)
 struct LabScratch {
   int32_t GU;          // row chunks of the U^T U partials
-  int32_t GA2;         // row chunks of the assignment pass
-  double* gpart;       // GU x r x r
-  double* A;           // r x r: U^T U, diagonalised in place
-  double* V;           // r x r: eigenvectors
+  int32_t W;           // row chunks of the cluster sums
+  int32_t r64;         // r rounded up to a multiple of 64: row stride of A and V
+  double* gpart;       // GU x r x r (before the passes)
+  long long* spart;    // W x K x r: integer cluster sums (same memory as gpart)
+  int32_t* cpart;      // W x K: rows per cluster
+  double* A;           // r64 x r64: U^T U, diagonalised in place
+  double* V;           // r64 x r64: eigenvectors
+  double* Q;           // 64 x 64 rotations of each pair of column blocks
+  double* jpart;       // 2 kLabJacParts: squared off-diagonal, diagonal entries
   double* P;           // r x K: V_K Lambda_K^(-1/2)
-  double* cent;        // K x K centroids
-  double* apart;       // GA2 x (K*K + K + 1): cluster sums, counts, changed labels
+  double* Pt;          // K x r: its transpose
+  double* Mimg;        // P cent^T in the assignment's operand order (r16 x K16)
+  double* centT;       // K x K centroids, component-major
+  double* cn;          // K: |cent_k|^2
+  double* cscale;      // r: power-of-two scale of the integer sums
+  double* cinv;        // r: its inverse
+  double* pmax;        // 1 / sqrt(K-th eigenvalue), a bound on the rows of P
+  unsigned long long* changed;  // labels changed by the pass
   int64_t* seeds;      // K seed rows
-  int32_t* flag;       // [0] degenerate spectrum, [1] changed labels of the last pass
+  int32_t* flag;       // [0] degenerate spectrum, [1] iteration done, [2] passes, [3] Jacobi converged
 };
-constexpr int kLabMaxK = 128;
 size_t lab_scratch_bytes(int64_t n, int32_t r, int32_t K);
 LabScratch carve_lab_scratch(int64_t n, int32_t r, int32_t K, char* base);
 
@@ -188,6 +201,10 @@ hipError_t launch_ctl_init(const Bufs& b, float gamma_f, hipStream_t st);
 hipError_t launch_clear_stop(const Bufs& b, hipStream_t st);
 hipError_t launch_colsum(const Geometry& g, const Bufs& b, hipStream_t st);
 hipError_t launch_gram(const Geometry& g, const Bufs& b, hipStream_t st);
+// partials (one d x d array a row chunk) of (M - 1 mean^T)^T (M - 1 mean^T), blocks on and above
+// the diagonal of 64 x 64 blocks; mean null: M^T M
+hipError_t launch_gram_partials(const float* M, int64_t n, int d, const double* mean, double* part, int chunks,
+                                hipStream_t st);
 hipError_t launch_spectral(const Geometry& g, const Bufs& b, hipStream_t st);
 hipError_t launch_normalise(const Geometry& g, const Bufs& b, hipStream_t st);
 hipError_t launch_project(const Geometry& g, const Bufs& b, double K, int in_omega, hipStream_t st);
@@ -211,9 +228,13 @@ hipError_t launch_pass_b_split(const Geometry& g, const Bufs& b, const StepArgs&
 hipError_t launch_seg_theta(const Geometry& g, const Bufs& b, int64_t rows, int nseg, hipStream_t st);
 hipError_t launch_data_start(const Geometry& g, const Bufs& b, const StepArgs& a0, bool x_normalised,
                              hipStream_t st);
+// U^T U, `count` Jacobi sweeps from sweep `first` on (all of them up to 64 columns), the basis
+// and the seed centroids, one assignment pass with its centroids
+hipError_t launch_lab_gram(const Geometry& g, const Bufs& b, const LabScratch& L, hipStream_t st);
+hipError_t launch_lab_sweeps(const LabScratch& L, int r, int first, int count, hipStream_t st);
 hipError_t launch_lab_embed(const Geometry& g, const Bufs& b, const LabScratch& L, int K, hipStream_t st);
 hipError_t launch_lab_pass(const Geometry& g, const Bufs& b, const LabScratch& L, int K, int32_t* labels,
-                           int first, hipStream_t st);
+                           hipStream_t st);
 hipError_t launch_labels(const Geometry& g, const Bufs& b, int32_t* labels, hipStream_t st);
 hipError_t launch_pass_a_panel(const Geometry& g, const Bufs& b, const StepArgs& a, hipStream_t st);
 hipError_t launch_theta_split_panel(const Geometry& g, const Bufs& b, hipStream_t st);

@@ -102,3 +102,49 @@ def test_labels_spectral_degenerate_and_errors():
     assert e.value.status == nlr.NLR_EINVAL
     lab, passes = ctx.labels_spectral(3, [0, 1, 2])  # rank 3 is enough for K = 3
     assert passes >= 1
+
+
+def _pattern_factor(n, K, r, seed):
+    """A factor near a solution: the rows of a cluster share a non-negative pattern over the
+    cluster's own columns, plus non-negative noise everywhere."""
+    rng = np.random.default_rng(seed)
+    own = np.arange(r) % K
+    pattern = np.zeros((K, r))
+    pattern[own, np.arange(r)] = 0.5 + rng.random(r)
+    pattern /= np.linalg.norm(pattern, axis=1, keepdims=True)
+    lab = rng.integers(0, K, n)
+    lab[:K] = np.arange(K)
+    return (pattern[lab] + 0.05 * np.abs(rng.standard_normal((n, r)))).astype(np.float32), lab
+
+
+@pytest.mark.parametrize("n,r,K", [
+    (1, 1, 1), (17, 2, 2), (300, 5, 3), (1000, 13, 4), (1029, 16, 16), (1111, 30, 17), (1500, 33, 15),
+    (2000, 64, 33), (2049, 65, 48), (1800, 66, 64), (2500, 128, 100), (3001, 129, 65), (2600, 200, 100),
+    (3100, 257, 113), (3333, 448, 128)])
+def test_labels_spectral_shapes(n, r, K):
+    """Edges of the 64-column Jacobi blocks, of the 16-row and 16-cluster tiles, 16-byte rows or
+    not, ranks from 1 to 448: labels and pass counts identical to the oracle's."""
+    U, lab = _pattern_factor(n, K, r, seed=100 + r)
+    X, _, _ = gaussian_mixture(n, 4, 1, 1.0, seed=3) if n > 1 else (np.ones((1, 4), np.float32), None, None)
+    ctx = make_ctx(X, U, K, 0.01, flags=4)  # NLR_INIT_X_NORMALISED: only the factor matters here
+    rng = np.random.default_rng(7)
+    seeds = rng.choice(n, size=K, replace=False).tolist()
+    _check(ctx, K, seeds, max_iter=12)
+
+
+def test_labels_spectral_equal_rows():
+    """Every row of a cluster equal and two seeds in one cluster: two equal centroids, the lower
+    index takes all of that cluster's rows and the other keeps its place without any."""
+    n, K, r = 1200, 6, 9
+    U, lab = _pattern_factor(n, K, r, seed=5)
+    U = U[:K][lab]  # rows of a cluster bitwise equal
+    X, _, _ = gaussian_mixture(n, 4, 1, 1.0, seed=3)
+    ctx = make_ctx(X, U, K, 0.01, flags=4)
+    seeds = [int(np.flatnonzero(lab == k)[0]) for k in range(K)]
+    seeds[4] = int(np.flatnonzero(lab == 1)[1])  # cluster 4 has no seed, cluster 1 has two
+    got, passes = ctx.labels_spectral(K, seeds)
+    got = got.cpu().numpy()
+    for k in (0, 1, 2, 3, 5):
+        assert (got[lab == k] == k).all()
+    assert len(set(got[lab == 4])) == 1 and not (got == 4).any()
+    assert passes == 2
