@@ -125,6 +125,30 @@ __device__ __forceinline__ float f16_range_scale(float vmax) {
   return ldexpf(1.0f, k);
 }
 
+// FP64 matrix core v_mfma_f64_16x16x4f64, D += A B: lane l supplies A[l % 16][l / 16] and
+// B[l / 16][l % 16]; entry v of D is D[4 v + l / 16][l % 16].
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ f64x4 mfma16x16x4d(double a, double b, f64x4 c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
+// acc += A B over `steps` steps of 4 for a 64 x 64 result of one workgroup: wave w holds rows
+// 16 w .. 16 w + 15 in four column tiles.  fa(k0): this lane's A element of row 16 w + lane % 16,
+// k = k0 + lane / 16; fb(k0, J): its B element of k = k0 + lane / 16, column 16 J + lane % 16.
+template <int UNROLL, class FA, class FB>
+__device__ __forceinline__ void mm64(int steps, FA fa, FB fb, f64x4 (&acc)[4]) {
+#pragma unroll UNROLL
+  for (int st = 0; st < steps; ++st) {
+    const double av = fa(4 * st);
+#pragma unroll
+    for (int J = 0; J < 4; ++J) acc[J] = mfma16x16x4d(av, fb(4 * st, J), acc[J]);
+  }
+}
+__device__ __forceinline__ void mm64_zero(f64x4 (&acc)[4]) {
+#pragma unroll
+  for (int J = 0; J < 4; ++J) acc[J] = (f64x4){0.0, 0.0, 0.0, 0.0};
+}
+
 // Fixed-order sum over a 512-thread workgroup; result valid in thread 0.
 __device__ __forceinline__ double block_sum8_d(double v, double* red) {
   for (int m = 32; m >= 1; m >>= 1) v += shfl_xor_d(v, m);

@@ -21,8 +21,6 @@
 
 namespace nlr {
 
-typedef double f64x4 __attribute__((ext_vector_type(4)));
-
 constexpr int kLabUpd = 512;      // threads of the centroid kernel
 constexpr int kJacLd = 65;        // LDS row stride (doubles) of the Jacobi and apply tiles
 
@@ -79,16 +77,19 @@ __device__ __forceinline__ void lab_pair(int m, int t, int a, int& lo, int& hi) 
 // N / 2 disjoint rotations per step, ended early once the off-diagonal mass is at rounding
 // level.  The rotated block replaces the pivot block of A; the rotations go to Q[pair]
 // (block form, one sweep a visit) or to V (whole = 1: r <= 64, run to the end).
-// What bounds it: the chain of N - 1 steps, each two barriers and the latency of a fp64
-// divide and square root, about 0.35 us; all 32 rotations of a step and both sides of the
-// 2 x 2 updates are taken between the barriers.
-__global__ __launch_bounds__(kThreads) void k_lab_sub(LabScratch L, int step, int nb, int N, int sweeps, int whole,
-                                                      int check, int last) {
+// What bounds it: the chain of N - 1 steps, each two barriers, the latency of a fp64 square
+// root, divide and reciprocal root, and that of the 2 x 2 updates' LDS reads.  All rotations of
+// a step and both sides of the updates are taken between the barriers; the update of Q by a
+// step's rotations runs on the other waves while the first one forms the next step's.
+constexpr int kJacThreads = 1024;
+__global__ __launch_bounds__(kJacThreads) void k_lab_sub(LabScratch L, int step, int nb, int N, int sweeps, int whole,
+                                                         int check, int last) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   double* As = reinterpret_cast<double*>(smem_raw);
   double* Qs = As + 64 * kJacLd;
-  __shared__ double cs[32], sn[32], red[4], tot[2];
-  __shared__ int pp[32], qq[32];
+  // rotations of the current and the previous step: c, s, and the two columns
+  __shared__ double cs[2][32], sn[2][32], red[2][kJacThreads / 64], tot[2];
+  __shared__ int pq[2][32];
   const int tid = threadIdx.x;
   const int a = blockIdx.x, np = nb / 2;
   if (L.flag[kFlagEig]) return;
@@ -104,7 +105,7 @@ __global__ __launch_bounds__(kThreads) void k_lab_sub(LabScratch L, int step, in
   int I, J;
   lab_pair(nb, step, a, I, J);
   const int ld = L.r64;
-  for (int e = tid; e < 64 * 64; e += kThreads) {
+  for (int e = tid; e < 64 * 64; e += kJacThreads) {
     const int i = e >> 6, j = e & 63;
     const int gi = i < 32 ? 32 * I + i : 32 * J + i - 32, gj = j < 32 ? 32 * I + j : 32 * J + j - 32;
     As[i * kJacLd + j] = L.A[(int64_t)gi * ld + gj];
@@ -112,100 +113,119 @@ __global__ __launch_bounds__(kThreads) void k_lab_sub(LabScratch L, int step, in
   }
   __syncthreads();
   const int h = N >> 1;
-  // the (k, l), k <= l, pairs of rotations whose 2 x 2 blocks this thread updates: rows a and
-  // h - 1 - a of the triangle make one run of h + 1
-  int uk[3], ul[3];
-#pragma unroll
-  for (int u = 0; u < 3; ++u) {
-    const int x = tid + u * kThreads;
-    uk[u] = -1;
-    ul[u] = 0;
-    if (x < ((h + 1) >> 1) * (h + 1)) {
-      const int ra = x / (h + 1), rb = x - ra * (h + 1);
-      if (rb < h - ra) {
-        uk[u] = ra;
-        ul[u] = ra + rb;
-      } else if (h - 1 - ra != ra) {
-        uk[u] = h - 1 - ra;
-        ul[u] = uk[u] + rb - (h - ra);
-      }
+  // the (k, l), k <= l, pair of rotations whose 2 x 2 block this thread updates: rows ra and
+  // h - 1 - ra of the triangle make one run of h + 1 (at most 16 runs of 33)
+  int uk = -1, ul = 0;
+  if (tid < ((h + 1) >> 1) * (h + 1)) {
+    const int ra = tid / (h + 1), rb = tid - ra * (h + 1);
+    if (rb < h - ra) {
+      uk = ra;
+      ul = ra + rb;
+    } else if (h - 1 - ra != ra) {
+      uk = h - 1 - ra;
+      ul = uk + rb - (h - ra);
     }
   }
   auto sums = [&]() {
     double off = 0.0, dia = 0.0;
-    for (int e = tid; e < 64 * 64; e += kThreads) {
+    for (int e = tid; e < 64 * 64; e += kJacThreads) {
       const double v = As[(e >> 6) * kJacLd + (e & 63)];
       if ((e >> 6) == (e & 63))
         dia += v * v;
       else
         off += v * v;
     }
-    off = block_sum_d(off, red);
-    dia = block_sum_d(dia, red);
-    if (tid == 0) {
-      tot[0] = off;
-      tot[1] = dia;
+    for (int m = 32; m >= 1; m >>= 1) {
+      off += shfl_xor_d(off, m);
+      dia += shfl_xor_d(dia, m);
+    }
+    if ((tid & 63) == 0) {
+      red[0][tid >> 6] = off;
+      red[1][tid >> 6] = dia;
+    }
+    __syncthreads();
+    if (tid < 2) {
+      double t = 0.0;
+      for (int w = 0; w < kJacThreads / 64; ++w) t += red[tid][w];
+      tot[tid] = t;
     }
     __syncthreads();
   };
+  // Q <- Q J with the rotations in slot b: row i = lane, rotations k = first, first + every, ...
+  auto rotate_q = [&](int b, int first, int every) {
+    const int i = tid & 63;
+    for (int k = first; k < h; k += every) {
+      const int p = pq[b][k] >> 8, q = pq[b][k] & 255;
+      const double c = cs[b][k], s = sn[b][k];
+      const double vp = Qs[i * kJacLd + p], vq = Qs[i * kJacLd + q];
+      Qs[i * kJacLd + p] = c * vp - s * vq;
+      Qs[i * kJacLd + q] = s * vp + c * vq;
+    }
+  };
+  int slot = 0;
+  bool pending = false;  // the previous step's rotations are not yet in Q
   for (int sw = 0; sw < sweeps; ++sw) {
     if (whole) {
       sums();
       if (!(tot[0] > 1e-30 * (tot[0] + tot[1]))) break;
     }
     for (int t = 0; t < N - 1; ++t) {
-      if (tid < h) {
-        int p, q;
-        lab_pair(N, t, tid, p, q);
-        const double apq = As[p * kJacLd + q];
-        double c = 1.0, s = 0.0;
-        if (apq != 0.0) {
-          const double th = (As[q * kJacLd + q] - As[p * kJacLd + p]) / (2.0 * apq);
-          const double tt = (th >= 0.0 ? 1.0 : -1.0) / (fabs(th) + sqrt(th * th + 1.0));
-          c = 1.0 / sqrt(tt * tt + 1.0);
-          s = tt * c;
-        }
-        cs[tid] = c;
-        sn[tid] = s;
-        pp[tid] = p;
-        qq[tid] = q;
-      }
-      __syncthreads();
-#pragma unroll
-      for (int u = 0; u < 3; ++u)
-        if (uk[u] >= 0) {
-          const int k = uk[u], l = ul[u];
-          const double ck = cs[k], sk = sn[k], cl = cs[l], sl = sn[l];
-          const int pk = pp[k], qk = qq[k], pl = pp[l], ql = qq[l];
-          const double b00 = As[pk * kJacLd + pl], b01 = As[pk * kJacLd + ql];
-          const double b10 = As[qk * kJacLd + pl], b11 = As[qk * kJacLd + ql];
-          const double r00 = ck * b00 - sk * b10, r01 = ck * b01 - sk * b11;
-          const double r10 = sk * b00 + ck * b10, r11 = sk * b01 + ck * b11;
-          const double n00 = cl * r00 - sl * r01, n11 = sl * r10 + cl * r11;
-          double n01 = sl * r00 + cl * r01, n10 = cl * r10 - sl * r11;
-          if (k == l && sk != 0.0) n01 = n10 = 0.0;
-          As[pk * kJacLd + pl] = n00;
-          As[pk * kJacLd + ql] = n01;
-          As[qk * kJacLd + pl] = n10;
-          As[qk * kJacLd + ql] = n11;
-          if (k != l) {
-            As[pl * kJacLd + pk] = n00;
-            As[ql * kJacLd + pk] = n01;
-            As[pl * kJacLd + qk] = n10;
-            As[ql * kJacLd + qk] = n11;
+      if (tid < 64) {
+        if (tid < h) {
+          // round-robin pairing, as lab_pair
+          int x = t + tid, y = t + N - 1 - tid;
+          x -= x >= N - 1 ? N - 1 : 0;
+          y -= y >= N - 1 ? N - 1 : 0;
+          if (tid == 0) y = N - 1;
+          const int p = x < y ? x : y, q = x < y ? y : x;
+          // tan of the angle: t = sign(d) b / (|d| + sqrt(d^2 + b^2)), d = a_qq - a_pp, b = 2 a_pq
+          const double b = 2.0 * As[p * kJacLd + q], d = As[q * kJacLd + q] - As[p * kJacLd + p];
+          const double hyp = d * d + b * b;
+          double c = 1.0, s = 0.0;
+          if (b != 0.0 && hyp > 0.0) {
+            const double tt = (d >= 0.0 ? b : -b) / (fabs(d) + sqrt(hyp));
+            c = rsqrt(1.0 + tt * tt);
+            s = tt * c;
           }
+          cs[slot][tid] = c;
+          sn[slot][tid] = s;
+          pq[slot][tid] = (p << 8) | q;
         }
-      for (int k = tid >> 6; k < h; k += 4) {
-        const int i = tid & 63, p = pp[k], q = qq[k];
-        const double vp = Qs[i * kJacLd + p], vq = Qs[i * kJacLd + q];
-        Qs[i * kJacLd + p] = cs[k] * vp - sn[k] * vq;
-        Qs[i * kJacLd + q] = sn[k] * vp + cs[k] * vq;
+      } else if (pending) {
+        rotate_q(slot ^ 1, (tid >> 6) - 1, kJacThreads / 64 - 1);
       }
       __syncthreads();
+      if (uk >= 0) {
+        const int k = uk, l = ul;
+        const double ck = cs[slot][k], sk = sn[slot][k], cl = cs[slot][l], sl = sn[slot][l];
+        const int pk = pq[slot][k] >> 8, qk = pq[slot][k] & 255, pl = pq[slot][l] >> 8, ql = pq[slot][l] & 255;
+        const double b00 = As[pk * kJacLd + pl], b01 = As[pk * kJacLd + ql];
+        const double b10 = As[qk * kJacLd + pl], b11 = As[qk * kJacLd + ql];
+        const double r00 = ck * b00 - sk * b10, r01 = ck * b01 - sk * b11;
+        const double r10 = sk * b00 + ck * b10, r11 = sk * b01 + ck * b11;
+        const double n00 = cl * r00 - sl * r01, n11 = sl * r10 + cl * r11;
+        double n01 = sl * r00 + cl * r01, n10 = cl * r10 - sl * r11;
+        if (k == l && sk != 0.0) n01 = n10 = 0.0;
+        As[pk * kJacLd + pl] = n00;
+        As[pk * kJacLd + ql] = n01;
+        As[qk * kJacLd + pl] = n10;
+        As[qk * kJacLd + ql] = n11;
+        if (k != l) {
+          As[pl * kJacLd + pk] = n00;
+          As[ql * kJacLd + pk] = n01;
+          As[pl * kJacLd + qk] = n10;
+          As[ql * kJacLd + qk] = n11;
+        }
+      }
+      __syncthreads();
+      slot ^= 1;
+      pending = true;
     }
   }
+  if (pending) rotate_q(slot ^ 1, tid >> 6, kJacThreads / 64);
+  __syncthreads();
   double* Qo = whole ? L.V : L.Q + (int64_t)a * 4096;
-  for (int e = tid; e < 64 * 64; e += kThreads) {
+  for (int e = tid; e < 64 * 64; e += kJacThreads) {
     const int i = e >> 6, j = e & 63;
     const int gi = i < 32 ? 32 * I + i : 32 * J + i - 32, gj = j < 32 ? 32 * I + j : 32 * J + j - 32;
     L.A[(int64_t)gi * ld + gj] = As[i * kJacLd + j];
@@ -220,91 +240,89 @@ __global__ __launch_bounds__(kThreads) void k_lab_sub(LabScratch L, int step, in
   }
 }
 
-// 64 x 64 product accumulators of one workgroup: wave w rows 16 w .. 16 w + 15, four column
-// tiles; element (row 4 v + lane / 16, column lane % 16) in entry v.
-template <class FA, class FB>
-__device__ __forceinline__ void mm64(FA fa, FB fb, f64x4 (&acc)[4]) {
-#pragma unroll
-  for (int J = 0; J < 4; ++J) acc[J] = (f64x4){0.0, 0.0, 0.0, 0.0};
-#pragma unroll 4
-  for (int st = 0; st < 16; ++st) {
-    const double av = fa(4 * st);
-#pragma unroll
-    for (int J = 0; J < 4; ++J) acc[J] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, fb(4 * st, J), acc[J], 0, 0, 0);
-  }
-}
-
 // Rotations of one block-Jacobi step applied to the rest of A and to V: workgroup (a, b), a < b,
 // takes A_ab <- Q_a^T A_ab Q_b (and its mirror); the others V rows 64 rb .. + 63, columns of pair
-// b, <- times Q_b.  The pivot blocks themselves come rotated from k_lab_sub.
+// b, <- times Q_b.  The pivot blocks themselves come rotated from k_lab_sub.  All operands are
+// loaded into LDS at once, so one memory latency is paid (operands read from L2 inside the
+// products: 15 us a step at 200 columns).
+constexpr size_t kApplyLds = (64 * kJacLd + 2 * 64 * 64) * sizeof(double);
 __global__ __launch_bounds__(kThreads) void k_lab_apply(LabScratch L, int step, int nb, int last) {
   if (L.flag[kFlagEig]) return;
-  __shared__ double S[64 * kJacLd];
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  double* S = reinterpret_cast<double*>(smem_raw);
+  double* Qa = S + 64 * kJacLd;
+  double* Qb = Qa + 64 * 64;
   __shared__ double red[4];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, kq = lane >> 4, cl = lane & 15;
   const int np = nb / 2, nA = np * (np - 1) / 2, ld = L.r64;
-  int x = blockIdx.x;
-  f64x4 acc[4];
-  if (x < nA) {
-    int a = 0;
+  int x = blockIdx.x, a = 0, b, rb = 0;
+  const bool isA = x < nA;
+  if (isA) {
     while (x >= np - 1 - a) {
       x -= np - 1 - a;
       ++a;
     }
-    const int b = a + 1 + x;
-    int Ia, Ja, Ib, Jb;
-    lab_pair(nb, step, a, Ia, Ja);
-    lab_pair(nb, step, b, Ib, Jb);
-    const double* Qa = L.Q + (int64_t)a * 4096;
-    const double* Qb = L.Q + (int64_t)b * 4096;
-    auto row = [&](int i) { return i < 32 ? 32 * Ia + i : 32 * Ja + i - 32; };
-    auto col = [&](int j) { return j < 32 ? 32 * Ib + j : 32 * Jb + j - 32; };
-    for (int e = tid; e < 64 * 64; e += kThreads)
-      S[(e >> 6) * kJacLd + (e & 63)] = L.A[(int64_t)row(e >> 6) * ld + col(e & 63)];
-    __syncthreads();
-    mm64([&](int k0) { return Qa[(k0 + kq) * 64 + 16 * w + cl]; },
-         [&](int k0, int J) { return S[(k0 + kq) * kJacLd + 16 * J + cl]; }, acc);
+    b = a + 1 + x;
+  } else {
+    b = (x - nA) % np;
+    rb = (x - nA) / np;
+  }
+  int Ia, Ja, Ib, Jb;
+  lab_pair(nb, step, a, Ia, Ja);
+  lab_pair(nb, step, b, Ib, Jb);
+  auto row = [&](int i) { return !isA ? 64 * rb + i : (i < 32 ? 32 * Ia + i : 32 * Ja + i - 32); };
+  auto col = [&](int j) { return j < 32 ? 32 * Ib + j : 32 * Jb + j - 32; };
+  double* M = isA ? L.A : L.V;
+  {
+    double v[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      const int e = tid + u * kThreads;
+      v[u] = M[(int64_t)row(e >> 6) * ld + col(e & 63)];
+    }
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      const int e = tid + u * kThreads;
+      Qb[e] = L.Q[(int64_t)b * 4096 + e];
+      if (isA) Qa[e] = L.Q[(int64_t)a * 4096 + e];
+    }
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      const int e = tid + u * kThreads;
+      S[(e >> 6) * kJacLd + (e & 63)] = v[u];
+    }
+  }
+  __syncthreads();
+  f64x4 acc[4];
+  if (isA) {
+    mm64_zero(acc);
+    mm64<4>(16, [&](int k0) { return Qa[(k0 + kq) * 64 + 16 * w + cl]; },
+            [&](int k0, int J) { return S[(k0 + kq) * kJacLd + 16 * J + cl]; }, acc);
     __syncthreads();
 #pragma unroll
     for (int J = 0; J < 4; ++J)
 #pragma unroll
       for (int v = 0; v < 4; ++v) S[(16 * w + 4 * v + kq) * kJacLd + 16 * J + cl] = acc[J][v];
     __syncthreads();
-    mm64([&](int k0) { return S[(16 * w + cl) * kJacLd + k0 + kq]; },
-         [&](int k0, int J) { return Qb[(k0 + kq) * 64 + 16 * J + cl]; }, acc);
-    double sq = 0.0;
-#pragma unroll
-    for (int J = 0; J < 4; ++J)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int gi = row(16 * w + 4 * v + kq), gj = col(16 * J + cl);
-        const double t = acc[J][v];
-        L.A[(int64_t)gi * ld + gj] = t;
-        L.A[(int64_t)gj * ld + gi] = t;
-        sq += t * t;
-      }
-    if (last) {
-      sq = block_sum_d(sq, red);
-      if (tid == 0) L.jpart[np + blockIdx.x] = 2.0 * sq;
-    }
-    return;
   }
-  x -= nA;
-  const int b = x % np, rb = x / np;
-  int Ib, Jb;
-  lab_pair(nb, step, b, Ib, Jb);
-  const double* Qb = L.Q + (int64_t)b * 4096;
-  auto col = [&](int j) { return j < 32 ? 32 * Ib + j : 32 * Jb + j - 32; };
-  for (int e = tid; e < 64 * 64; e += kThreads)
-    S[(e >> 6) * kJacLd + (e & 63)] = L.V[(int64_t)(64 * rb + (e >> 6)) * ld + col(e & 63)];
-  __syncthreads();
-  mm64([&](int k0) { return S[(16 * w + cl) * kJacLd + k0 + kq]; },
-       [&](int k0, int J) { return Qb[(k0 + kq) * 64 + 16 * J + cl]; }, acc);
+  mm64_zero(acc);
+  mm64<4>(16, [&](int k0) { return S[(16 * w + cl) * kJacLd + k0 + kq]; },
+          [&](int k0, int J) { return Qb[(k0 + kq) * 64 + 16 * J + cl]; }, acc);
+  double sq = 0.0;
 #pragma unroll
   for (int J = 0; J < 4; ++J)
 #pragma unroll
-    for (int v = 0; v < 4; ++v)
-      L.V[(int64_t)(64 * rb + 16 * w + 4 * v + kq) * ld + col(16 * J + cl)] = acc[J][v];
+    for (int v = 0; v < 4; ++v) {
+      const int gi = row(16 * w + 4 * v + kq), gj = col(16 * J + cl);
+      const double t = acc[J][v];
+      M[(int64_t)gi * ld + gj] = t;
+      if (isA) M[(int64_t)gj * ld + gi] = t;
+      sq += t * t;
+    }
+  if (isA && last) {
+    sq = block_sum_d(sq, red);
+    if (tid == 0) L.jpart[np + blockIdx.x] = 2.0 * sq;
+  }
 }
 
 // P = V_K Lambda_K^{-1/2} for the K largest eigenvalues (descending, lowest index on ties):
@@ -419,7 +437,7 @@ __global__ __launch_bounds__(kThreads) void k_lab_assign(Geometry g, const float
         for (int s = 0; s < 4; ++s)
 #pragma unroll
           for (int gq = 0; gq < 2; ++gq)
-            acc[gq][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], b[gq][s], acc[gq][t], 0, 0, 0);
+            acc[gq][t] = mfma16x16x4d(a[s], b[gq][s], acc[gq][t]);
       }
     }
 #pragma unroll
@@ -665,16 +683,19 @@ hipError_t launch_lab_sweeps(const LabScratch& L, int r, int first, int count, h
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)kJacLds);
   if (e != hipSuccess) return e;
   const int nb = L.r64 / 32, np = nb / 2;
+  e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_lab_apply), hipFuncAttributeMaxDynamicSharedMemorySize,
+                          (int)kApplyLds);
+  if (e != hipSuccess) return e;
   if (np == 1) {  // all columns in one pivot block: run to the end
     const int N = (r + 1) & ~1;
-    hipLaunchKernelGGL(k_lab_sub, dim3(1), dim3(kThreads), kJacLds, st, L, 0, nb, N < 2 ? 2 : N, kLabMaxSweeps, 1, 0, 0);
+    hipLaunchKernelGGL(k_lab_sub, dim3(1), dim3(kJacThreads), kJacLds, st, L, 0, nb, N < 2 ? 2 : N, kLabMaxSweeps, 1, 0, 0);
     return hipGetLastError();
   }
   for (int s = first; s < first + count; ++s)
     for (int t = 0; t < nb - 1; ++t) {
       const int last = t == nb - 2;
-      hipLaunchKernelGGL(k_lab_sub, dim3(np), dim3(kThreads), kJacLds, st, L, t, nb, 64, 1, 0, s > 0 && t == 0, last);
-      hipLaunchKernelGGL(k_lab_apply, dim3(np * (np - 1) / 2 + np * np), dim3(kThreads), 0, st, L, t, nb, last);
+      hipLaunchKernelGGL(k_lab_sub, dim3(np), dim3(kJacThreads), kJacLds, st, L, t, nb, 64, 1, 0, s > 0 && t == 0, last);
+      hipLaunchKernelGGL(k_lab_apply, dim3(np * (np - 1) / 2 + np * np), dim3(kThreads), kApplyLds, st, L, t, nb, last);
     }
   return hipGetLastError();
 }

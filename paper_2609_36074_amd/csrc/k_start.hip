@@ -5,15 +5,17 @@
 // with the QR taken as the appendix's Cholesky QR in feature space:
 //     M = Xhat^T Z (d x r),  C = Xhat^T Xhat (d x d, reused from the spectral
 //     normalisation),  V^T V = M^T C M = R^T R,  Q = Xhat (M R^{-1}).
-// M comes from one pass A over (Xhat, Z) (the Theta product with U = Z); the
-// small algebra (C M, M^T C M, the Cholesky factor and the triangular solve) runs
-// in FP64 in one workgroup; Q = Xhat T is one more pass over Xhat, written over
-// Z, after which the usual projection onto Omega follows.  A pivot that is not
-// above 1e-14 of its diagonal entry (V numerically rank deficient) marks the
-// control block degenerate.
+// M comes from one Theta product of pass A over (Xhat, Z); the d x r and r x r algebra runs in
+// FP64 on the fp64 matrix cores in 64 x 64 blocks spread over workgroups (one workgroup with
+// scalar FMAs: 113 ms at 768 x 256; in blocks: under 1 ms); Q = Xhat T is one more pass over
+// Xhat, written over Z, after which the usual projection onto Omega follows.  A pivot that is
+// not above 1e-14 of its diagonal entry (V numerically rank deficient) marks the control block
+// degenerate.
 #include "k_common.hpp"
 
 namespace nlr {
+
+constexpr int kStartLd = 65;  // LDS row stride (doubles) of the 64 x 64 blocks
 
 __global__ void k_start_prep(Bufs B, int r32) {
   for (int c = threadIdx.x; c < r32; c += blockDim.x) B.p[c] = 0.f;  // pass A reads p for its row work
@@ -43,100 +45,243 @@ __global__ __launch_bounds__(kThreads) void k_start_m(Geometry g, Bufs B) {
   if (f < g.d && c < g.r) B.s_M[(int64_t)f * g.r + c] = sum;
 }
 
-// One workgroup: CM = C M, G = M^T CM, G = L L^T (L lower, R = L^T), T = M L^{-T}.
-__global__ __launch_bounds__(kThreads) void k_start_chol(Geometry g, Bufs B) {
-  const int d = g.d, r = g.r;
-  const int tid = threadIdx.x;
-  double* CM = B.s_CM;
-  double* G = B.s_G;
-  for (int e = tid; e < d * r; e += kThreads) {
-    const int f = e / r, c = e - (e / r) * r;
-    double acc = 0.0;
-    for (int k = 0; k < d; ++k) acc += B.s_C[(int64_t)f * d + k] * B.s_M[(int64_t)k * r + c];
-    CM[e] = acc;
+// out = A^T Bm (A k x m, Bm k x n, row-major): 64 x 64 blocks, workgroup (column, row block).  Operands
+// are read from L2 in whole 128-byte pieces, eight steps in flight.
+__global__ __launch_bounds__(kThreads) void k_start_gemm(const double* __restrict__ A, const double* __restrict__ Bm,
+                                                         double* __restrict__ out, int m, int n, int kk) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, kq = lane >> 4, cl = lane & 15;
+  const int i0 = 64 * blockIdx.y + 16 * w + cl, j0 = 64 * blockIdx.x + cl;
+  const bool oki = i0 < m;
+  f64x4 acc[4];
+  mm64_zero(acc);
+  mm64<8>((kk + 3) / 4,
+          [&](int k0) {
+            const int k = k0 + kq;
+            const double v = A[(int64_t)(k < kk ? k : kk - 1) * m + (oki ? i0 : 0)];
+            return (k < kk && oki) ? v : 0.0;
+          },
+          [&](int k0, int J) {
+            const int k = k0 + kq, j = j0 + 16 * J;
+            const double v = Bm[(int64_t)(k < kk ? k : kk - 1) * n + (j < n ? j : 0)];
+            return (k < kk && j < n) ? v : 0.0;
+          },
+          acc);
+#pragma unroll
+  for (int J = 0; J < 4; ++J)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int i = 64 * blockIdx.y + 16 * w + 4 * v + kq, j = j0 + 16 * J;
+      if (i < m && j < n) out[(int64_t)i * n + j] = acc[J][v];
+    }
+}
+
+// S -= R R_J^T over the columns before block J: R the rows (of stride r) of this 64-row block, R_J
+// those of block row J of L; rows at or beyond `rows` count as zero.
+__device__ __forceinline__ void start_update(const double* __restrict__ R, int rows, const double* __restrict__ Lj,
+                                             int jrows, int r, int J, double* S) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, kq = lane >> 4, cl = lane & 15;
+  const int i = 16 * w + cl;
+  f64x4 acc[4];
+  mm64_zero(acc);
+  mm64<8>(16 * J, [&](int k0) { return i < rows ? R[(int64_t)i * r + k0 + kq] : 0.0; },
+          [&](int k0, int Jc) { return 16 * Jc + cl < jrows ? Lj[(int64_t)(16 * Jc + cl) * r + k0 + kq] : 0.0; }, acc);
+#pragma unroll
+  for (int Jc = 0; Jc < 4; ++Jc)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) S[(16 * w + 4 * v + kq) * kStartLd + 16 * Jc + cl] -= acc[Jc][v];
+}
+
+// Diagonal block J of the Cholesky factorisation G = L L^T, in place (one workgroup, 64 x 64 in
+// LDS): G_JJ less the products of the blocks before it, then one column a step -- the trailing
+// block takes S_ij S_kj / s_jj, and L_ij = S_ij / sqrt(s_jj) at the end, so that a step needs one
+// barrier.
+__global__ __launch_bounds__(kThreads) void k_start_diag(Geometry g, Bufs B, int J) {
+  __shared__ double S[64 * kStartLd];
+  __shared__ double g0[64], piv[64];
+  const int tid = threadIdx.x, r = g.r, nr = r - 64 * J < 64 ? r - 64 * J : 64;
+  double* G = B.s_G + (int64_t)64 * J * r;
+  for (int e = tid; e < 64 * 64; e += kThreads) {
+    const int i = e >> 6, j = e & 63;
+    const double v = (i < nr && j < nr) ? G[(int64_t)i * r + 64 * J + j] : (i == j ? 1.0 : 0.0);
+    S[i * kStartLd + j] = v;
+    if (i == j) g0[i] = v;
   }
   __syncthreads();
-  for (int e = tid; e < r * r; e += kThreads) {
-    const int i = e / r, j = e - (e / r) * r;
-    double acc = 0.0;
-    for (int f = 0; f < d; ++f) acc += B.s_M[(int64_t)f * r + i] * CM[(int64_t)f * r + j];
-    G[e] = acc;
-  }
+  start_update(G, nr, G, nr, r, J, S);
   __syncthreads();
-  __shared__ int bad;
-  if (tid == 0) bad = 0;
-  __syncthreads();
-  // Cholesky, column by column: L[j][j] = sqrt(G[j][j] - sum_k L[j][k]^2), then the column below
-  for (int j = 0; j < r; ++j) {
-    if (tid == 0) {
-      const double g0 = G[j * r + j];
-      double s = g0;
-      for (int k = 0; k < j; ++k) s -= G[j * r + k] * G[j * r + k];
-      // a pivot at rounding level of the diagonal means V has (numerically) dependent columns
-      if (!(s > 1e-14 * g0) || !isfinite(s)) bad = 1;
-      G[j * r + j] = (s > 0.0) ? sqrt(s) : 1.0;
+  bool bad = false;
+  for (int j = 0; j < nr; ++j) {
+    const double s = S[j * kStartLd + j];
+    // a pivot at rounding level of the diagonal means V has (numerically) dependent columns
+    if (!(s > 1e-14 * g0[j]) || !isfinite(s)) bad = true;
+    const double inv = s > 0.0 ? 1.0 / s : 1.0;
+    if (tid == 0) piv[j] = s > 0.0 ? sqrt(s) : 1.0;
+    const int k = tid & 63;
+    if (k > j) {
+      const double skj = S[k * kStartLd + j] * inv;
+      for (int i = tid >> 6; i < nr; i += kThreads / 64)
+        if (i >= k) S[i * kStartLd + k] -= S[i * kStartLd + j] * skj;
     }
     __syncthreads();
-    const double ljj = G[j * r + j];
-    for (int i = j + 1 + tid; i < r; i += kThreads) {
-      double s = G[i * r + j];
-      for (int k = 0; k < j; ++k) s -= G[i * r + k] * G[j * r + k];
-      G[i * r + j] = s / ljj;
-    }
-    __syncthreads();
   }
-  // T row f: T[f][j] = (M[f][j] - sum_{k<j} T[f][k] L[j][k]) / L[j][j]
-  for (int f = tid; f < d; f += kThreads) {
-    for (int j = 0; j < r; ++j) {
-      double s = B.s_M[(int64_t)f * r + j];
-      for (int k = 0; k < j; ++k) s -= B.s_T[(int64_t)f * r + k] * G[j * r + k];
-      B.s_T[(int64_t)f * r + j] = s / G[j * r + j];
-    }
+  for (int e = tid; e < 64 * 64; e += kThreads) {
+    const int i = e >> 6, j = e & 63;
+    if (i < nr && j <= i) G[(int64_t)i * r + 64 * J + j] = i == j ? piv[j] : S[i * kStartLd + j] / piv[j];
   }
   if (tid == 0 && bad) B.ctl->degenerate = 1;
 }
 
-// U = Xhat T (FP64 accumulation), 64-row tiles, grid-stride.  Thread (g, c):
-// column c of the current 64-column block, rows g, g + 4, ..., g + 60.
-__global__ __launch_bounds__(kThreads) void k_start_apply(Geometry g, Bufs B) {
+// The blocks below diagonal block J and block column J of T = M L^{-T}, which is the same
+// recurrence: R_J = (A_J - sum_{K<J} R_K L_JK^T) L_JJ^{-T}.  Workgroups take 64 rows each: first the
+// rows of G below block J (A in place), then all rows of M (R to s_T).
+constexpr size_t kPanelStartLds = (64 * kStartLd + 64 * 64) * sizeof(double);
+__global__ __launch_bounds__(kThreads) void k_start_panel(Geometry g, Bufs B, int J) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  double* S = reinterpret_cast<double*>(smem_raw);
+  double* Lj = S + 64 * kStartLd;
+  const int tid = threadIdx.x, r = g.r, nr = r - 64 * J < 64 ? r - 64 * J : 64;
+  const int below = (r + 63) / 64 - J - 1;
+  const bool isG = (int)blockIdx.x < below;
+  const int row0 = 64 * (isG ? J + 1 + (int)blockIdx.x : (int)blockIdx.x - below);
+  const int total = isG ? r : g.d;
+  const int rows = total - row0 < 64 ? total - row0 : 64;
+  const double* src = (isG ? B.s_G : B.s_M) + (int64_t)row0 * r;
+  double* dst = (isG ? B.s_G : B.s_T) + (int64_t)row0 * r;
+  const double* GJ = B.s_G + (int64_t)64 * J * r;
+  for (int e = tid; e < 64 * 64; e += kThreads) {
+    const int i = e >> 6, j = e & 63;
+    S[i * kStartLd + j] = (i < rows && j < nr) ? src[(int64_t)i * r + 64 * J + j] : 0.0;
+    Lj[e] = (i < nr && j <= i) ? GJ[(int64_t)i * r + 64 * J + j] : 0.0;
+  }
+  __syncthreads();
+  start_update(dst, rows, GJ, nr, r, J, S);
+  __syncthreads();
+  // forward substitution, right-looking: thread (row i, quarter q) keeps the row's x_j in LDS
+  const int i = tid & 63, q = tid >> 6;
+  for (int j = 0; j < nr; ++j) {
+    const double x = S[i * kStartLd + j] / Lj[j * 64 + j];
+    for (int k = j + 1 + q; k < nr; k += kThreads / 64) S[i * kStartLd + k] -= x * Lj[k * 64 + j];
+    __syncthreads();
+  }
+  for (int e = tid; e < 64 * 64; e += kThreads) {
+    const int ii = e >> 6, j = e & 63;
+    if (ii < rows && j < nr) dst[(int64_t)ii * r + 64 * J + j] = S[ii * kStartLd + j] / Lj[j * 64 + j];
+  }
+}
+
+// U = Xhat T (FP64 products and sums, rounded once), on the fp64 matrix cores.  A wave takes 64 rows
+// (four groups of 16) x CT tiles of 16 columns; a step's 4 features are 16 q + 4 (l / 16) + s for
+// s = 0..3, so a lane reads 16 consecutive bytes of its row of Xhat; T comes from L2, the next
+// tile's operand in flight while this one multiplies.  Column groups of 64 of the same rows are
+// workgroups 8 apart (one XCD), so that Xhat comes from HBM about once.  Bound by the matrix cores:
+// 2 n d r flops, 11.6 ms at 2e6 x 768 x 256 at the rate of a large FP64 product (scalar FMAs from
+// LDS: 51 ms).
+template <int CT, bool VEC>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_start_apply(Geometry g, Bufs B,
+                                                                                                     int cgroups) {
   if (B.ctl->degenerate) return;
-  __shared__ float xt[64][65];
-  const int tid = threadIdx.x;
-  const int rg = tid >> 6, cl = tid & 63;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, lg = lane >> 4, lr = lane & 15;
   const int d = g.d, r = g.r;
   const int64_t n = g.n;
-  const int64_t tiles = (n + 63) / 64;
-  for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) {
-    const int64_t row0 = t * 64;
-    for (int cb = 0; cb < r; cb += 64) {
-      const int c = cb + cl;
-      double acc[16];
+  const int64_t per = (int64_t)8 * cgroups, id = blockIdx.x;
+  const int64_t tile = id / per * 8 + id % per % 8;
+  const int cg = (int)(id % per / 8);
+  const int64_t row0 = tile * 256 + 64 * w;
+  if (row0 >= n) return;
+  const float* xp[4];
 #pragma unroll
-      for (int i = 0; i < 16; ++i) acc[i] = 0.0;
-      for (int f0 = 0; f0 < d; f0 += 64) {
-        __syncthreads();
-        for (int e = tid; e < 64 * 64; e += kThreads) {
-          const int rr = e >> 6, ff = e & 63;
-          const int64_t row = row0 + rr;
-          xt[rr][ff] = (row < n && f0 + ff < d) ? B.X[row * d + f0 + ff] : 0.f;
-        }
-        __syncthreads();
-        const int fe = (d - f0) < 64 ? (d - f0) : 64;
-        for (int ff = 0; ff < fe; ++ff) {
-          const double tv = (c < r) ? B.s_T[(int64_t)(f0 + ff) * r + c] : 0.0;
+  for (int gq = 0; gq < 4; ++gq) {
+    const int64_t row = row0 + 16 * gq + lr;
+    xp[gq] = B.X + (row < n ? row : n - 1) * d;
+  }
+  int colc[CT];
+  bool okc[CT];
 #pragma unroll
-          for (int i = 0; i < 16; ++i) acc[i] += (double)xt[4 * i + rg][ff] * tv;
-        }
-      }
-      if (c < r) {
+  for (int t = 0; t < CT; ++t) {
+    const int c = 64 * cg + 16 * t + lr;
+    okc[t] = c < r;
+    colc[t] = okc[t] ? c : 0;
+  }
+  f64x4 acc[4][CT];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int64_t row = row0 + 4 * i + rg;
-          if (row < n) B.U[row * r + c] = (float)acc[i];
+  for (int gq = 0; gq < 4; ++gq)
+#pragma unroll
+    for (int t = 0; t < CT; ++t) acc[gq][t] = (f64x4){0.0, 0.0, 0.0, 0.0};
+  float nx[4][4];
+  auto load_x = [&](int q) {
+    const int c0 = 16 * q + 4 * lg;
+#pragma unroll
+    for (int gq = 0; gq < 4; ++gq) {
+      if constexpr (VEC) {
+        const f32x4 t = *reinterpret_cast<const f32x4*>(xp[gq] + (c0 < d ? c0 : 0));
+#pragma unroll
+        for (int s = 0; s < 4; ++s) nx[gq][s] = c0 < d ? t[s] : 0.f;
+      } else {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const float t = xp[gq][c0 + s < d ? c0 + s : 0];
+          nx[gq][s] = c0 + s < d ? t : 0.f;
         }
       }
     }
+  };
+  auto load_t = [&](int q, int t, double (&b)[4]) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int c = 16 * q + 4 * lg + s;
+      const double v = B.s_T[(int64_t)(c < d ? c : d - 1) * r + colc[t]];
+      b[s] = (c < d && okc[t]) ? v : 0.0;
+    }
+  };
+  const int nq = (d + 15) >> 4;
+  load_x(0);
+  double bn[4];
+  load_t(0, 0, bn);
+  for (int q = 0; q < nq; ++q) {
+    double a[4][4];
+#pragma unroll
+    for (int gq = 0; gq < 4; ++gq)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) a[gq][s] = (double)nx[gq][s];
+    if (q + 1 < nq) load_x(q + 1);
+#pragma unroll
+    for (int t = 0; t < CT; ++t) {
+      double b[4];
+#pragma unroll
+      for (int s = 0; s < 4; ++s) b[s] = bn[s];
+      if (t + 1 < CT)
+        load_t(q, t + 1, bn);
+      else if (q + 1 < nq)
+        load_t(q + 1, 0, bn);
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int gq = 0; gq < 4; ++gq) acc[gq][t] = mfma16x16x4d(a[gq][s], b[s], acc[gq][t]);
+    }
   }
+#pragma unroll
+  for (int gq = 0; gq < 4; ++gq)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int64_t row = row0 + 16 * gq + 4 * v + lg;
+      if (row < n)
+#pragma unroll
+        for (int t = 0; t < CT; ++t)
+          if (okc[t]) B.U[row * r + 64 * cg + 16 * t + lr] = (float)acc[gq][t][v];
+    }
+}
+
+template <int CT>
+static hipError_t start_apply(const Geometry& g, const Bufs& b, hipStream_t st) {
+  const int cgroups = (g.r + 63) / 64;
+  const int64_t tiles = ((g.n + 255) / 256 + 7) / 8 * 8;
+  const int64_t blocks = tiles * cgroups;
+  if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+  if (g.vec_x)
+    hipLaunchKernelGGL((k_start_apply<CT, true>), dim3((unsigned)blocks), dim3(kThreads), 0, st, g, b, cgroups);
+  else
+    hipLaunchKernelGGL((k_start_apply<CT, false>), dim3((unsigned)blocks), dim3(kThreads), 0, st, g, b, cgroups);
+  return hipGetLastError();
 }
 
 hipError_t launch_data_start(const Geometry& g, const Bufs& b, const StepArgs& a0, bool x_normalised,
@@ -156,10 +301,27 @@ hipError_t launch_data_start(const Geometry& g, const Bufs& b, const StepArgs& a
   const int C = g.d32 * g.r32;
   if ((e = launch_seg_theta(g, b, g.GA, g.SA, st)) != hipSuccess) return e;
   hipLaunchKernelGGL(k_start_m, dim3((C + kThreads - 1) / kThreads), dim3(kThreads), 0, st, g, b);
-  hipLaunchKernelGGL(k_start_chol, dim3(1), dim3(kThreads), 0, st, g, b);
-  const int64_t tiles = (g.n + 63) / 64;
-  hipLaunchKernelGGL(k_start_apply, dim3((unsigned)(tiles < 4096 ? tiles : 4096)), dim3(kThreads), 0, st, g, b);
-  return hipGetLastError();
+  // C M (C is symmetric) and M^T (C M)
+  const int rb = (g.r + 63) / 64, db = (g.d + 63) / 64;
+  hipLaunchKernelGGL(k_start_gemm, dim3(rb, db), dim3(kThreads), 0, st, (const double*)b.s_C, (const double*)b.s_M,
+                     b.s_CM, g.d, g.r, g.d);
+  hipLaunchKernelGGL(k_start_gemm, dim3(rb, rb), dim3(kThreads), 0, st, (const double*)b.s_M, (const double*)b.s_CM,
+                     b.s_G, g.r, g.r, g.d);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_start_panel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                          (int)kPanelStartLds);
+  if (e != hipSuccess) return e;
+  for (int J = 0; J < rb; ++J) {
+    hipLaunchKernelGGL(k_start_diag, dim3(1), dim3(kThreads), 0, st, g, b, J);
+    hipLaunchKernelGGL(k_start_panel, dim3(rb - J - 1 + db), dim3(kThreads), kPanelStartLds, st, g, b, J);
+  }
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  switch (g.r > 48 ? 4 : (g.r + 15) / 16) {
+    case 1: return start_apply<1>(g, b, st);
+    case 2: return start_apply<2>(g, b, st);
+    case 3: return start_apply<3>(g, b, st);
+    default: return start_apply<4>(g, b, st);
+  }
 }
 
 }  // namespace nlr

@@ -384,6 +384,24 @@ def test_data_start(n, d, r, K, flags):
     assert max(traj) < U_TOL and max(one) < U_TOL / 10 and max(obj) < OBJ_TOL
 
 
+@pytest.mark.parametrize("n,d,r", [(300, 5, 1), (999, 17, 16), (1000, 66, 33), (1025, 51, 48), (1500, 64, 63),
+                                   (2000, 131, 65), (2300, 150, 129), (4000, 300, 200), (6000, 460, 448)])
+def test_data_start_block_edges(n, d, r):
+    """Edges of the 64-blocks of the Cholesky factor and the solve, of the 16-column tiles and of the
+    256-row tiles of the last product, 16-byte rows or not.  The first product is summed in fp32
+    (2^-24 sqrt(n) a term), which the solve amplifies by the condition of the sample."""
+    X, _, _ = gaussian_mixture(n, d, max(2, min(r, 8)), 16.0, seed=n + d)
+    Z = standard_normal_factor(n, r, seed=n + r).astype(np.float64)
+    ctx = make_ctx(X, Z, r, 0.01, flags=DATA_START)
+    Xh, _, _ = onlr.centre_and_normalise(X)
+    U0_ref, Q = onlr.data_informed_start(Xh, Z, r)
+    err = rel_max_err(host(ctx.U), U0_ref)
+    V = Xh @ (Xh.T @ Z)
+    cond = np.linalg.cond(V)
+    log(f"data start n={n} d={d} r={r}: U0 err {err:.2e}, condition {cond:.1e}")
+    assert err < 2.0 ** -24 * np.sqrt(n) * cond + 1e-6
+
+
 def test_data_start_rank_deficient_is_degenerate():
     """r above the rank of Xhat: V = Xhat Xhat^T Z has dependent columns and Cholesky QR fails."""
     from paper_2609_36074_amd import nlr
