@@ -132,6 +132,16 @@ __device__ __forceinline__ f64x4 mfma16x16x4d(double a, double b, f64x4 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
+// v_mfma_f64_4x4x4f64: four independent 4 x 4 blocks, block b = (l >> 2) & 3; lane l supplies
+// A_b[l % 4][l / 16] and B_b[l / 16][l % 4] and holds D_b[l / 16][l % 4].  It sustains 68 TFLOP/s
+// on the whole chip where the 16x16x4 form stops at 47 (both measured; 35 with one wave a SIMD),
+// so the long FP64 products use it: with A in the 16x16x4 layout (row l % 16) and B rotated by 4 R
+// columns inside its 16 (column (l + 4 R) % 16), result R = 0..3 of a 16 x 16 tile is
+// D[4 b + l / 16][4 ((b + R) % 4) + l % 4].
+__device__ __forceinline__ double mfma4x4x4d(double a, double b, double c) {
+  return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
+}
+
 // acc += A B over `steps` steps of 4 for a 64 x 64 result of one workgroup: wave w holds rows
 // 16 w .. 16 w + 15 in four column tiles.  fa(k0): this lane's A element of row 16 w + lane % 16,
 // k = k0 + lane / 16; fb(k0, J): its B element of k = k0 + lane / 16, column 16 J + lane % 16.

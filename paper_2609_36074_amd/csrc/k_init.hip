@@ -9,7 +9,7 @@
 // power iterations on C, and the Rayleigh quotient of the final unit vector is
 // lambda_max.  Appendix D notes C is reused from this normalisation by the
 // data-informed initialisation.
-#include "nlr_internal.hpp"
+#include "k_common.hpp"
 
 namespace nlr {
 
@@ -36,6 +36,24 @@ __global__ void k_ctl_init(Bufs B, float gamma_f) {
 
 __global__ void k_clear_stop(Bufs B) {
   if (threadIdx.x == 0 && blockIdx.x == 0) B.ctl->stop = 0;
+}
+
+// Sum of p[k * stride] over k = first, first + step, ... below count, UN loads in flight, added in
+// order.
+template <int UN>
+__device__ __forceinline__ double strided_sum(const double* __restrict__ p, int64_t stride, int first, int step,
+                                              int count) {
+  double t = 0.0;
+  int k = first;
+  for (; k + (UN - 1) * step < count; k += UN * step) {
+    double v[UN];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) v[u] = p[(int64_t)(k + u * step) * stride];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) t += v[u];
+  }
+  for (; k < count; k += step) t += p[(int64_t)k * stride];
+  return t;
 }
 
 // Column sums of X over row chunks (FP64).  Threads map to (column, row offset).
@@ -88,12 +106,20 @@ __global__ __launch_bounds__(kThreads) void k_colsum(Geometry g, Bufs B) {
   }
 }
 
+// Means from the chunk sums: 16 columns a workgroup, 16 groups of threads over the chunks (eight
+// loads in flight), added in a fixed order.  One thread a column over all 512 chunks took 95 to
+// 206 us, a dependent load at a time.
 __global__ __launch_bounds__(kThreads) void k_colmean(Geometry g, Bufs B) {
-  const int j = blockIdx.x * kThreads + threadIdx.x;
-  if (j >= g.d) return;
-  double t = 0.0;
-  for (int gx = 0; gx < g.GI; ++gx) t += B.i_colsum[(int64_t)gx * g.d + j];
-  B.i_xbar[j] = t / (double)g.n;
+  __shared__ double red[kThreads];
+  const int tid = threadIdx.x, cl = tid & 15, gq = tid >> 4;
+  const int j = blockIdx.x * 16 + cl;
+  red[tid] = j < g.d ? strided_sum<8>(B.i_colsum + j, g.d, gq, 16, g.GI) : 0.0;
+  __syncthreads();
+  if (tid < 16 && j < g.d) {
+    double t = 0.0;
+    for (int k = 0; k < 16; ++k) t += red[16 * k + cl];
+    B.i_xbar[j] = t / (double)g.n;
+  }
 }
 
 // Partial centred Gram blocks on the fp64 matrix cores (v_mfma_f64_16x16x4f64):
@@ -105,7 +131,6 @@ __global__ __launch_bounds__(kThreads) void k_colmean(Geometry g, Bufs B) {
 // holds result element (4 v + l / 16, l % 16) of a tile in entry v.  The blocks
 // below the diagonal are not formed (the sum is symmetric; k_gram_reduce reads
 // their mirror).
-typedef double f64x4_t __attribute__((ext_vector_type(4)));
 static_assert(kThreads == 256, "k_gram stages a 32 x 64 operand as 8 elements per thread of 4 waves");
 __global__ __launch_bounds__(kThreads) void k_gram(const float* __restrict__ M, int64_t n, int d,
                                                    const double* __restrict__ mean, double* __restrict__ part) {
@@ -121,9 +146,9 @@ __global__ __launch_bounds__(kThreads) void k_gram(const float* __restrict__ M, 
   const int64_t r1 = (int64_t)(blockIdx.x + 1) * n / gridDim.x;
   const int lane = tid & 63, w = tid >> 6;
   const int kq = lane >> 4, cl = lane & 15;
-  f64x4_t acc[4];
+  f64x4 acc[4];
 #pragma unroll
-  for (int J = 0; J < 4; ++J) acc[J] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+  for (int J = 0; J < 4; ++J) acc[J] = (f64x4){0.0, 0.0, 0.0, 0.0};
   // Rounds of 32 rows.  The round's centred values of the block's 64 row features
   // and 64 column features are formed once in FP64 by the workgroup and staged in
   // LDS (rows padded to 80 doubles, so that the 32 lanes of a read pass meet all 64
@@ -180,142 +205,296 @@ __global__ __launch_bounds__(kThreads) void k_gram(const float* __restrict__ M, 
     }
 }
 
-// C = the sum of the chunks' partials in chunk order; entries below the block
-// diagonal from the mirrored entry.
+// C = the sum of the chunks' partials; entries below the block diagonal from the mirrored entry.
+// Small matrices share an entry's chunks among 16 groups of threads (EPG = 16 entries a workgroup),
+// added in a fixed order: one thread an entry left d = 32 on four workgroups with 256 dependent
+// loads each (63 us).
+template <int EPG>
 __global__ __launch_bounds__(kThreads) void k_gram_reduce(Geometry g, Bufs B) {
+  __shared__ double red[kThreads];
+  constexpr int NG = kThreads / EPG;
   const int64_t dd = (int64_t)g.d * g.d;
-  const int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (e >= dd) return;
-  const int i = (int)(e / g.d), j = (int)(e - (int64_t)i * g.d);
-  const int64_t src = (i / 64 > j / 64) ? (int64_t)j * g.d + i : e;
+  const int cl = threadIdx.x % EPG, gq = threadIdx.x / EPG;
+  const int64_t e = (int64_t)blockIdx.x * EPG + cl;
   double t = 0.0;
-  for (int gx = 0; gx < g.GG; ++gx) t += B.i_gram[(int64_t)gx * dd + src];
-  B.i_C[e] = t;
-}
-
-// scal[slot] = 1 / trace(M) (0 when the trace is not positive).
-__global__ __launch_bounds__(kThreads) void k_trace(Geometry g, const double* __restrict__ M, double* scal, int slot) {
-  __shared__ double red[8];
-  double t = 0.0;
-  for (int i = threadIdx.x; i < g.d; i += kThreads) t += M[(int64_t)i * g.d + i];
-  t = block_sum_d(t, red);
-  if (threadIdx.x == 0) scal[slot] = (t > 0.0 && isfinite(t)) ? 1.0 / t : 0.0;
-}
-
-// out = (in * scal[slot])^2 for a symmetric d x d matrix (32 x 32 tiles).
-__global__ __launch_bounds__(kThreads) void k_square(Geometry g, const double* __restrict__ in, double* __restrict__ out,
-                                                     const double* scal, int slot) {
-  __shared__ double As[32][33];
-  __shared__ double Bs[32][33];
-  const int d = g.d;
-  const int tid = threadIdx.x;
-  const int ty = tid >> 3, tx = tid & 7;
-  const int bi = blockIdx.y, bj = blockIdx.x;
-  const double s = scal[slot];
-  double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int k0 = 0; k0 < d; k0 += 32) {
+  if (e < dd) {
+    const int i = (int)(e / g.d), j = (int)(e - (int64_t)i * g.d);
+    const int64_t src = (i / 64 > j / 64) ? (int64_t)j * g.d + i : e;
+    t = strided_sum<8>(B.i_gram + src, dd, gq, NG, g.GG);
+  }
+  if constexpr (NG > 1) {
+    red[threadIdx.x] = t;
     __syncthreads();
-    for (int v = tid; v < 32 * 32; v += kThreads) {
-      const int rr = v >> 5, cc = v & 31;
-      const int ia = bi * 32 + rr, ka = k0 + cc;
-      const int kb = k0 + rr, jb = bj * 32 + cc;
-      As[rr][cc] = (ia < d && ka < d) ? in[(int64_t)ia * d + ka] * s : 0.0;
-      Bs[rr][cc] = (kb < d && jb < d) ? in[(int64_t)kb * d + jb] * s : 0.0;
-    }
-    __syncthreads();
-#pragma unroll 8
-    for (int k = 0; k < 32; ++k) {
-      const double a = As[ty][k];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) acc[e] += a * Bs[k][4 * tx + e];
+    if (gq == 0) {
+      t = 0.0;
+      for (int k = 0; k < NG; ++k) t += red[EPG * k + cl];
     }
   }
-  const int ia = bi * 32 + ty;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const int jb = bj * 32 + 4 * tx + e;
-    if (ia < d && jb < d) out[(int64_t)ia * d + jb] = acc[e];
-  }
+  if (gq == 0 && e < dd) B.i_C[e] = t;
 }
 
-// Power iterations on C from the dominant column of Bf; a = sqrt(Rayleigh quotient).
-__global__ __launch_bounds__(kThreads) void k_power(Geometry g, Bufs B, const double* __restrict__ Bf) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  double* v = reinterpret_cast<double*>(smem_raw);  // d
-  double* w = v + g.d;                               // d
-  __shared__ double red[8];
-  __shared__ double sh[2];
-  __shared__ int shi[1];
-  const int d = g.d;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const double* C = B.i_C;
-  // start column: largest diagonal of Bf, lowest index on ties
+// Up to 64 features: the whole power method in one workgroup of 16 waves, the matrix (zero padded to
+// D = 16, 32 or 64) in LDS.  A squaring is one 16 x 16 tile a wave on the fp64 matrix cores (the
+// matrix is symmetric, so both operands are read by rows), its trace summed on the way; then the
+// power iterations on C, 16 threads a row.  As 20 squarings, 21 traces and the iteration in launches
+// of their own: 210 us at d = 32, nearly all of it latency.
+template <int D>
+__global__ __launch_bounds__(1024) void k_power_small(Geometry g, Bufs B) {
+  constexpr int LD = D + 2, NT = D / 16;
+  __shared__ double C[D * LD], M[D * LD];
+  __shared__ double v[D], y[D], part[16];
+  __shared__ double sc;
+  __shared__ int j0;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, d = g.d;
+  for (int e = tid; e < D * D; e += 1024) {
+    const int i = e / D, j = e % D;
+    const double t = (i < d && j < d) ? B.i_C[i * d + j] : 0.0;
+    C[i * LD + j] = t;
+    M[i * LD + j] = t;
+  }
+  __syncthreads();
+  for (int k = 0; k < kSquarings; ++k) {
+    if (tid < 64) {
+      double t = tid < D ? M[tid * LD + tid] : 0.0;
+      for (int m = 32; m >= 1; m >>= 1) t += shfl_xor_d(t, m);
+      if (tid == 0) sc = (t > 0.0 && isfinite(t)) ? 1.0 / t : 0.0;
+    }
+    __syncthreads();
+    const double s = sc;
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    const int ti = w / NT, tj = w % NT, kq = lane >> 4, cl = lane & 15;
+    if (w < NT * NT)
+#pragma unroll
+      for (int st = 0; st < D / 4; ++st) {
+        const int row = (4 * st + kq) * LD;
+        const double a = M[row + 16 * ti + cl] * s;
+#pragma unroll
+        for (int R = 0; R < 4; ++R) acc[R] = mfma4x4x4d(a, M[row + 16 * tj + ((cl + 4 * R) & 15)] * s, acc[R]);
+      }
+    __syncthreads();
+    if (w < NT * NT) {
+      const int bl = (lane >> 2) & 3;
+#pragma unroll
+      for (int R = 0; R < 4; ++R)
+        M[(16 * ti + 4 * bl + kq) * LD + 16 * tj + 4 * ((bl + R) & 3) + (lane & 3)] = acc[R];
+    }
+    __syncthreads();
+  }
+  // start column: largest diagonal entry, lowest index on ties
   if (tid == 0) {
     double best = -1.0;
     int arg = 0;
-    for (int j = 0; j < d; ++j) {
-      const double x = Bf[(int64_t)j * d + j];
-      if (x > best) {
-        best = x;
+    for (int j = 0; j < d; ++j)
+      if (M[j * LD + j] > best) {
+        best = M[j * LD + j];
         arg = j;
       }
-    }
-    shi[0] = arg;
+    j0 = arg;
   }
   __syncthreads();
-  const int j0 = shi[0];
-  double nn = 0.0;
-  for (int i = tid; i < d; i += kThreads) {
-    v[i] = Bf[(int64_t)i * d + j0];
-    nn += v[i] * v[i];
-  }
-  nn = block_sum_d(nn, red);
-  if (tid == 0) sh[0] = nn;
-  __syncthreads();
-  double inv = (sh[0] > 0.0) ? 1.0 / sqrt(sh[0]) : 0.0;
-  for (int i = tid; i < d; i += kThreads) v[i] *= inv;
+  if (tid < D) y[tid] = M[tid * LD + j0];
   __syncthreads();
   double lam = 0.0;
   for (int it = 0; it <= kPowerIters; ++it) {
-    // w = C v, one wave per row (four rows of a wave at a time, their loads in
-    // flight together), lanes stride the columns
-    for (int i0 = 4 * wave; i0 < d; i0 += 16) {
-      double t[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll 4
-      for (int j = lane; j < d; j += 64) {
-        const double vj = v[j];
+    // v = y / |y|, each wave for itself
+    const double yl = lane < D ? y[lane] : 0.0;
+    double nn = yl * yl;
+    for (int m = 32; m >= 1; m >>= 1) nn += shfl_xor_d(nn, m);
+    const double vl = nn > 0.0 ? yl / sqrt(nn) : 0.0;
+    if (w == 0 && lane < D) v[lane] = vl;
+    __syncthreads();
+    const int row = tid >> 4, c0 = tid & 15;  // 16 threads a row
+    if (row < D) {
+      double t = 0.0;
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-          if (i0 + q < d) t[q] += C[(int64_t)(i0 + q) * d + j] * vj;
-      }
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        double tq = t[q];
-        for (int m = 32; m >= 1; m >>= 1) tq += shfl_xor_d(tq, m);
-        if (lane == 0 && i0 + q < d) w[i0 + q] = tq;
-      }
+      for (int j = 0; j < D / 16; ++j) t += C[row * LD + c0 + 16 * j] * v[c0 + 16 * j];
+      t = row16_sum_d(t);
+      if (c0 == 0) y[row] = t;
     }
     __syncthreads();
-    double vw = 0.0, ww = 0.0;
-    for (int i = tid; i < d; i += kThreads) {
-      vw += v[i] * w[i];
-      ww += w[i] * w[i];
+    if (it == kPowerIters) {  // Rayleigh quotient of the last unit vector
+      double q = lane < D ? vl * y[lane] : 0.0;
+      for (int m = 32; m >= 1; m >>= 1) q += shfl_xor_d(q, m);
+      lam = q;
     }
-    vw = block_sum_d(vw, red);
-    ww = block_sum_d(ww, red);
-    if (tid == 0) {
-      sh[0] = vw;
-      sh[1] = ww;
-    }
-    __syncthreads();
-    lam = sh[0];  // Rayleigh quotient of the unit vector v
-    if (it == kPowerIters) break;
-    inv = (sh[1] > 0.0) ? 1.0 / sqrt(sh[1]) : 0.0;
-    for (int i = tid; i < d; i += kThreads) v[i] = w[i] * inv;
-    __syncthreads();
   }
   if (tid == 0) {
+    const double a = (lam > 0.0) ? sqrt(lam) : 0.0;
+    B.ctl->spectral_a = a;
+    if (!(a > 0.0) || !isfinite(a)) B.ctl->degenerate = 1;
+  }
+}
+
+// out = (in s)^2 for a symmetric d x d matrix, s = 1 / tr in (0 when the trace is not positive),
+// above 64 features: 64 x 64 blocks on the fp64 matrix cores, those on and above the diagonal
+// (blockIdx.x), each written with its mirror; a wave takes a quarter (32 x 32).  Both operands are
+// rows of the input, staged 32 rows at a time.  A diagonal block also writes its part of the trace,
+// from which the next launch forms its s.  (A thread a row and scalar FMAs, with a launch for each
+// trace: 127 us a squaring at d = 768.)
+constexpr int kSqMax = 64;  // diagonal blocks at most (d <= 4096)
+__global__ __launch_bounds__(kThreads) void k_square(Geometry g, const double* __restrict__ in, double* __restrict__ out,
+                                                     const double* __restrict__ tr_in, double* __restrict__ tr_out) {
+  __shared__ double xs[2][32][80];
+  __shared__ double red[8];
+  const int d = g.d, tid = threadIdx.x, lane = tid & 63, w = tid >> 6, kq = lane >> 4, cl = lane & 15;
+  const int nb = (d + 63) / 64;
+  int bp = blockIdx.x, bi = 0;
+  while (bp >= nb - bi) {
+    bp -= nb - bi;
+    ++bi;
+  }
+  const int bj = bi + bp;
+  const bool same = bi == bj;
+  double tr = 0.0;
+  if (tr_in) {
+    for (int k = 0; k < nb; ++k) tr += tr_in[k];
+  } else {
+    for (int k = tid; k < d; k += kThreads) tr += in[(int64_t)k * d + k];
+    tr = block_sum_d(tr, red);
+    if (tid == 0) red[4] = tr;
+    __syncthreads();
+    tr = red[4];
+    __syncthreads();
+  }
+  const double s = (tr > 0.0 && isfinite(tr)) ? 1.0 / tr : 0.0;
+  const int wi = 32 * (w >> 1), wj = 32 * (w & 1);
+  double acc[2][2][4];
+#pragma unroll
+  for (int I = 0; I < 2; ++I)
+#pragma unroll
+    for (int J = 0; J < 2; ++J)
+#pragma unroll
+      for (int R = 0; R < 4; ++R) acc[I][J][R] = 0.0;
+  const int sf = tid & 63, sr = tid >> 6;
+  const int fa = 64 * bi + sf, fb = 64 * bj + sf;
+  double ra[8], rb[8];
+  auto load_round = [&](int k0) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int k = k0 + sr + 4 * q;
+      const int64_t row = (int64_t)(k < d ? k : 0) * d;
+      ra[q] = (k < d && fa < d) ? in[row + (fa < d ? fa : 0)] : 0.0;
+      rb[q] = (k < d && fb < d) ? in[row + (fb < d ? fb : 0)] : 0.0;
+    }
+  };
+  load_round(0);
+  for (int k0 = 0; k0 < d; k0 += 32) {
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      xs[0][sr + 4 * q][sf] = ra[q] * s;
+      xs[1][sr + 4 * q][sf] = rb[q] * s;
+    }
+    __syncthreads();
+    if (k0 + 32 < d) load_round(k0 + 32);
+#pragma unroll
+    for (int st = 0; st < 8; ++st) {
+      const int row = 4 * st + kq;
+      double a[2];
+#pragma unroll
+      for (int I = 0; I < 2; ++I) a[I] = xs[0][row][wi + 16 * I + cl];
+#pragma unroll
+      for (int J = 0; J < 2; ++J)
+#pragma unroll
+        for (int R = 0; R < 4; ++R) {
+          const double b = xs[1][row][wj + 16 * J + ((cl + 4 * R) & 15)];
+#pragma unroll
+          for (int I = 0; I < 2; ++I) acc[I][J][R] = mfma4x4x4d(a[I], b, acc[I][J][R]);
+        }
+    }
+  }
+  const int bl = (lane >> 2) & 3;
+  double t = 0.0;
+#pragma unroll
+  for (int I = 0; I < 2; ++I)
+#pragma unroll
+    for (int J = 0; J < 2; ++J)
+#pragma unroll
+      for (int R = 0; R < 4; ++R) {
+        const int ia = 64 * bi + wi + 16 * I + 4 * bl + kq;
+        const int jb = 64 * bj + wj + 16 * J + 4 * ((bl + R) & 3) + (lane & 3);
+        if (ia < d && jb < d) {
+          out[(int64_t)ia * d + jb] = acc[I][J][R];
+          if (!same) out[(int64_t)jb * d + ia] = acc[I][J][R];
+          if (ia == jb) t += acc[I][J][R];
+        }
+      }
+  if (same) {
+    t = block_sum_d(t, red);
+    if (tid == 0) tr_out[bi] = t;
+  }
+}
+
+// The power iterations above 64 features, the products spread over workgroups.  x_0 is the column of
+// Bf with the largest diagonal entry (lowest index on ties); launch `it` forms v = x / |x| (every
+// workgroup for itself, in the same order) and writes y = C v, the next launch's x; a wave takes a
+// row of C at a time.
+__global__ __launch_bounds__(kThreads) void k_power_mv(Geometry g, const double* __restrict__ C,
+                                                       const double* __restrict__ Bf, const double* __restrict__ x,
+                                                       double* __restrict__ y) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  double* v = reinterpret_cast<double*>(smem_raw);  // d
+  __shared__ double red[8];
+  __shared__ double sh;
+  __shared__ double bv[kThreads];
+  __shared__ int bk[kThreads];
+  const int d = g.d, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  int j0 = 0;
+  if (!x) {
+    double best = -1.0;
+    int arg = d;
+    for (int j = tid; j < d; j += kThreads) {
+      const double t = Bf[(int64_t)j * d + j];
+      if (t > best) {
+        best = t;
+        arg = j;
+      }
+    }
+    bv[tid] = best;
+    bk[tid] = arg;
+    __syncthreads();
+    for (int h = kThreads / 2; h >= 1; h >>= 1) {
+      if (tid < h && (bv[tid + h] > bv[tid] || (bv[tid + h] == bv[tid] && bk[tid + h] < bk[tid]))) {
+        bv[tid] = bv[tid + h];
+        bk[tid] = bk[tid + h];
+      }
+      __syncthreads();
+    }
+    j0 = bk[0] < d ? bk[0] : 0;
+  }
+  double nn = 0.0;
+  for (int i = tid; i < d; i += kThreads) {
+    const double t = x ? x[i] : Bf[(int64_t)i * d + j0];
+    v[i] = t;
+    nn += t * t;
+  }
+  nn = block_sum_d(nn, red);
+  if (tid == 0) sh = nn > 0.0 ? 1.0 / sqrt(nn) : 0.0;
+  __syncthreads();
+  const double inv = sh;
+  const int rows = gridDim.x * (kThreads / 64);
+  for (int i = blockIdx.x * (kThreads / 64) + w; i < d; i += rows) {
+    double t = 0.0;
+#pragma unroll 4
+    for (int j = lane; j < d; j += 64) t += C[(int64_t)i * d + j] * (v[j] * inv);
+    for (int m = 32; m >= 1; m >>= 1) t += shfl_xor_d(t, m);
+    if (lane == 0) y[i] = t;
+  }
+}
+
+// a = sqrt of the Rayleigh quotient v . C v, v = x / |x|, y = C v.
+__global__ __launch_bounds__(kThreads) void k_power_end(Geometry g, Bufs B, const double* __restrict__ x,
+                                                        const double* __restrict__ y) {
+  __shared__ double red[8];
+  double nn = 0.0, xy = 0.0;
+  for (int i = threadIdx.x; i < g.d; i += kThreads) {
+    nn += x[i] * x[i];
+    xy += x[i] * y[i];
+  }
+  nn = block_sum_d(nn, red);
+  xy = block_sum_d(xy, red);
+  if (threadIdx.x == 0) {
+    const double lam = nn > 0.0 ? xy / sqrt(nn) : 0.0;
     const double a = (lam > 0.0) ? sqrt(lam) : 0.0;
     B.ctl->spectral_a = a;
     if (!(a > 0.0) || !isfinite(a)) B.ctl->degenerate = 1;
@@ -384,7 +563,19 @@ __global__ __launch_bounds__(kThreads) void k_proj_partial(Geometry g, Bufs B) {
   if (r > kThreads) {
     for (int c = tid; c < r; c += kThreads) {
       double csc = 0.0;
-      for (int64_t i = r0; i < r1; ++i) {
+      int64_t i = r0;
+      for (; i + 15 < r1; i += 16) {  // sixteen rows' loads in flight, added in row order
+        float v[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v[u] = B.U[(i + u) * r + c];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+          const float uu = fmaxf(v[u], 0.f);
+          csc += (double)uu;
+          sq += (double)uu * (double)uu;
+        }
+      }
+      for (; i < r1; ++i) {
         const float u = fmaxf(B.U[i * r + c], 0.f);
         csc += (double)u;
         sq += (double)u * (double)u;
@@ -425,36 +616,39 @@ __global__ __launch_bounds__(kThreads) void k_proj_partial(Geometry g, Bufs B) {
   }
 }
 
-// c_f = FP32(sqrt(K) / ||U_+||_F) (1 when U is already in Omega); p = FP32(c colsum).
+// c_f = FP32(sqrt(K) / ||U_+||_F) (1 when U is already in Omega); p = FP32(c colsum).  Workgroup b
+// takes columns 16 b .. 16 b + 15, 16 groups of threads over the chunks; each forms the sum of
+// squares for itself, in the same order (a thread a column over all 512 chunks: 100 to 160 us).
 __global__ __launch_bounds__(kThreads) void k_proj_ctl(Geometry g, Bufs B, double K, int in_omega) {
-  __shared__ double red[8];
+  __shared__ double red[kThreads];
+  __shared__ double red8[8];
   __shared__ double cbuf[1];
   const int tid = threadIdx.x;
   const int stride = 4 + g.r32;
   double S = 0.0;
   for (int gx = tid; gx < g.GI; gx += kThreads) S += B.i_proj[(int64_t)gx * stride];
-  S = block_sum_d(S, red);
+  S = block_sum_d(S, red8);
   if (tid == 0) {
     double c = 1.0;
     if (!in_omega) {
       const double nu = sqrt(S);
       if (!(nu > 1e-20) || !isfinite(S)) {
-        B.ctl->breakdown = 1;
+        if (blockIdx.x == 0) B.ctl->breakdown = 1;
         c = 0.0;
       } else {
         c = (double)(float)(sqrt(K) / nu);
       }
     }
     cbuf[0] = c;
-    B.i_scal[0] = c;
+    if (blockIdx.x == 0) B.i_scal[0] = c;
   }
+  const int cl = tid & 15, gq = tid >> 4, col = blockIdx.x * 16 + cl;
+  red[tid] = col < g.r ? strided_sum<8>(B.i_proj + 4 + col, stride, gq, 16, g.GI) : 0.0;
   __syncthreads();
-  const double c = cbuf[0];
-  for (int col = tid; col < g.r32; col += kThreads) {
+  if (tid < 16 && col < g.r32) {
     double t = 0.0;
-    if (col < g.r)
-      for (int gx = 0; gx < g.GI; ++gx) t += B.i_proj[(int64_t)gx * stride + 4 + col];
-    B.p[col] = (col < g.r) ? (float)(c * t) : 0.f;
+    for (int k = 0; k < 16; ++k) t += red[16 * k + cl];
+    B.p[col] = (col < g.r) ? (float)(cbuf[0] * t) : 0.f;
   }
 }
 
@@ -472,95 +666,6 @@ __global__ __launch_bounds__(kThreads) void k_zero_y(Geometry g, Bufs B) {
 }
 
 // ---------------------------------------------------------------------------
-// The same power method for wide inputs (d > 256), the matrix-vector products
-// spread over workgroups: C does not stay in one compute unit's cache there, and
-// one workgroup streaming it each iteration dominates the initialisation.
-// v and w live in the squaring buffer the last squaring did not write (vw[0..d),
-// vw[d..2d)); state[0] the Rayleigh quotient.
-// ---------------------------------------------------------------------------
-// v = the column of Bf with the largest diagonal entry (lowest index on ties), normalised.
-__global__ __launch_bounds__(kThreads) void k_power_start(Geometry g, const double* __restrict__ Bf,
-                                                          double* __restrict__ vw) {
-  __shared__ double red[8];
-  __shared__ int shi[1];
-  __shared__ double sh[1];
-  const int d = g.d, tid = threadIdx.x;
-  if (tid == 0) {
-    double best = -1.0;
-    int arg = 0;
-    for (int j = 0; j < d; ++j) {
-      const double x = Bf[(int64_t)j * d + j];
-      if (x > best) {
-        best = x;
-        arg = j;
-      }
-    }
-    shi[0] = arg;
-  }
-  __syncthreads();
-  const int j0 = shi[0];
-  double nn = 0.0;
-  for (int i = tid; i < d; i += kThreads) {
-    const double x = Bf[(int64_t)i * d + j0];
-    nn += x * x;
-  }
-  nn = block_sum_d(nn, red);
-  if (tid == 0) sh[0] = nn;
-  __syncthreads();
-  const double inv = (sh[0] > 0.0) ? 1.0 / sqrt(sh[0]) : 0.0;
-  for (int i = tid; i < d; i += kThreads) vw[i] = Bf[(int64_t)i * d + j0] * inv;
-}
-
-// w = C v: workgroup b forms rows 64 b .. 64 b + 63; lane l row 64 b + l (column l of the
-// symmetric C, read row by row: coalesced), wave k the terms j = k, k + 4, ...; the four
-// partial sums are added in order.
-__global__ __launch_bounds__(kThreads) void k_power_mv(Geometry g, const double* __restrict__ C,
-                                                       double* __restrict__ vw) {
-  __shared__ double part[kThreads];
-  const int d = g.d, tid = threadIdx.x;
-  const int i = blockIdx.x * 64 + (tid & 63), sub = tid >> 6;
-  const double* v = vw;
-  double t = 0.0;
-  if (i < d)
-#pragma unroll 4
-    for (int j = sub; j < d; j += 4) t += C[(int64_t)j * d + i] * v[j];
-  part[tid] = t;
-  __syncthreads();
-  if (sub == 0 && i < d) vw[d + i] = ((part[tid] + part[64 + tid]) + part[128 + tid]) + part[192 + tid];
-}
-
-// Rayleigh quotient of v, then v = w / |w| (not after the last product); with last set,
-// a = sqrt(Rayleigh quotient) to the control block.
-__global__ __launch_bounds__(kThreads) void k_power_norm(Geometry g, Bufs B, double* __restrict__ vw, int last) {
-  __shared__ double red[8];
-  __shared__ double sh[2];
-  const int d = g.d, tid = threadIdx.x;
-  double s1 = 0.0, s2 = 0.0;
-  for (int i = tid; i < d; i += kThreads) {
-    s1 += vw[i] * vw[d + i];
-    s2 += vw[d + i] * vw[d + i];
-  }
-  s1 = block_sum_d(s1, red);
-  s2 = block_sum_d(s2, red);
-  if (tid == 0) {
-    sh[0] = s1;
-    sh[1] = s2;
-  }
-  __syncthreads();
-  if (last) {
-    if (tid == 0) {
-      const double lam = sh[0];
-      const double a = (lam > 0.0) ? sqrt(lam) : 0.0;
-      B.ctl->spectral_a = a;
-      if (!(a > 0.0) || !isfinite(a)) B.ctl->degenerate = 1;
-    }
-    return;
-  }
-  const double inv = (sh[1] > 0.0) ? 1.0 / sqrt(sh[1]) : 0.0;
-  for (int i = tid; i < d; i += kThreads) vw[i] = vw[d + i] * inv;
-}
-
-// ---------------------------------------------------------------------------
 hipError_t launch_ctl_init(const Bufs& b, float gamma_f, hipStream_t st) {
   hipLaunchKernelGGL(k_ctl_init, dim3(1), dim3(64), 0, st, b, gamma_f);
   return hipGetLastError();
@@ -575,7 +680,7 @@ hipError_t launch_colsum(const Geometry& g, const Bufs& b, hipStream_t st) {
   hipLaunchKernelGGL(k_colsum, dim3(g.GI), dim3(kThreads), 0, st, g, b);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_colmean, dim3((g.d + kThreads - 1) / kThreads), dim3(kThreads), 0, st, g, b);
+  hipLaunchKernelGGL(k_colmean, dim3((g.d + 15) / 16), dim3(kThreads), 0, st, g, b);
   return hipGetLastError();
 }
 
@@ -590,42 +695,51 @@ hipError_t launch_gram(const Geometry& g, const Bufs& b, hipStream_t st) {
   hipError_t e = launch_gram_partials(b.X, g.n, g.d, b.i_xbar, b.i_gram, g.GG, st);
   if (e != hipSuccess) return e;
   const int64_t dd = (int64_t)g.d * g.d;
-  hipLaunchKernelGGL(k_gram_reduce, dim3((unsigned)((dd + kThreads - 1) / kThreads)), dim3(kThreads), 0, st, g, b);
+  // enough entries to fill the chip with a thread each, or not
+  if (dd >= (int64_t)256 * kThreads)
+    hipLaunchKernelGGL(k_gram_reduce<kThreads>, dim3((unsigned)((dd + kThreads - 1) / kThreads)), dim3(kThreads), 0, st,
+                       g, b);
+  else
+    hipLaunchKernelGGL(k_gram_reduce<16>, dim3((unsigned)((dd + 15) / 16)), dim3(kThreads), 0, st, g, b);
   return hipGetLastError();
 }
 
 hipError_t launch_spectral(const Geometry& g, const Bufs& b, hipStream_t st) {
-  // B_0 = C; scal[k] = 1/tr(B_k); B_{k+1} = (B_k scal[k])^2, ping-ponging B0/B1.
-  hipLaunchKernelGGL(k_trace, dim3(1), dim3(kThreads), 0, st, g, (const double*)b.i_C, b.i_scal, 1);
+  // up to 64 features the matrix fits one workgroup's LDS
+  if (g.d <= 64) {
+    if (g.d <= 16)
+      hipLaunchKernelGGL(k_power_small<16>, dim3(1), dim3(1024), 0, st, g, b);
+    else if (g.d <= 32)
+      hipLaunchKernelGGL(k_power_small<32>, dim3(1), dim3(1024), 0, st, g, b);
+    else
+      hipLaunchKernelGGL(k_power_small<64>, dim3(1), dim3(1024), 0, st, g, b);
+    return hipGetLastError();
+  }
+  // B_0 = C; B_{k+1} = (B_k / tr B_k)^2, ping-ponging B0/B1; the traces' block sums likewise
+  const int nb = (g.d + 63) / 64;
   const double* in = b.i_C;
   double* bufs[2] = {b.i_B0, b.i_B1};
-  const dim3 grid(g.gblk, g.gblk);
   for (int k = 0; k < kSquarings; ++k) {
     double* out = bufs[k & 1];
-    hipLaunchKernelGGL(k_square, grid, dim3(kThreads), 0, st, g, in, out, (const double*)b.i_scal, 1 + k);
-    hipLaunchKernelGGL(k_trace, dim3(1), dim3(kThreads), 0, st, g, (const double*)out, b.i_scal, 2 + k);
+    hipLaunchKernelGGL(k_square, dim3(nb * (nb + 1) / 2), dim3(kThreads), 0, st, g, in, out,
+                       k ? (const double*)(b.i_trace + ((k - 1) & 1) * kSqMax) : nullptr,
+                       b.i_trace + (k & 1) * kSqMax);
     in = out;
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (g.d > kThreads) {
-    // wide inputs: the products over workgroups; v and w in the buffer the last
-    // squaring did not write
-    double* vw = (in == b.i_B0) ? b.i_B1 : b.i_B0;
-    hipLaunchKernelGGL(k_power_start, dim3(1), dim3(kThreads), 0, st, g, in, vw);
-    for (int it = 0; it <= kPowerIters; ++it) {
-      hipLaunchKernelGGL(k_power_mv, dim3((g.d + 63) / 64), dim3(kThreads), 0, st, g, (const double*)b.i_C, vw);
-      hipLaunchKernelGGL(k_power_norm, dim3(1), dim3(kThreads), 0, st, g, b, vw, it == kPowerIters ? 1 : 0);
-    }
-    return hipGetLastError();
+  // x and y in the buffer the last squaring did not write (d >= 65: 2 d entries fit)
+  double* xy = (in == b.i_B0) ? b.i_B1 : b.i_B0;
+  const double* x = nullptr;
+  double* y = xy;
+  const int grid = (g.d + 3) / 4 < 256 ? (g.d + 3) / 4 : 256;
+  for (int it = 0; it <= kPowerIters; ++it) {
+    y = xy + (it & 1) * g.d;
+    hipLaunchKernelGGL(k_power_mv, dim3(grid), dim3(kThreads), (size_t)g.d * sizeof(double), st, g,
+                       (const double*)b.i_C, in, x, y);
+    if (it < kPowerIters) x = y;
   }
-  const size_t lds = 2 * (size_t)g.d * sizeof(double);
-  if (lds > (64u << 10)) {
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_power), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)lds);
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(k_power, dim3(1), dim3(kThreads), lds, st, g, b, in);
+  hipLaunchKernelGGL(k_power_end, dim3(1), dim3(kThreads), 0, st, g, b, x, (const double*)y);
   return hipGetLastError();
 }
 
@@ -637,7 +751,7 @@ hipError_t launch_normalise(const Geometry& g, const Bufs& b, hipStream_t st) {
 
 hipError_t launch_project(const Geometry& g, const Bufs& b, double K, int in_omega, hipStream_t st) {
   hipLaunchKernelGGL(k_proj_partial, dim3(g.GI), dim3(kThreads), 0, st, g, b);
-  hipLaunchKernelGGL(k_proj_ctl, dim3(1), dim3(kThreads), 0, st, g, b, K, in_omega);
+  hipLaunchKernelGGL(k_proj_ctl, dim3(g.r32 / 16), dim3(kThreads), 0, st, g, b, K, in_omega);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || in_omega) return e;
   hipLaunchKernelGGL(k_proj_apply, dim3(2048), dim3(kThreads), 0, st, g, b);

@@ -171,15 +171,18 @@ __global__ __launch_bounds__(kThreads) void k_start_panel(Geometry g, Bufs B, in
 
 // U = Xhat T (FP64 products and sums, rounded once), on the fp64 matrix cores.  A wave takes 64 rows
 // (four groups of 16) x CT tiles of 16 columns; a step's 4 features are 16 q + 4 (l / 16) + s for
-// s = 0..3, so a lane reads 16 consecutive bytes of its row of Xhat; T comes from L2, the next
-// tile's operand in flight while this one multiplies.  Column groups of 64 of the same rows are
-// workgroups 8 apart (one XCD), so that Xhat comes from HBM about once.  Bound by the matrix cores:
-// 2 n d r flops, 11.6 ms at 2e6 x 768 x 256 at the rate of a large FP64 product (scalar FMAs from
-// LDS: 51 ms).
+// s = 0..3, so a lane reads 16 consecutive bytes of its row of Xhat, two chunks of 16 features
+// ahead; the chunk's rows of T pass through LDS (one of two buffers, shared by the four waves, a
+// chunk ahead), read in the four rotations of the 4x4x4 form.  Loads complete in order, so T's are
+// issued before Xhat's: with T read by each wave between the products, every chunk waited for
+// Xhat's HBM latency (matrix cores 42% busy, 24 ms at 2e6 x 768 x 256).  Column groups of 64 of the
+// same rows are workgroups 8 apart (one XCD), so that Xhat comes from HBM about once.  Bound by the
+// matrix cores: 2 n d r flops.
 template <int CT, bool VEC>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_start_apply(Geometry g, Bufs B,
                                                                                                      int cgroups) {
   if (B.ctl->degenerate) return;
+  __shared__ double ts[2][16][16 * CT + 4];  // rows 4 apart (lanes 16 apart) on the other half of the banks
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, lg = lane >> 4, lr = lane & 15;
   const int d = g.d, r = g.r;
   const int64_t n = g.n;
@@ -187,88 +190,98 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
   const int64_t tile = id / per * 8 + id % per % 8;
   const int cg = (int)(id % per / 8);
   const int64_t row0 = tile * 256 + 64 * w;
-  if (row0 >= n) return;
+  if (tile * 256 >= n) return;
   const float* xp[4];
 #pragma unroll
   for (int gq = 0; gq < 4; ++gq) {
     const int64_t row = row0 + 16 * gq + lr;
     xp[gq] = B.X + (row < n ? row : n - 1) * d;
   }
-  int colc[CT];
-  bool okc[CT];
-#pragma unroll
-  for (int t = 0; t < CT; ++t) {
-    const int c = 64 * cg + 16 * t + lr;
-    okc[t] = c < r;
-    colc[t] = okc[t] ? c : 0;
-  }
-  f64x4 acc[4][CT];
+  double acc[4][CT][4];
 #pragma unroll
   for (int gq = 0; gq < 4; ++gq)
 #pragma unroll
-    for (int t = 0; t < CT; ++t) acc[gq][t] = (f64x4){0.0, 0.0, 0.0, 0.0};
-  float nx[4][4];
-  auto load_x = [&](int q) {
+    for (int t = 0; t < CT; ++t)
+#pragma unroll
+      for (int R = 0; R < 4; ++R) acc[gq][t][R] = 0.0;
+  auto load_x = [&](int q, float (&x)[4][4]) {
     const int c0 = 16 * q + 4 * lg;
 #pragma unroll
     for (int gq = 0; gq < 4; ++gq) {
       if constexpr (VEC) {
         const f32x4 t = *reinterpret_cast<const f32x4*>(xp[gq] + (c0 < d ? c0 : 0));
 #pragma unroll
-        for (int s = 0; s < 4; ++s) nx[gq][s] = c0 < d ? t[s] : 0.f;
+        for (int s = 0; s < 4; ++s) x[gq][s] = t[s];
       } else {
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          const float t = xp[gq][c0 + s < d ? c0 + s : 0];
-          nx[gq][s] = c0 + s < d ? t : 0.f;
-        }
+        for (int s = 0; s < 4; ++s) x[gq][s] = xp[gq][c0 + s < d ? c0 + s : 0];
       }
     }
   };
-  auto load_t = [&](int q, int t, double (&b)[4]) {
+  // CT elements of the chunk's 16 x 16 CT of T a thread; features beyond d are zero (what Xhat's
+  // clamped loads hold there does not matter), columns beyond r are not stored
+  double tn[CT];
+  auto load_t = [&](int q) {
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const int c = 16 * q + 4 * lg + s;
-      const double v = B.s_T[(int64_t)(c < d ? c : d - 1) * r + colc[t]];
-      b[s] = (c < d && okc[t]) ? v : 0.0;
+    for (int u = 0; u < CT; ++u) {
+      const int e = tid + u * kThreads, f = 16 * q + e / (16 * CT), c = 64 * cg + e % (16 * CT);
+      const double v = B.s_T[(int64_t)(f < d ? f : 0) * r + (c < r ? c : 0)];
+      tn[u] = f < d ? v : 0.0;
+    }
+  };
+  auto put_t = [&](int b) {
+#pragma unroll
+    for (int u = 0; u < CT; ++u) {
+      const int e = tid + u * kThreads;
+      ts[b][e / (16 * CT)][e % (16 * CT)] = tn[u];
     }
   };
   const int nq = (d + 15) >> 4;
-  load_x(0);
-  double bn[4];
-  load_t(0, 0, bn);
-  for (int q = 0; q < nq; ++q) {
+  float x0[4][4], x1[4][4];
+  load_t(0);
+  load_x(0, x0);
+  load_x(nq > 1 ? 1 : 0, x1);
+  put_t(0);
+  __syncthreads();
+  // chunk q from xc; afterwards xc holds chunk q + 2
+  auto chunk = [&](int q, float (&xc)[4][4]) {
     double a[4][4];
 #pragma unroll
     for (int gq = 0; gq < 4; ++gq)
 #pragma unroll
-      for (int s = 0; s < 4; ++s) a[gq][s] = (double)nx[gq][s];
-    if (q + 1 < nq) load_x(q + 1);
+      for (int s = 0; s < 4; ++s) a[gq][s] = (double)xc[gq][s];
+    if (q + 1 < nq) load_t(q + 1);
+    if (q + 2 < nq) load_x(q + 2, xc);
 #pragma unroll
-    for (int t = 0; t < CT; ++t) {
-      double b[4];
+    for (int s = 0; s < 4; ++s)
 #pragma unroll
-      for (int s = 0; s < 4; ++s) b[s] = bn[s];
-      if (t + 1 < CT)
-        load_t(q, t + 1, bn);
-      else if (q + 1 < nq)
-        load_t(q + 1, 0, bn);
+      for (int t = 0; t < CT; ++t)
 #pragma unroll
-      for (int s = 0; s < 4; ++s)
+        for (int R = 0; R < 4; ++R) {
+          const double b = ts[q & 1][4 * lg + s][16 * t + ((lr + 4 * R) & 15)];
 #pragma unroll
-        for (int gq = 0; gq < 4; ++gq) acc[gq][t] = mfma16x16x4d(a[gq][s], b[s], acc[gq][t]);
-    }
+          for (int gq = 0; gq < 4; ++gq) acc[gq][t][R] = mfma4x4x4d(a[gq][s], b, acc[gq][t][R]);
+        }
+    if (q + 1 < nq) put_t((q + 1) & 1);
+    __syncthreads();
+  };
+  for (int q = 0; q < nq; q += 2) {
+    chunk(q, x0);
+    if (q + 1 < nq) chunk(q + 1, x1);
   }
+  const int bl = (lane >> 2) & 3;
 #pragma unroll
-  for (int gq = 0; gq < 4; ++gq)
+  for (int gq = 0; gq < 4; ++gq) {
+    const int64_t row = row0 + 16 * gq + 4 * bl + lg;
+    if (row < n)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int64_t row = row0 + 16 * gq + 4 * v + lg;
-      if (row < n)
+      for (int t = 0; t < CT; ++t)
 #pragma unroll
-        for (int t = 0; t < CT; ++t)
-          if (okc[t]) B.U[row * r + 64 * cg + 16 * t + lr] = (float)acc[gq][t][v];
-    }
+        for (int R = 0; R < 4; ++R) {
+          const int c = 64 * cg + 16 * t + 4 * ((bl + R) & 3) + (lane & 3);
+          if (c < r) B.U[row * r + c] = (float)acc[gq][t][R];
+        }
+  }
 }
 
 template <int CT>

@@ -121,7 +121,6 @@ Geometry make_geometry(int64_t n, int32_t d, int32_t r, int32_t K, bool aligned1
     const int64_t t64 = (n + 63) / 64;
     if (gg > t64) gg = t64;
     g.GG = (int32_t)gg;
-    g.gblk = g.d32 / 32;
   }
   // single-Xhat-pass iteration: the row pass and the fused pass B need the
   // register-resident shapes (d <= 128, r <= 64, 16-byte aligned X and U rows of
@@ -315,7 +314,8 @@ size_t carve_workspace(const Geometry& g, char* base, Bufs* out) {
   u_init += align256((size_t)g.GI * d * 8);            // colsum
   u_init += align256((size_t)g.GG * d * d * 8);         // gram partials
   u_init += 3 * align256(d * d * 8);                    // C, B0, B1
-  u_init += align256(2 * (kSquarings + 2) * 8);         // scal
+  u_init += align256(8);                                // scal
+  u_init += align256(2 * 64 * 8);                       // traces
   u_init += align256((size_t)g.GI * (4 + r32) * 8);     // projection partials
   // the spectral label recovery (between host calls) uses the same region
   const int32_t kmax = g.r < kLabMaxK ? g.r : kLabMaxK;
@@ -336,7 +336,8 @@ size_t carve_workspace(const Geometry& g, char* base, Bufs* out) {
     b.i_C = reinterpret_cast<double*>(sub(d * d * 8));
     b.i_B0 = reinterpret_cast<double*>(sub(d * d * 8));
     b.i_B1 = reinterpret_cast<double*>(sub(d * d * 8));
-    b.i_scal = reinterpret_cast<double*>(sub(2 * (kSquarings + 2) * 8));
+    b.i_scal = reinterpret_cast<double*>(sub(8));
+    b.i_trace = reinterpret_cast<double*>(sub(2 * 64 * 8));
     b.i_proj = reinterpret_cast<double*>(sub((size_t)g.GI * (4 + r32) * 8));
   }
   if (out) *out = b;

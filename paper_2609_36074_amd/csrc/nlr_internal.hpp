@@ -99,7 +99,6 @@ struct Geometry {
   // init
   int32_t GI;           // row-chunk workgroups of the init reductions
   int32_t GG;           // row-chunk workgroups of the Gram partials
-  int32_t gblk;         // 32-wide blocks of d for the Gram
   int32_t vec_x, vec_u; // 16-byte vector loads allowed on X / U rows
   int32_t GAF;          // workgroups of the finish pass (generic pass A form)
   // split-fp16 panel form (large d x r, two passes)
@@ -142,7 +141,8 @@ struct Bufs {
   double* i_C;         // d x d
   double* i_B0;        // d x d
   double* i_B1;        // d x d
-  double* i_scal;      // 2*(kSquarings+2)
+  double* i_scal;      // c of the projection
+  double* i_trace;     // 2 x 64: traces of the squarings' diagonal blocks
   double* i_proj;      // GI x (4 + r32)
   // data-informed start (FP64, not aliased)
   double* s_C;         // d x d: Xhat^T Xhat
