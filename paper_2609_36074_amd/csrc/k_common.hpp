@@ -45,6 +45,51 @@ __device__ __forceinline__ void load_vec(float (&dst)[W], const float* src, bool
   }
 }
 
+// Rows that are not 16-byte aligned (UN): global memory takes 16- and 8-byte accesses at any 4-byte
+// address, so a row moves in pieces of four as aligned rows do; a row's last piece may run up to
+// three floats into the next row (masked where used).  Past the end of the matrix there is nothing
+// to read, so tiles that hold the last row -- or any, where a row is shorter than three -- load
+// element by element (edge).
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));
+template <bool UN>
+__device__ __forceinline__ f32x4 load4(const float* p) {
+  if constexpr (UN)
+    return *reinterpret_cast<const f32x4u*>(p);
+  else
+    return *reinterpret_cast<const f32x4*>(p);
+}
+// W elements from column c of a row of `len` (unaligned); edge: those past its end as the last one.
+template <int W>
+__device__ __forceinline__ void load_piece(float (&dst)[W], const float* row, int c, int len, bool edge) {
+  if (edge) {
+    asm volatile("" : "+v"(c));  // as load4_edge
+#pragma unroll
+    for (int e = 0; e < W; ++e) dst[e] = row[c + e < len ? c + e : len - 1];
+    __builtin_amdgcn_sched_barrier(0);
+  } else if constexpr (W == 4) {
+    const f32x4u t = *reinterpret_cast<const f32x4u*>(row + c);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) dst[e] = t[e];
+  } else if constexpr (W == 2) {
+    const f32x2u t = *reinterpret_cast<const f32x2u*>(row + c);
+    dst[0] = t[0];
+    dst[1] = t[1];
+  } else {
+    dst[0] = row[c];
+  }
+}
+// Elements c .. c + 3 of a row of `len`, those past its end as the last one.  (The opaque column
+// and the barrier keep the addresses of this rare path out of registers that live across the loop.)
+__device__ __forceinline__ f32x4 load4_edge(const float* row, int c, int len) {
+  f32x4 t;
+  asm volatile("" : "+v"(c));
+#pragma unroll
+  for (int e = 0; e < 4; ++e) t[e] = row[c + e < len ? c + e : len - 1];
+  __builtin_amdgcn_sched_barrier(0);
+  return t;
+}
+
 template <int CTRL>
 __device__ __forceinline__ double dpp_d(double v) {
   const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false);

@@ -25,257 +25,21 @@
 namespace nlr {
 
 // ---------------------------------------------------------------------------
-// Tile staging: rows [row0, row0+kTPA) x cols [c0, c0+cw) of a row-major matrix
-// with leading dimension ld, multiplied by `scale`, into LDS with row stride ls.
-// Rows >= n and cols >= cmax are zero-filled.
+// Pass A where Theta does not fit one wave's registers runs as two launches: the row work
+// (k_rows_wide, below) and this product, Theta = Xhat^T U.  Grid (GA, mgroups * ngroups).
+// Workgroup (gx, gy) owns a contiguous range of kTPA-row tiles and the Theta blocks of group gy
+// (MBG x NBG blocks of 32 x 32).  Wave w owns m-block w % MBG and all NBG n-blocks, over the
+// k-slice w / MBG of each tile (KS = 4 / MBG slices).  The next tile's rows are loaded into
+// registers while the matrix cores work on the current one: per tile a thread holds XV + UV
+// pieces of four; loads past the last row or column read a valid address and are zeroed, so none
+// waits behind a branch.  The waves whose m-block lies past the last feature skip the product
+// (their partial rows are not written).  UN: rows of X or U not 16-byte aligned.  Bound by the
+// fp32 matrix cores (74% busy at 2e6 x 768 x 256); rows that are not 16-byte aligned used to be
+// staged a float a thread with nothing in flight meanwhile (13 to 20 TFLOP/s).
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void stage_tile(float* __restrict__ dst, int ls, const float* __restrict__ src,
-                                           int64_t ld, int64_t n, int64_t row0, int c0, int cw,
-                                           int cmax, float scale, bool vec) {
-  if (vec) {
-    const int cw4 = cw >> 2;
-    const int total = kTPA * cw4;
-    for (int v = threadIdx.x; v < total; v += kThreads) {
-      const int row = v / cw4;
-      const int c = (v - row * cw4) * 4;
-      const int64_t gr = row0 + row;
-      f32x4 x = {0.f, 0.f, 0.f, 0.f};
-      if (gr < n && c0 + c < cmax) {
-        x = *reinterpret_cast<const f32x4*>(src + gr * ld + c0 + c);
-        x.x = x.x * scale;
-        x.y = x.y * scale;
-        x.z = x.z * scale;
-        x.w = x.w * scale;
-      }
-      *reinterpret_cast<f32x4*>(dst + row * ls + c) = x;
-    }
-  } else {
-    const int total = kTPA * cw;
-    for (int v = threadIdx.x; v < total; v += kThreads) {
-      const int row = v / cw;
-      const int c = v - row * cw;
-      const int64_t gr = row0 + row;
-      float x = 0.f;
-      if (gr < n && c0 + c < cmax) x = src[gr * ld + c0 + c] * scale;
-      dst[row * ls + c] = x;
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Pass A.  Grid (GA, mgroups*ngroups).  Workgroup (gx, gy) owns a contiguous
-// range of kTPA-row tiles and the Theta blocks of group gy (MBG x NBG blocks of
-// 32 x 32).  Wave w owns m-block w % MBG and all NBG n-blocks, over the k-slice
-// w / MBG of each tile (KS = 4 / MBG slices).  Group 0 also does the row work.
-// MODE kAFinish: no matrix product; materialise U and do the row work only.
-// Above 128 columns the iteration's pass A runs as two launches: the row work
-// (k_rows_wide, below) and kATheta: the product alone, every group staging only its
-// own columns of U, so that a workgroup's LDS is about a third of the combined form's.
-// ---------------------------------------------------------------------------
-constexpr int kAIter = 0, kAFinish = 1, kATheta = 2;
-template <int MBG, int NBG, int MODE>
-__global__ __launch_bounds__(kThreads) void k_pass_a(Geometry g, Bufs B, StepArgs S) {
-  constexpr bool FINISH = MODE == kAFinish;
-  constexpr bool THETA = MODE == kAIter || MODE == kATheta;  // the matrix product
-  constexpr bool ROWS = MODE != kATheta;                     // the row work (group 0)
-  // The finish pass runs after a stop (it still materialises U) but not after a breakdown.
-  if (FINISH ? (B.ctl->breakdown != 0) : halted(B.ctl)) return;
-  const bool stopped = FINISH && (B.ctl->stop != 0);
-  constexpr int KS = 4 / MBG;
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  float* smem = reinterpret_cast<float*>(smem_raw);
-  const int xs_stride = g.xs_stride;  // MBG*32
-  const int us_stride = MODE == kATheta ? NBG * 32 + 4 : g.us_stride;  // staged columns + 4
-  float* Xs = smem;                                  // kTPA x xs_stride
-  float* Us = Xs + (THETA ? kTPA * xs_stride : 0);   // kTPA x us_stride
-  float* ybar_s = Us + kTPA * us_stride;             // kTPA
-  float* p_s = ybar_s + kTPA;                        // r32
-  double* dred = reinterpret_cast<double*>(p_s + g.r32);  // 256 + 8 doubles (8-byte aligned: r32 even)
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int gx = blockIdx.x;
-  const int gy = blockIdx.y;
-  const int mg = gy / g.ngroups;
-  const int ng = gy - mg * g.ngroups;
-  const bool do_rows = ROWS && (gy == 0);
-  const int64_t n = g.n;
-  const int d = g.d, r = g.r, r32 = g.r32;
-  const int f0 = mg * MBG * 32;       // first feature of the group
-  const int c0 = ng * NBG * 32;       // first column of the group
-  const float cf = B.ctl->c_f;
-  // after a stop the end-of-iteration work was already done by pass A
-  const bool gate = (S.end_work != 0) && (B.ctl->gate != 0) && !stopped;
-  const float gam = S.gamma_f;
-
-  // the grid is GA (Theta product) or GAF (finish pass, row-work launch)
-  const int64_t tb = (int64_t)gx * g.tilesA / gridDim.x;
-  const int64_t te = (int64_t)(gx + 1) * g.tilesA / gridDim.x;
-
-  if (do_rows)
-    for (int c = tid; c < r32; c += kThreads) p_s[c] = (c < r) ? B.p[c] : 0.f;
-
-  // row-work accumulators
-  double acc_qq = 0.0, acc_yq = 0.0, acc_s = 0.0, acc_s2 = 0.0;
-  // s ownership: column sc, points ps0, ps0 + pstep, ...; above 256 columns every
-  // point, columns tid and tid + 256 (acc_s2)
-  const int pstep = kThreads / r32 > 0 ? kThreads / r32 : 1;
-  const int sc = tid % r32;
-  const int ps0 = tid / r32;
-  const int sc2 = tid + kThreads;
-
-  // matrix-core accumulators
-  const int mb = wave % MBG;
-  const int ks = wave / MBG;
-  f32x16 acc[NBG];
-#pragma unroll
-  for (int j = 0; j < NBG; ++j)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
-
-  const int ucols = do_rows ? r32 : NBG * 32;      // staged U columns
-  const int ucol0 = do_rows ? 0 : c0;              // first staged U column
-  const int ub = do_rows ? c0 : 0;                 // offset of the group's columns in Us
-
-  for (int64_t tile = tb; tile < te; ++tile) {
-    const int64_t row0 = tile * kTPA;
-    __syncthreads();
-    if (THETA)
-      stage_tile(Xs, xs_stride, B.X, d, n, row0, f0, MBG * 32, d, 1.0f, g.vec_x != 0);
-    stage_tile(Us, us_stride, B.U, r, n, row0, ucol0, ucols, r, cf, g.vec_u != 0);
-    __syncthreads();
-
-    if (do_rows) {
-      // R1: four threads per row: q = u.p - 1 (FP64 dot), dual step, ybar.
-      const int tp = tid >> 2;
-      const int j4 = tid & 3;
-      double dot = 0.0;
-      for (int c = j4; c < r; c += 4) dot += (double)Us[tp * us_stride + c] * (double)p_s[c];
-      dot += shfl_xor_d(dot, 1);
-      dot += shfl_xor_d(dot, 2);
-      const int64_t gr = row0 + tp;
-      float ybar = 0.f;
-      if (gr < n) {
-        const float q = (float)(dot - 1.0);
-        float yt = B.y[gr];
-        if (gate) {
-          yt = fmaf(gam, q, yt);
-          if (j4 == 0) B.y[gr] = yt;
-        }
-        ybar = fmaf(gam, q, yt);
-        if (j4 == 0) {
-          acc_qq += (double)q * (double)q;
-          acc_yq += (double)yt * (double)q;
-        }
-      }
-      if (j4 == 0) ybar_s[tp] = ybar;
-      if (FINISH) {
-        // materialise U = fl(c_f w) from the staged tile
-        const int64_t rows_here = (n - row0) < kTPA ? (n - row0) : kTPA;
-        const int64_t total = rows_here * r;
-        for (int64_t v = tid; v < total; v += kThreads) {
-          const int rr = (int)(v / r);
-          const int cc = (int)(v - (int64_t)rr * r);
-          B.U[(row0 + rr) * r + cc] = Us[rr * us_stride + cc];
-        }
-      }
-      __syncthreads();
-      if (!FINISH && sc < r) {
-        // R2: s_c += ybar_p u_pc
-        for (int pt = ps0; pt < kTPA; pt += pstep)
-          acc_s += (double)ybar_s[pt] * (double)Us[pt * us_stride + sc];
-      }
-      if (!FINISH && sc2 < r)
-        for (int pt = 0; pt < kTPA; ++pt) acc_s2 += (double)ybar_s[pt] * (double)Us[pt * us_stride + sc2];
-    }
-
-    if (THETA) {
-      // Theta_blk += Xs^T Us over this wave's k-slice (2 rows per instruction).
-      const int kbeg = ks * (kTPA / KS);
-      const int kend = kbeg + kTPA / KS;
-      const int lr = lane >> 5;   // row within the pair
-      const int lc = lane & 31;
-#pragma unroll 4
-      for (int k = kbeg; k < kend; k += 2) {
-        const float a = Xs[(k + lr) * xs_stride + mb * 32 + lc];
-#pragma unroll
-        for (int j = 0; j < NBG; ++j) {
-          const float bv = Us[(k + lr) * us_stride + ub + j * 32 + lc];
-          acc[j] = mfma32x32x2(a, bv, acc[j]);
-        }
-      }
-    }
-  }
-
-  // ---- write partials ----
-  if (THETA) {
-    // combine k-slices (waves with the same m-block) in a fixed order
-    __syncthreads();
-    float* comb = smem;  // MBG * NBG * 16 * 64 floats
-    for (int slice = 1; slice < KS; ++slice) {
-      if (ks == slice) {
-#pragma unroll
-        for (int j = 0; j < NBG; ++j)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) comb[((mb * NBG + j) * 16 + v) * 64 + lane] = acc[j][v];
-      }
-      __syncthreads();
-      if (ks == 0) {
-#pragma unroll
-        for (int j = 0; j < NBG; ++j)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) acc[j][v] += comb[((mb * NBG + j) * 16 + v) * 64 + lane];
-      }
-      __syncthreads();
-    }
-    if (ks == 0) {
-      float* part = B.theta_part + (int64_t)gx * g.theta_cols;
-      const int lr = lane >> 5, lc = lane & 31;
-#pragma unroll
-      for (int j = 0; j < NBG; ++j) {
-        const int col = c0 + j * 32 + lc;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int f = f0 + mb * 32 + 8 * (v >> 2) + 4 * lr + (v & 3);
-          if (f < g.d32 && col < r32) part[(int64_t)f * r32 + col] = acc[j][v];
-        }
-      }
-    }
-  }
-  if (do_rows) {
-    double* ap = B.a_part + (int64_t)gx * (4 + r32);
-    const double qq = block_sum_d(acc_qq, dred + 256);
-    const double yq = block_sum_d(acc_yq, dred + 256);
-    if (tid == 0) {
-      ap[0] = qq;
-      ap[1] = yq;
-      ap[2] = ap[3] = 0.0;
-    }
-    // s: threads sharing a column reduce in a fixed order
-    __syncthreads();
-    dred[tid] = acc_s;
-    __syncthreads();
-    if (tid < r32) {
-      double t = 0.0;
-      for (int k = 0; k < pstep; ++k) t += dred[tid + k * r32];
-      ap[4 + tid] = FINISH ? 0.0 : t;
-    }
-    if (sc2 < r32) ap[4 + sc2] = FINISH ? 0.0 : acc_s2;
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Theta = Xhat^T U of the generic pass A above 128 columns for 16-byte aligned rows
-// (d % 4 == 0, r % 4 == 0): the product of k_pass_a's Theta mode (same groups, waves,
-// k-slices and summation order, so the same bits) with the next tile's rows loaded
-// into registers while the matrix cores work on the current one.  Per tile a thread
-// holds XV + UV 16-byte pieces; loads past the last row or column read a valid
-// address and are zeroed, so none waits behind a branch.  The waves whose m-block
-// lies past the last feature skip the product (their partial rows are not written).
-// ---------------------------------------------------------------------------
-template <int MBG, int NBG>
-__global__ __launch_bounds__(kThreads) void k_theta_wide(Geometry g, Bufs B) {
+template <int MBG, int NBG, bool UN>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NBG >= 7 ? 1 : 2, 8))) void k_theta_wide(
+    Geometry g, Bufs B) {
   if (halted(B.ctl)) return;
   constexpr int KS = 4 / MBG;
   constexpr int XS = MBG * 32 + 4;                // LDS row strides (floats)
@@ -328,15 +92,28 @@ __global__ __launch_bounds__(kThreads) void k_theta_wide(Geometry g, Bufs B) {
     const int valid = (int)((n - row0) < kTPA ? (n - row0) : kTPA);
     const float* xb = B.X + row0 * d;
     const float* ub = B.U + row0 * r;
+    if (UN && (row0 + kTPA >= n || d < 3 || r < 3)) {
+#pragma unroll
+      for (int i = 0; i < XV; ++i) {
+        const int v = tid + i * kThreads, row = v / XR4, c = 4 * (v - row * XR4);
+        xr[i] = load4_edge(xb + (row < valid ? row : 0) * d, xk[i] ? f0 + c : 0, d);
+      }
+#pragma unroll
+      for (int i = 0; i < UV; ++i) {
+        const int v = tid + i * kThreads, row = v / UR4, c = 4 * (v - row * UR4);
+        ur[i] = load4_edge(ub + (row < valid ? row : 0) * r, uk[i] ? c0 + c : 0, r);
+      }
+      return;
+    }
 #pragma unroll
     for (int i = 0; i < XV; ++i) {
       const int row = (tid + i * kThreads) / XR4;
-      xr[i] = *reinterpret_cast<const f32x4*>(xb + (row < valid ? xo[i] : xo[i] - row * d));
+      xr[i] = load4<UN>(xb + (row < valid ? xo[i] : xo[i] - row * d));
     }
 #pragma unroll
     for (int i = 0; i < UV; ++i) {
       const int row = (tid + i * kThreads) / UR4;
-      ur[i] = *reinterpret_cast<const f32x4*>(ub + (row < valid ? uo[i] : uo[i] - row * r));
+      ur[i] = load4<UN>(ub + (row < valid ? uo[i] : uo[i] - row * r));
     }
   };
 
@@ -355,18 +132,18 @@ __global__ __launch_bounds__(kThreads) void k_theta_wide(Geometry g, Bufs B) {
     for (int i = 0; i < XV; ++i) {
       const int v = tid + i * kThreads, row = v / XR4, c = 4 * (v - row * XR4);
       const bool ok = xk[i] && row < valid;
-      const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-      *reinterpret_cast<f32x4*>(Xs + row * XS + c) = ok ? xr[i] : zero;
+      f32x4 t = xr[i];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) t[e] = (UN ? ok && f0 + c + e < d : ok) ? t[e] : 0.f;
+      *reinterpret_cast<f32x4*>(Xs + row * XS + c) = t;
     }
 #pragma unroll
     for (int i = 0; i < UV; ++i) {
       const int v = tid + i * kThreads, row = v / UR4, c = 4 * (v - row * UR4);
       const bool ok = uk[i] && row < valid;
       f32x4 t = ur[i];
-      t.x = ok ? t.x * cf : 0.f;
-      t.y = ok ? t.y * cf : 0.f;
-      t.z = ok ? t.z * cf : 0.f;
-      t.w = ok ? t.w * cf : 0.f;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) t[e] = (UN ? ok && c0 + c + e < r : ok) ? t[e] * cf : 0.f;
       *reinterpret_cast<f32x4*>(Us + row * US + c) = t;
     }
     __syncthreads();
@@ -423,18 +200,21 @@ __global__ __launch_bounds__(kThreads) void k_theta_wide(Geometry g, Bufs B) {
 }
 
 // ---------------------------------------------------------------------------
-// Row work of the generic pass A above 128 columns (its first launch): no LDS
-// staging; each wave streams whole rows of U, lane l holding the columns
-// l + 64 j (CPL = ceil(r / 64) of them), RPI rows at a time.  Per row: u = fl(c_f w),
-// q = u.p - 1 (FP64, summed over the wave by an xor butterfly, so every lane has
-// the same bits), the gated dual step (eq. of the stored dual), ybar (stored for
-// pass B); then s += ybar u, ||q||^2 and ytilde^T q in FP64.  Grid GAF; workgroup gx takes a
-// contiguous range of rows, its waves every fourth row of it, and writes partial row
-// gx in the layout of pass A (qq, yq, 0, 0, s).
+// Row work of pass A where Theta does not fit one wave (its first launch), and the finish pass of
+// those shapes and of the panel form: no LDS staging; each wave streams whole rows of U, lane l
+// holding the columns l + 64 j (CPL = ceil(r / 64) of them), RPI rows at a time.  Per row:
+// u = fl(c_f w), q = u.p - 1 (FP64, summed over the wave by an xor butterfly, so every lane has
+// the same bits), the gated dual step (eq. of the stored dual), ybar (stored for pass B above 128
+// columns); then s += ybar u, ||q||^2 and ytilde^T q in FP64.  FINISH: materialises u instead of
+// forming s and ybar.  Grid GAF; workgroup gx takes a contiguous range of rows, its waves every
+// fourth row of it, and writes partial row gx (qq, yq, 0, 0, s).  Bound by the row stream (the
+// finish pass as LDS-staged tiles took 1.94 ms at 1e6 x 300, 2.4 GB).
 // ---------------------------------------------------------------------------
-template <int CPL>
+template <int CPL, bool FINISH>
 __global__ __launch_bounds__(kThreads) void k_rows_wide(Geometry g, Bufs B, StepArgs S) {
-  if (halted(B.ctl)) return;
+  // the finish pass runs after a stop (it still materialises U) but not after a breakdown
+  if (FINISH ? (B.ctl->breakdown != 0) : halted(B.ctl)) return;
+  const bool stopped = FINISH && (B.ctl->stop != 0);
   constexpr int RPI = 8;  // rows per wave and step
   __shared__ double sred[4 * 64 * CPL];
   __shared__ double dred[kThreads + 8];
@@ -444,7 +224,8 @@ __global__ __launch_bounds__(kThreads) void k_rows_wide(Geometry g, Bufs B, Step
   const int64_t n = g.n;
   const int r = g.r;
   const float cf = B.ctl->c_f;
-  const bool gate = (S.end_work != 0) && (B.ctl->gate != 0);
+  // after a stop the end-of-iteration work was already done by pass A
+  const bool gate = (S.end_work != 0) && (B.ctl->gate != 0) && !stopped;
   const float gam = S.gamma_f;
 
   float pl[CPL];
@@ -509,12 +290,18 @@ __global__ __launch_bounds__(kThreads) void k_rows_wide(Geometry g, Bufs B, Step
         }
         const float ybar = fmaf(gam, q, y);
         if (lane == 0) {
-          B.ybar[row] = ybar;
+          if (!FINISH && CPL > 2) B.ybar[row] = ybar;
           acc_qq += (double)q * (double)q;
           acc_yq += (double)y * (double)q;
         }
 #pragma unroll
-        for (int j = 0; j < CPL; ++j) sacc[j] += (double)ybar * (double)u[i][j];
+        for (int j = 0; j < CPL; ++j) {
+          if constexpr (FINISH) {
+            if (okc[j]) B.U[row * r + colo[j]] = u[i][j];
+          } else {
+            sacc[j] += (double)ybar * (double)u[i][j];
+          }
+        }
       }
     }
   }
@@ -526,6 +313,10 @@ __global__ __launch_bounds__(kThreads) void k_rows_wide(Geometry g, Bufs B, Step
     ap[0] = qq;
     ap[1] = yq;
     ap[2] = ap[3] = 0.0;
+  }
+  if (FINISH) {
+    for (int c = tid; c < g.r32; c += kThreads) ap[4 + c] = 0.0;
+    return;
   }
   // s: the four waves' sums of a column, added in wave order
 #pragma unroll
@@ -556,7 +347,8 @@ __global__ __launch_bounds__(kThreads) void k_rows_wide(Geometry g, Bufs B, Step
 // MODE kPassRows: no matrix product and no write of U: the row work of the fused
 // iteration, whose Theta comes from the previous pass B.
 // ---------------------------------------------------------------------------
-template <int FV, int NGF, int CV, int MODE>
+// UN: rows of X or U that are not a whole number of aligned pieces (any d <= 128, r <= 64).
+template <int FV, int NGF, int CV, int MODE, bool UN>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_pass_a_rows(
     Geometry g, Bufs B, StepArgs S) {
   constexpr bool FINISH = MODE == kPassFinish;
@@ -624,14 +416,27 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
     const int64_t row = 4 * k + grp;
     const bool ok = (k < k1) && (row < n);
     const int64_t rr = ok ? row : 0;
-    if (THETA) {
+    if constexpr (UN) {
+      // the step that holds the last row, and any where a row is shorter than a piece: by elements
+      const bool edge = 4 * k + 4 >= n || n <= 4 || d < 3 || r < 3;
+      if (THETA) {
 #pragma unroll
-      for (int gg = 0; gg < NGF; ++gg) {
-        const int f = 16 * FV * gg + FV * li;
-        load_vec<FV>(xr[slot][gg], B.X + rr * d + (f < d ? f : 0), true);
+        for (int gg = 0; gg < NGF; ++gg) {
+          const int f = 16 * FV * gg + FV * li;
+          load_piece<FV>(xr[slot][gg], B.X + rr * d, f < d ? f : 0, d, edge);
+        }
       }
+      load_piece<CV>(ur[slot], Usrc + rr * r, cx ? cu : 0, r, edge);
+    } else {
+      if (THETA) {
+#pragma unroll
+        for (int gg = 0; gg < NGF; ++gg) {
+          const int f = 16 * FV * gg + FV * li;
+          load_vec<FV>(xr[slot][gg], B.X + rr * d + (f < d ? f : 0), true);
+        }
+      }
+      load_vec<CV>(ur[slot], Usrc + rr * r + (cx ? cu : 0), true);
     }
-    load_vec<CV>(ur[slot], Usrc + rr * r + (cx ? cu : 0), true);
     yr[slot] = B.y[rr];
   };
 #pragma unroll
@@ -652,13 +457,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
       const bool valid = (k < k1) && (row < n);
       float u[CV];
 #pragma unroll
-      for (int c = 0; c < CV; ++c) u[c] = (valid && cx) ? ur[i][c] * cf : 0.f;
+      for (int c = 0; c < CV; ++c) u[c] = (valid && (UN ? cu + c < r : cx)) ? ur[i][c] * cf : 0.f;
       if (THETA) {
 #pragma unroll
         for (int gg = 0; gg < NGF; ++gg)
 #pragma unroll
           for (int e = 0; e < FV; ++e) {
-            const float x = fx[gg] ? xr[i][gg][e] : 0.f;
+            const float x = (UN ? 16 * FV * gg + FV * li + e < d : fx[gg]) ? xr[i][gg][e] : 0.f;
 #pragma unroll
             for (int c = 0; c < CV; ++c)
               acc[(gg * FV + e) * CV + c] = mfma16x16x4(x, u[c], acc[(gg * FV + e) * CV + c]);
@@ -682,7 +487,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
       yq += lead ? (double)yt * (double)q : 0.0;
       if (FINISH) {
         float* dst = (valid && cx) ? (B.U + row * r + cu) : B.dump;
-        if constexpr (CV == 4) {
+        if constexpr (UN) {
+#pragma unroll
+          for (int c = 0; c < CV; ++c)
+            if (valid && cu + c < r) B.U[row * r + cu + c] = u[c];
+        } else if constexpr (CV == 4) {
           f32x4 o = {u[0], u[1], u[2], u[3]};
           *reinterpret_cast<f32x4*>(dst) = o;
         } else if constexpr (CV == 2) {
@@ -1062,220 +871,31 @@ __global__ __launch_bounds__(kThreads) void k_ctl_a(Geometry g, Bufs B, StepArgs
   }
 }
 
-// ---------------------------------------------------------------------------
-// Pass B.  Grid GB, persistent over 128-row super-tiles; wave w computes rows
-// [32w, 32w+32) of each super-tile for all r32 columns:
-//   acc (D layout) = Theta^T (A operand, from LDS or global) x Xhat^T (B operand,
-//   lane l loads row l%32, features 32ch + 16 (l/32) + [0, 16)).
-// Epilogue per element: w = max(u + 2 alpha acc - alpha ybar p - alpha s, 0).
-// ---------------------------------------------------------------------------
-template <int NB, bool THETA_LDS, bool VEC>
-__global__ __launch_bounds__(kThreads) void k_pass_b(Geometry g, Bufs B, StepArgs S) {
-  if (halted(B.ctl)) return;
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  float* th_s = reinterpret_cast<float*>(smem_raw);                 // d32*r32 if THETA_LDS
-  float* ps = th_s + (THETA_LDS ? g.d32 * g.r32 : 0);               // r32
-  float* ss = ps + g.r32;                                           // r32
-  double* colred = reinterpret_cast<double*>(ss + g.r32);          // 4 x r32
-  double* dred = colred + 4 * g.r32;                                // 8
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int h = lane >> 5;
-  const int li = lane & 31;
-  const int64_t n = g.n;
-  const int d = g.d, r = g.r, r32 = g.r32;
-  const int nch = g.nch;
-  const float cf = B.ctl->c_f;
-  const float gam = S.gamma_f;
-  const float two_alpha = S.two_alpha_f;
-  const float neg_alpha = -S.alpha_f;
-
-  if (THETA_LDS) {
-    const int tot4 = (g.d32 * r32) >> 2;
-    const f32x4* src = reinterpret_cast<const f32x4*>(B.theta);
-    f32x4* dst = reinterpret_cast<f32x4*>(th_s);
-    for (int v = tid; v < tot4; v += kThreads) dst[v] = src[v];
-  }
-  for (int c = tid; c < r32; c += kThreads) {
-    ps[c] = B.p[c];
-    ss[c] = B.s[c];
-  }
-  __syncthreads();
-  const float* theta = THETA_LDS ? th_s : B.theta;
-
-  double sa = 0.0, sb = 0.0, sh = 0.0;
-  // column sums: per 32-column block, a 16-value reduce-scatter over lane bits
-  // 16, 8, 4, 2 leaves one value per lane; lanes l and l^1 then share a column
-  double colacc[NB];
+// W of four columns c .. c + 3 of a row (ok: the row exists and c < r), as one store where all four
+// exist.
+template <bool UN>
+__device__ __forceinline__ void store4(float* urow, int c, int r, bool ok, const float* w) {
+  if (!ok) return;
+  if constexpr (UN) {
+    if (c + 4 <= r) {
+      *reinterpret_cast<f32x4u*>(urow + c) = (f32x4u){w[0], w[1], w[2], w[3]};
+    } else {
 #pragma unroll
-  for (int m = 0; m < NB; ++m) colacc[m] = 0.0;
-  int base = 0;  // local index (8 qd + e ordering) of the value this lane keeps
-  {
-    if (li & 16) base += 8;
-    if (li & 8) base += 4;
-    if (li & 4) base += 2;
-    if (li & 2) base += 1;
-  }
-
-  const int64_t sb0 = (int64_t)blockIdx.x * g.tilesB / g.GB;
-  const int64_t sb1 = (int64_t)(blockIdx.x + 1) * g.tilesB / g.GB;
-  for (int64_t st = sb0; st < sb1; ++st) {
-    const int64_t pt = st * kTPB + wave * 32 + li;
-    const bool vpt = pt < n;
-    f32x16 acc[NB];
-#pragma unroll
-    for (int j = 0; j < NB; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
-
-    const float* xrow = B.X + (vpt ? pt : 0) * (int64_t)d;
-    for (int ch = 0; ch < nch; ++ch) {
-      const int fb = ch * 32 + h * 16;
-      float xv[16];
-      if (VEC) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          f32x4 t = {0.f, 0.f, 0.f, 0.f};
-          if (vpt && fb + 4 * q < d) t = *reinterpret_cast<const f32x4*>(xrow + fb + 4 * q);
-          xv[4 * q + 0] = t.x;
-          xv[4 * q + 1] = t.y;
-          xv[4 * q + 2] = t.z;
-          xv[4 * q + 3] = t.w;
-        }
-      } else {
-#pragma unroll
-        for (int q = 0; q < 16; ++q) xv[q] = (vpt && fb + q < d) ? xrow[fb + q] : 0.f;
-      }
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-#pragma unroll
-        for (int m = 0; m < NB; ++m) {
-          const f32x4 a = *reinterpret_cast<const f32x4*>(theta + ((((int64_t)ch * 4 + j) * NB + m) * 64 + lane) * 4);
-          acc[m] = mfma32x32x2(a.x, xv[4 * j + 0], acc[m]);
-          acc[m] = mfma32x32x2(a.y, xv[4 * j + 1], acc[m]);
-          acc[m] = mfma32x32x2(a.z, xv[4 * j + 2], acc[m]);
-          acc[m] = mfma32x32x2(a.w, xv[4 * j + 3], acc[m]);
-        }
-      }
+      for (int e = 0; e < 3; ++e)
+        if (c + e < r) urow[c + e] = w[e];
     }
-
-    // ---- epilogue ----
-    // lane holds row pt and columns 32 m + 8 qd + 4 h + e (m < NB, qd < 4, e < 4)
-    // (the opaque copy keeps the p/s reads inside the tile loop instead of
-    // hoisting 2*16*NB loop-invariant registers out of it)
-    int lds_off = 0;  // opaque zero offset: keeps the reads in LDS address space
-    asm volatile("" : "+v"(lds_off));
-    const float* psl = ps + lds_off;
-    const float* ssl = ss + lds_off;
-    float* urow = B.U + (vpt ? pt : 0) * (int64_t)r;
-    auto load_u4 = [&](int c, float out[4]) {
-      if (VEC) {
-        f32x4 t = {0.f, 0.f, 0.f, 0.f};
-        if (vpt && c < r) t = *reinterpret_cast<const f32x4*>(urow + c);
-        out[0] = t.x * cf;
-        out[1] = t.y * cf;
-        out[2] = t.z * cf;
-        out[3] = t.w * cf;
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) out[e] = (vpt && c + e < r) ? urow[c + e] * cf : 0.f;
-      }
-    };
-    // q = u.p - 1 (fp32 dot over the lane's half of the row, then the other half)
-    float dotf = 0.f;
-#pragma unroll
-    for (int m = 0; m < NB; ++m)
-#pragma unroll
-      for (int qd = 0; qd < 4; ++qd) {
-        const int c = 32 * m + 8 * qd + 4 * h;
-        float u4[4];
-        load_u4(c, u4);
-        const f32x4 pv = *reinterpret_cast<const f32x4*>(psl + c);
-        dotf = fmaf(u4[0], pv.x, dotf);
-        dotf = fmaf(u4[1], pv.y, dotf);
-        dotf = fmaf(u4[2], pv.z, dotf);
-        dotf = fmaf(u4[3], pv.w, dotf);
-      }
-    dotf += shfl_xor_f(dotf, 32);
-    float ybar = 0.f;
-    if (vpt) ybar = fmaf(gam, dotf - 1.0f, B.y[pt]);
-#pragma unroll
-    for (int m = 0; m < NB; ++m) {
-      float wv[16];
-#pragma unroll
-      for (int qd = 0; qd < 4; ++qd) {
-        const int c = 32 * m + 8 * qd + 4 * h;
-        float u4[4];
-        load_u4(c, u4);
-        const f32x4 pv = *reinterpret_cast<const f32x4*>(psl + c);
-        const f32x4 sv = *reinterpret_cast<const f32x4*>(ssl + c);
-        const float pe[4] = {pv.x, pv.y, pv.z, pv.w};
-        const float se[4] = {sv.x, sv.y, sv.z, sv.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float uu = u4[e];
-          float t = fmaf(two_alpha, acc[m][4 * qd + e], uu);
-          t = fmaf(neg_alpha, ybar * pe[e], t);
-          t = fmaf(neg_alpha, se[e], t);
-          float w = fmaxf(t, 0.f);
-          if (!vpt || c + e >= r) w = 0.f;
-          wv[4 * qd + e] = w;
-          const double wd = (double)w, ud = (double)uu;
-          sa = fma(wd, wd, sa);
-          sb = fma(ud, ud, sb);
-          sh = fma(wd, ud, sh);
-        }
-        if (vpt) {
-          if (VEC) {
-            if (c < r) {
-              f32x4 o = {wv[4 * qd + 0], wv[4 * qd + 1], wv[4 * qd + 2], wv[4 * qd + 3]};
-              *reinterpret_cast<f32x4*>(urow + c) = o;
-            }
-          } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              if (c + e < r) urow[c + e] = wv[4 * qd + e];
-          }
-        }
-      }
-      reduce_scatter<16, 16>(wv, li);
-      colacc[m] += (double)wv[0];
-    }
-  }
-
-  // ---- workgroup partials ----
-  for (int c = tid; c < 4 * r32; c += kThreads) colred[c] = 0.0;
-  __syncthreads();
-#pragma unroll
-  for (int m = 0; m < NB; ++m) {
-    const double v = colacc[m] + shfl_xor_d(colacc[m], 1);
-    if ((li & 1) == 0) {
-      const int col = 32 * m + 8 * (base >> 2) + 4 * h + (base & 3);
-      colred[wave * r32 + col] = v;
-    }
-  }
-  __syncthreads();
-  double* out = B.b_part + (int64_t)blockIdx.x * (4 + r32);
-  for (int c = tid; c < r32; c += kThreads)
-    out[4 + c] = ((colred[c] + colred[r32 + c]) + colred[2 * r32 + c]) + colred[3 * r32 + c];
-  const double ta = block_sum_d(sa, dred);
-  const double tb2 = block_sum_d(sb, dred);
-  const double th = block_sum_d(sh, dred);
-  if (tid == 0) {
-    out[0] = ta;
-    out[1] = tb2;
-    out[2] = th;
-    out[3] = 0.0;
+  } else {
+    *reinterpret_cast<f32x4*>(urow + c) = (f32x4){w[0], w[1], w[2], w[3]};
   }
 }
 
 // ---------------------------------------------------------------------------
-// Pass B with Theta streamed through LDS, for a Theta that does not fit pass B's 64 KiB
-// of LDS beside p, s and the reductions, and 16-byte rows.  As k_pass_b (waves, rows, the operand
-// layout of Theta and the k-order of the products), with the columns in groups of
-// CG blocks (the last group may be short): per 128-row super-tile, for each group
+// Pass B with Theta streamed through LDS, for every shape the resident form below does not hold.
+// Grid GB, persistent over 128-row super-tiles; wave w computes rows [32w, 32w+32) of each:
+//   acc (D layout) = Theta^T (A operand) x Xhat^T (B operand, lane l loads row l%32, features
+//   32ch + 16 (l/32) + [0, 16)),
+// then the epilogue per element, w = max(u + 2 alpha acc - alpha ybar p - alpha s, 0).  The columns
+// go in groups of CG blocks (the last group may be short): per super-tile, for each group
 // and each 32-feature chunk, the workgroup stages the chunk's Theta operands (4 KiB
 // per block) in one of two LDS buffers and every wave multiplies its rows by them.
 // The next chunk's Theta operands and Xhat features are loaded into registers while
@@ -1286,8 +906,9 @@ __global__ __launch_bounds__(kThreads) void k_pass_b(Geometry g, Bufs B, StepArg
 // behind a branch.  Above 128 columns ybar comes from the row launch of pass A
 // (which stores it), else from q = u.p - 1 formed here.  Column sums: lanes l and
 // l ^ 1 combined, then added to the wave's row of an LDS table per super-tile.
+// UN: rows of X or U not 16-byte aligned.
 // ---------------------------------------------------------------------------
-template <int CG>
+template <int CG, bool UN>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_pass_b_stream(
     Geometry g, Bufs B, StepArgs S) {
   if (halted(B.ctl)) return;
@@ -1342,6 +963,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
   }
   f32x4 tr[CG];
   f32x4 xr[4];
+  // super-tiles from this one on read rows by elements (it holds the last row)
+  const int64_t edge_st = g.tilesB - 1;
   auto load_chunk = [&](int64_t st, int cgi, int ch) {
     // (an opaque zero keeps the address arithmetic here, not hoisted out of the loops
     // into registers that would stay live across them)
@@ -1356,8 +979,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
     const int64_t pt = st * kTPB + wave * 32 + li + z;
     const float* xrow = B.X + (pt < n ? pt : 0) * (int64_t)d;
     const int fb = ch * 32 + h * 16;
+    if (UN && (st >= edge_st || d < 3)) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) xr[q] = *reinterpret_cast<const f32x4*>(xrow + (fb + 4 * q < d ? fb + 4 * q : 0));
+      for (int q = 0; q < 4; ++q) xr[q] = load4_edge(xrow, fb + 4 * q < d ? fb + 4 * q : 0, d);
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) xr[q] = load4<UN>(xrow + (fb + 4 * q < d ? fb + 4 * q : 0));
+    }
   };
 
   if (sb0 < sb1) load_chunk(sb0, 0, 0);
@@ -1366,6 +994,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
     const int64_t pt = st * kTPB + wave * 32 + li;
     const bool vpt = pt < n;
     float* urow = B.U + (vpt ? pt : 0) * (int64_t)r;
+    const bool uedge = UN && (st >= edge_st || r < 3);
     // (the opaque copy keeps the p/s reads inside the tile loop instead of hoisting
     // loop-invariant registers out of it)
     int lds_off = 0;
@@ -1384,13 +1013,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
 #pragma unroll
         for (int qd = 0; qd < 4; ++qd) {
           const int c = 32 * m + 8 * qd + 4 * h;
-          const f32x4 t = *reinterpret_cast<const f32x4*>(urow + (c < r ? c : 0));
+          const f32x4 t = (UN && uedge) ? load4_edge(urow, c < r ? c : 0, r) : load4<UN>(urow + (c < r ? c : 0));
           const bool ok = vpt && c < r;
           const f32x4 pv = *reinterpret_cast<const f32x4*>(psl + c);
           dotf = fmaf(ok ? t.x * cf : 0.f, pv.x, dotf);
-          dotf = fmaf(ok ? t.y * cf : 0.f, pv.y, dotf);
-          dotf = fmaf(ok ? t.z * cf : 0.f, pv.z, dotf);
-          dotf = fmaf(ok ? t.w * cf : 0.f, pv.w, dotf);
+          dotf = fmaf((UN ? ok && c + 1 < r : ok) ? t.y * cf : 0.f, pv.y, dotf);
+          dotf = fmaf((UN ? ok && c + 2 < r : ok) ? t.z * cf : 0.f, pv.z, dotf);
+          dotf = fmaf((UN ? ok && c + 3 < r : ok) ? t.w * cf : 0.f, pv.w, dotf);
         }
       dotf += shfl_xor_f(dotf, 32);
       const float yv = B.y[vpt ? pt : 0];
@@ -1452,7 +1081,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
 #pragma unroll
           for (int qd = 0; qd < 4; ++qd) {
             const int c = 32 * (cgi * CG + m) + 8 * qd + 4 * h;
-            ua[m][qd] = *reinterpret_cast<const f32x4*>(urow + (c < r ? c : 0));
+            ua[m][qd] = (UN && uedge) ? load4_edge(urow, c < r ? c : 0, r) : load4<UN>(urow + (c < r ? c : 0));
           }
       });
       // ---- epilogue of the group: lane holds row pt, columns 32 (CG cgi + m) + 8 qd + 4 h + e ----
@@ -1472,8 +1101,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
           for (int qd = 0; qd < 4; ++qd) {
             const int c = 32 * mb + 8 * qd + 4 * h;
             const bool ok = vpt && c < r;
-            const float u4[4] = {ok ? ua[m][qd].x * cf : 0.f, ok ? ua[m][qd].y * cf : 0.f,
-                                 ok ? ua[m][qd].z * cf : 0.f, ok ? ua[m][qd].w * cf : 0.f};
+            float u4[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) u4[e] = (UN ? ok && c + e < r : ok) ? ua[m][qd][e] * cf : 0.f;
             const f32x4 pv = *reinterpret_cast<const f32x4*>(psl + c);
             const f32x4 sv = *reinterpret_cast<const f32x4*>(ssl + c);
             const float pe[4] = {pv.x, pv.y, pv.z, pv.w};
@@ -1492,10 +1122,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
               sb = fma(ud, ud, sb);
               sh = fma(wd, ud, sh);
             }
-            if (ok) {
-              const f32x4 o = {wv[4 * qd + 0], wv[4 * qd + 1], wv[4 * qd + 2], wv[4 * qd + 3]};
-              *reinterpret_cast<f32x4*>(urow + c) = o;
-            }
+            store4<UN>(urow, c, r, ok, &wv[4 * qd]);
           }
           reduce_scatter<16, 16>(wv, li);
           const double v = (double)wv[0] + shfl_xor_d((double)wv[0], 1);
@@ -1524,201 +1151,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
 }
 
 // ---------------------------------------------------------------------------
-// Pass B above 256 columns (NB = 10, 12 or 14 blocks of 32).  As k_pass_b, with
-// the columns taken two blocks at a time: per 128-row super-tile each wave forms
-// q = u.p - 1 over the whole row first, then for each pair of column blocks the
-// product (the Xhat row chunks re-read from cache), the epilogue and W; column
-// sums go to the wave's row of LDS per tile (lanes l and l^1 combined first).
-// ---------------------------------------------------------------------------
-template <bool THETA_LDS, bool VEC>
-__global__ __launch_bounds__(kThreads) void k_pass_b_wide(Geometry g, Bufs B, StepArgs S) {
-  if (halted(B.ctl)) return;
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  float* th_s = reinterpret_cast<float*>(smem_raw);                 // d32*r32 if THETA_LDS
-  float* ps = th_s + (THETA_LDS ? g.d32 * g.r32 : 0);               // r32
-  float* ss = ps + g.r32;                                           // r32
-  double* colred = reinterpret_cast<double*>(ss + g.r32);          // 4 x r32
-  double* dred = colred + 4 * g.r32;                                // 8
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int h = lane >> 5;
-  const int li = lane & 31;
-  const int64_t n = g.n;
-  const int d = g.d, r = g.r, r32 = g.r32, NBt = g.NB;
-  const int nch = g.nch;
-  const float cf = B.ctl->c_f;
-  const float gam = S.gamma_f;
-  const float two_alpha = S.two_alpha_f;
-  const float neg_alpha = -S.alpha_f;
-
-  if (THETA_LDS) {
-    const int tot4 = (g.d32 * r32) >> 2;
-    const f32x4* src = reinterpret_cast<const f32x4*>(B.theta);
-    f32x4* dst = reinterpret_cast<f32x4*>(th_s);
-    for (int v = tid; v < tot4; v += kThreads) dst[v] = src[v];
-  }
-  for (int c = tid; c < r32; c += kThreads) {
-    ps[c] = B.p[c];
-    ss[c] = B.s[c];
-  }
-  for (int c = tid; c < 4 * r32; c += kThreads) colred[c] = 0.0;
-  __syncthreads();
-  const float* theta = THETA_LDS ? th_s : B.theta;
-
-  double sa = 0.0, sb = 0.0, sh = 0.0;
-  int base = 0;  // local index (8 qd + e ordering) of the column sum this lane keeps
-  if (li & 16) base += 8;
-  if (li & 8) base += 4;
-  if (li & 4) base += 2;
-  if (li & 2) base += 1;
-
-  const int64_t sb0 = (int64_t)blockIdx.x * g.tilesB / g.GB;
-  const int64_t sb1 = (int64_t)(blockIdx.x + 1) * g.tilesB / g.GB;
-  for (int64_t st = sb0; st < sb1; ++st) {
-    const int64_t pt = st * kTPB + wave * 32 + li;
-    const bool vpt = pt < n;
-    const float* xrow = B.X + (vpt ? pt : 0) * (int64_t)d;
-    float* urow = B.U + (vpt ? pt : 0) * (int64_t)r;
-    auto load_u4 = [&](int c, float out[4]) {
-      if (VEC) {
-        f32x4 t = {0.f, 0.f, 0.f, 0.f};
-        if (vpt && c < r) t = *reinterpret_cast<const f32x4*>(urow + c);
-        out[0] = t.x * cf;
-        out[1] = t.y * cf;
-        out[2] = t.z * cf;
-        out[3] = t.w * cf;
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) out[e] = (vpt && c + e < r) ? urow[c + e] * cf : 0.f;
-      }
-    };
-    // q = u.p - 1 over the whole row (fp32 dot over the lane's half, then the other half)
-    float dotf = 0.f;
-    for (int m = 0; m < NBt; ++m)
-#pragma unroll
-      for (int qd = 0; qd < 4; ++qd) {
-        const int c = 32 * m + 8 * qd + 4 * h;
-        float u4[4];
-        load_u4(c, u4);
-        const f32x4 pv = *reinterpret_cast<const f32x4*>(ps + c);
-        dotf = fmaf(u4[0], pv.x, dotf);
-        dotf = fmaf(u4[1], pv.y, dotf);
-        dotf = fmaf(u4[2], pv.z, dotf);
-        dotf = fmaf(u4[3], pv.w, dotf);
-      }
-    dotf += shfl_xor_f(dotf, 32);
-    float ybar = 0.f;
-    if (vpt) ybar = fmaf(gam, dotf - 1.0f, B.y[pt]);
-
-    for (int cg = 0; cg < NBt; cg += 2) {
-      f32x16 acc[2];
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
-      for (int ch = 0; ch < nch; ++ch) {
-        const int fb = ch * 32 + h * 16;
-        float xv[16];
-        if (VEC) {
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            f32x4 t = {0.f, 0.f, 0.f, 0.f};
-            if (vpt && fb + 4 * q < d) t = *reinterpret_cast<const f32x4*>(xrow + fb + 4 * q);
-            xv[4 * q + 0] = t.x;
-            xv[4 * q + 1] = t.y;
-            xv[4 * q + 2] = t.z;
-            xv[4 * q + 3] = t.w;
-          }
-        } else {
-#pragma unroll
-          for (int q = 0; q < 16; ++q) xv[q] = (vpt && fb + q < d) ? xrow[fb + q] : 0.f;
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-#pragma unroll
-          for (int m = 0; m < 2; ++m) {
-            const f32x4 a =
-                *reinterpret_cast<const f32x4*>(theta + ((((int64_t)ch * 4 + j) * NBt + cg + m) * 64 + lane) * 4);
-            acc[m] = mfma32x32x2(a.x, xv[4 * j + 0], acc[m]);
-            acc[m] = mfma32x32x2(a.y, xv[4 * j + 1], acc[m]);
-            acc[m] = mfma32x32x2(a.z, xv[4 * j + 2], acc[m]);
-            acc[m] = mfma32x32x2(a.w, xv[4 * j + 3], acc[m]);
-          }
-        }
-      }
-      // ---- epilogue of the pair: lane holds row pt, columns 32 (cg + m) + 8 qd + 4 h + e ----
-#pragma unroll
-      for (int m = 0; m < 2; ++m) {
-        float wv[16];
-#pragma unroll
-        for (int qd = 0; qd < 4; ++qd) {
-          const int c = 32 * (cg + m) + 8 * qd + 4 * h;
-          float u4[4];
-          load_u4(c, u4);
-          const f32x4 pv = *reinterpret_cast<const f32x4*>(ps + c);
-          const f32x4 sv = *reinterpret_cast<const f32x4*>(ss + c);
-          const float pe[4] = {pv.x, pv.y, pv.z, pv.w};
-          const float se[4] = {sv.x, sv.y, sv.z, sv.w};
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float uu = u4[e];
-            float t = fmaf(two_alpha, acc[m][4 * qd + e], uu);
-            t = fmaf(neg_alpha, ybar * pe[e], t);
-            t = fmaf(neg_alpha, se[e], t);
-            float w = fmaxf(t, 0.f);
-            if (!vpt || c + e >= r) w = 0.f;
-            wv[4 * qd + e] = w;
-            const double wd = (double)w, ud = (double)uu;
-            sa = fma(wd, wd, sa);
-            sb = fma(ud, ud, sb);
-            sh = fma(wd, ud, sh);
-          }
-          if (vpt) {
-            if (VEC) {
-              if (c < r) {
-                f32x4 o = {wv[4 * qd + 0], wv[4 * qd + 1], wv[4 * qd + 2], wv[4 * qd + 3]};
-                *reinterpret_cast<f32x4*>(urow + c) = o;
-              }
-            } else {
-#pragma unroll
-              for (int e = 0; e < 4; ++e)
-                if (c + e < r) urow[c + e] = wv[4 * qd + e];
-            }
-          }
-        }
-        reduce_scatter<16, 16>(wv, li);
-        double v = (double)wv[0];
-        v += shfl_xor_d(v, 1);
-        if ((li & 1) == 0) colred[wave * r32 + 32 * (cg + m) + 8 * (base >> 2) + 4 * h + (base & 3)] += v;
-      }
-    }
-  }
-
-  // ---- workgroup partials ----
-  __syncthreads();
-  double* out = B.b_part + (int64_t)blockIdx.x * (4 + r32);
-  for (int c = tid; c < r32; c += kThreads)
-    out[4 + c] = ((colred[c] + colred[r32 + c]) + colred[2 * r32 + c]) + colred[3 * r32 + c];
-  const double ta = block_sum_d(sa, dred);
-  const double tb2 = block_sum_d(sb, dred);
-  const double th = block_sum_d(sh, dred);
-  if (tid == 0) {
-    out[0] = ta;
-    out[1] = tb2;
-    out[2] = th;
-    out[3] = 0.0;
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Pass B, resident-tile form (d <= 128, r <= 128, 16-byte rows).  Same
-// arithmetic and partial layout as k_pass_b; each wave holds its tile's whole
+// Pass B, resident-tile form (d <= 128, r <= 128, Theta in LDS).  Same
+// arithmetic and partial layout as the streamed form; each wave holds its tile's whole
 // Xhat slab (NCH chunks) and U slab in registers: the U loads of a tile are
 // issued before its matrix product and the next tile's Xhat before its epilogue.
+// UN: rows of X or U not 16-byte aligned (float by float, each tile's loads in front of its
+// products: 113 us at 700,001 x 51 x 13).
 // ---------------------------------------------------------------------------
-template <int NB, int NCH>
+template <int NB, int NCH, bool UN>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_pass_b_res(
     Geometry g, Bufs B, StepArgs S) {
   if (halted(B.ctl)) return;
@@ -1766,16 +1206,28 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
   const int64_t sb0 = (int64_t)blockIdx.x * g.tilesB / g.GB;
   const int64_t sb1 = (int64_t)(blockIdx.x + 1) * g.tilesB / g.GB;
 
+  // tiles from this one on read rows by elements (it holds the last row)
+  const int64_t edge_st = g.tilesB - 1;
   float xv[NCH][16];
   auto load_x = [&](int64_t st, int ch) {
     const int64_t pt = st * kTPB + wave * 32 + li;
     const bool ok = (st < sb1) && (pt < n);
     const float* xrow = B.X + (ok ? pt : 0) * (int64_t)d;
+    // raw values: features >= d meet zero rows of Theta, rows >= n are masked in the epilogue
+    if (UN && (st >= edge_st || d < 3)) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int f = ch * 32 + h * 16 + 4 * q;
+        const f32x4 t = load4_edge(xrow, f < d ? f : 0, d);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) xv[ch][4 * q + e] = t[e];
+      }
+      return;
+    }
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int f = ch * 32 + h * 16 + 4 * q;
-      // raw values: features >= d meet zero rows of Theta, rows >= n are masked in the epilogue
-      const f32x4 t = *reinterpret_cast<const f32x4*>(xrow + (f < d ? f : 0));
+      const f32x4 t = load4<UN>(xrow + (f < d ? f : 0));
       xv[ch][4 * q + 0] = t.x;
       xv[ch][4 * q + 1] = t.y;
       xv[ch][4 * q + 2] = t.z;
@@ -1796,13 +1248,23 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
     float* urow = B.U + (vpt ? pt : 0) * (int64_t)r;
     // epilogue operands, issued before the matrix product (raw; scaled and masked at use)
     f32x4 uraw[NB][4];
+    if (UN && (st >= edge_st || r < 3)) {
 #pragma unroll
-    for (int m = 0; m < NB; ++m)
+      for (int m = 0; m < NB; ++m)
 #pragma unroll
-      for (int qd = 0; qd < 4; ++qd) {
-        const int c = 32 * m + 8 * qd + 4 * h;
-        uraw[m][qd] = *reinterpret_cast<const f32x4*>(urow + (c < r ? c : 0));
-      }
+        for (int qd = 0; qd < 4; ++qd) {
+          const int c = 32 * m + 8 * qd + 4 * h;
+          uraw[m][qd] = load4_edge(urow, c < r ? c : 0, r);
+        }
+    } else {
+#pragma unroll
+      for (int m = 0; m < NB; ++m)
+#pragma unroll
+        for (int qd = 0; qd < 4; ++qd) {
+          const int c = 32 * m + 8 * qd + 4 * h;
+          uraw[m][qd] = load4<UN>(urow + (c < r ? c : 0));
+        }
+    }
     const float yraw = B.y[vpt ? pt : 0];
     __builtin_amdgcn_sched_barrier(0);
 
@@ -1837,11 +1299,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
     for (int m = 0; m < NB; ++m)
 #pragma unroll
       for (int qd = 0; qd < 4; ++qd) {
-        const bool ok = vpt && (32 * m + 8 * qd + 4 * h) < r;
-        u[m][4 * qd + 0] = ok ? uraw[m][qd].x * cf : 0.f;
-        u[m][4 * qd + 1] = ok ? uraw[m][qd].y * cf : 0.f;
-        u[m][4 * qd + 2] = ok ? uraw[m][qd].z * cf : 0.f;
-        u[m][4 * qd + 3] = ok ? uraw[m][qd].w * cf : 0.f;
+        const int c = 32 * m + 8 * qd + 4 * h;
+        const bool ok = vpt && c < r;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) u[m][4 * qd + e] = (UN ? ok && c + e < r : ok) ? uraw[m][qd][e] * cf : 0.f;
       }
     float dotf = 0.f;
 #pragma unroll
@@ -1880,10 +1341,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
           sb = fma(ud, ud, sb);
           sh = fma(wd, ud, sh);
         }
-        // unconditional store (invalid lanes write the dump slot): no branch around it
-        float* dst = (vpt && c < r) ? (urow + c) : B.dump;
-        f32x4 o = {wv[4 * qd + 0], wv[4 * qd + 1], wv[4 * qd + 2], wv[4 * qd + 3]};
-        *reinterpret_cast<f32x4*>(dst) = o;
+        if constexpr (UN) {
+          store4<true>(urow, c, r, vpt && c < r, &wv[4 * qd]);
+        } else {
+          // unconditional store (invalid lanes write the dump slot): no branch around it
+          float* dst = (vpt && c < r) ? (urow + c) : B.dump;
+          f32x4 o = {wv[4 * qd + 0], wv[4 * qd + 1], wv[4 * qd + 2], wv[4 * qd + 3]};
+          *reinterpret_cast<f32x4*>(dst) = o;
+        }
       }
       reduce_scatter<16, 16>(wv, li);
       colacc[m] += (double)wv[0];
@@ -2267,60 +1732,31 @@ static hipError_t allow_lds(F* kern, size_t lds) {
                              (int)lds);
 }
 
-// Dynamic LDS of k_pass_a in a mode: the staged tiles, ybar and p, the reductions; the
-// combine of the k-slices (MBG < 4) overlaps the tiles
-template <int MBG, int NBG, int MODE>
-static size_t pass_a_lds(const Geometry& g) {
-  const bool theta = MODE == kAIter || MODE == kATheta;
-  const int64_t us = MODE == kATheta ? NBG * 32 + 4 : g.us_stride;
-  const int64_t floats = (theta ? (int64_t)kTPA * g.xs_stride : 0) + (int64_t)kTPA * us + kTPA + g.r32;
-  int64_t bytes = floats * 4 + (256 + 8) * 8;
-  const int64_t comb = (int64_t)MBG * NBG * 16 * 64 * 4;
-  if (theta && MBG < 4 && comb > floats * 4) bytes = comb + (256 + 8) * 8 + 64;
-  return (size_t)((bytes + 15) & ~15);
-}
-
-template <int MBG, int NBG, int MODE>
-static hipError_t pass_a_launch(const Geometry& g, const Bufs& b, const StepArgs& a, hipStream_t st) {
-  // the finish pass writes no Theta partials: its grid is sized for the rows alone
-  const dim3 grid(MODE == kAFinish ? g.GAF : g.GA, MODE == kAFinish ? 1 : g.mgroups * g.ngroups);
-  const size_t lds = pass_a_lds<MBG, NBG, MODE>(g);
-  if (lds > (160u << 10)) return hipErrorInvalidValue;
-  hipError_t e = allow_lds(k_pass_a<MBG, NBG, MODE>, lds);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_pass_a<MBG, NBG, MODE>), grid, dim3(kThreads), lds, st, g, b, a);
-  return hipGetLastError();
-}
-
-template <int MBG, int MODE>
-static hipError_t pass_a_nbg(const Geometry& g, const Bufs& b, const StepArgs& a, hipStream_t st) {
-  switch (g.NBG) {
-    case 1: return pass_a_launch<MBG, 1, MODE>(g, b, a, st);
-    case 2: return pass_a_launch<MBG, 2, MODE>(g, b, a, st);
-    case 4: return pass_a_launch<MBG, 4, MODE>(g, b, a, st);
-    case 5: return pass_a_launch<MBG, 5, MODE>(g, b, a, st);
-    case 7: return pass_a_launch<MBG, 7, MODE>(g, b, a, st);
-    default: return hipErrorInvalidValue;
-  }
-}
-
-template <int MBG, int NBG>
+template <int MBG, int NBG, bool UN>
 static hipError_t theta_wide_launch(const Geometry& g, const Bufs& b, hipStream_t st) {
   const size_t tiles = (size_t)kTPA * ((MBG * 32 + 4) + (NBG * 32 + 4)) * 4;
   const size_t comb = MBG < 4 ? (size_t)MBG * NBG * 16 * 64 * 4 : 0;
   const size_t lds = tiles > comb ? tiles : comb;
-  hipError_t e = allow_lds(k_theta_wide<MBG, NBG>, lds);
+  hipError_t e = allow_lds(k_theta_wide<MBG, NBG, UN>, lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_theta_wide<MBG, NBG>), dim3(g.GA, g.mgroups * g.ngroups), dim3(kThreads), lds, st, g, b);
+  hipLaunchKernelGGL((k_theta_wide<MBG, NBG, UN>), dim3(g.GA, g.mgroups * g.ngroups), dim3(kThreads), lds, st, g, b);
   return hipGetLastError();
+}
+
+template <int MBG, int NBG>
+static hipError_t theta_wide_un(const Geometry& g, const Bufs& b, hipStream_t st) {
+  return (g.vec_x && g.vec_u) ? theta_wide_launch<MBG, NBG, false>(g, b, st)
+                              : theta_wide_launch<MBG, NBG, true>(g, b, st);
 }
 
 template <int MBG>
 static hipError_t theta_wide_nbg(const Geometry& g, const Bufs& b, hipStream_t st) {
   switch (g.NBG) {
-    case 4: return theta_wide_launch<MBG, 4>(g, b, st);
-    case 5: return theta_wide_launch<MBG, 5>(g, b, st);
-    case 7: return theta_wide_launch<MBG, 7>(g, b, st);
+    case 1: return theta_wide_un<MBG, 1>(g, b, st);
+    case 2: return theta_wide_un<MBG, 2>(g, b, st);
+    case 4: return theta_wide_un<MBG, 4>(g, b, st);
+    case 5: return theta_wide_un<MBG, 5>(g, b, st);
+    case 7: return theta_wide_un<MBG, 7>(g, b, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -2334,39 +1770,56 @@ static hipError_t launch_theta_wide(const Geometry& g, const Bufs& b, hipStream_
   }
 }
 
+template <bool FINISH>
 static hipError_t launch_rows_wide(const Geometry& g, const Bufs& b, const StepArgs& a, hipStream_t st) {
   const dim3 grid(g.GAF), blk(kThreads);
   switch ((g.r + 63) / 64) {
-    case 3: hipLaunchKernelGGL(k_rows_wide<3>, grid, blk, 0, st, g, b, a); break;
-    case 4: hipLaunchKernelGGL(k_rows_wide<4>, grid, blk, 0, st, g, b, a); break;
-    case 5: hipLaunchKernelGGL(k_rows_wide<5>, grid, blk, 0, st, g, b, a); break;
-    case 6: hipLaunchKernelGGL(k_rows_wide<6>, grid, blk, 0, st, g, b, a); break;
-    case 7: hipLaunchKernelGGL(k_rows_wide<7>, grid, blk, 0, st, g, b, a); break;
+    case 1: hipLaunchKernelGGL((k_rows_wide<1, FINISH>), grid, blk, 0, st, g, b, a); break;
+    case 2: hipLaunchKernelGGL((k_rows_wide<2, FINISH>), grid, blk, 0, st, g, b, a); break;
+    case 3: hipLaunchKernelGGL((k_rows_wide<3, FINISH>), grid, blk, 0, st, g, b, a); break;
+    case 4: hipLaunchKernelGGL((k_rows_wide<4, FINISH>), grid, blk, 0, st, g, b, a); break;
+    case 5: hipLaunchKernelGGL((k_rows_wide<5, FINISH>), grid, blk, 0, st, g, b, a); break;
+    case 6: hipLaunchKernelGGL((k_rows_wide<6, FINISH>), grid, blk, 0, st, g, b, a); break;
+    case 7: hipLaunchKernelGGL((k_rows_wide<7, FINISH>), grid, blk, 0, st, g, b, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
-template <int MODE>
-static hipError_t pass_a_mbg(const Geometry& g, const Bufs& b, const StepArgs& a, hipStream_t st) {
-  switch (g.MBG) {
-    case 1: return pass_a_nbg<1, MODE>(g, b, a, st);
-    case 2: return pass_a_nbg<2, MODE>(g, b, a, st);
-    case 4: return pass_a_nbg<4, MODE>(g, b, a, st);
-    default: return hipErrorInvalidValue;
-  }
+template <int FV, int NGF, int CV, bool UN>
+static hipError_t pass_a_rows_mode(const Geometry& g, const Bufs& b, const StepArgs& a, int mode, hipStream_t st) {
+  if (mode == kPassFinish)
+    hipLaunchKernelGGL((k_pass_a_rows<FV, NGF, CV, kPassFinish, UN>), dim3(g.GA), dim3(kThreads), 0, st, g, b, a);
+  else if (mode == kPassRows)
+    hipLaunchKernelGGL((k_pass_a_rows<FV, NGF, CV, kPassRows, UN>), dim3(g.GA), dim3(kThreads), 0, st, g, b, a);
+  else
+    hipLaunchKernelGGL((k_pass_a_rows<FV, NGF, CV, kPassIter, UN>), dim3(g.GA), dim3(kThreads), 0, st, g, b, a);
+  return hipGetLastError();
 }
 
 template <int FV, int NGF, int CV>
 static hipError_t pass_a_rows_launch(const Geometry& g, const Bufs& b, const StepArgs& a, int mode,
                                      hipStream_t st) {
-  if (mode == kPassFinish)
-    hipLaunchKernelGGL((k_pass_a_rows<FV, NGF, CV, kPassFinish>), dim3(g.GA), dim3(kThreads), 0, st, g, b, a);
-  else if (mode == kPassRows)
-    hipLaunchKernelGGL((k_pass_a_rows<FV, NGF, CV, kPassRows>), dim3(g.GA), dim3(kThreads), 0, st, g, b, a);
-  else
-    hipLaunchKernelGGL((k_pass_a_rows<FV, NGF, CV, kPassIter>), dim3(g.GA), dim3(kThreads), 0, st, g, b, a);
-  return hipGetLastError();
+  return pass_a_rows_mode<FV, NGF, CV, false>(g, b, a, mode, st);
+}
+
+// rows that are not whole aligned pieces: the fewest pieces of up to four features a lane
+static hipError_t pass_a_un_dispatch(const Geometry& g, const Bufs& b, const StepArgs& a, int mode, hipStream_t st) {
+  switch (g.a_fv * 100 + g.a_ngf * 10 + g.a_cv) {
+    case 111: return pass_a_rows_mode<1, 1, 1, true>(g, b, a, mode, st);
+    case 112: return pass_a_rows_mode<1, 1, 2, true>(g, b, a, mode, st);
+    case 114: return pass_a_rows_mode<1, 1, 4, true>(g, b, a, mode, st);
+    case 211: return pass_a_rows_mode<2, 1, 1, true>(g, b, a, mode, st);
+    case 212: return pass_a_rows_mode<2, 1, 2, true>(g, b, a, mode, st);
+    case 214: return pass_a_rows_mode<2, 1, 4, true>(g, b, a, mode, st);
+    case 411: return pass_a_rows_mode<4, 1, 1, true>(g, b, a, mode, st);
+    case 412: return pass_a_rows_mode<4, 1, 2, true>(g, b, a, mode, st);
+    case 414: return pass_a_rows_mode<4, 1, 4, true>(g, b, a, mode, st);
+    case 421: return pass_a_rows_mode<4, 2, 1, true>(g, b, a, mode, st);
+    case 422: return pass_a_rows_mode<4, 2, 2, true>(g, b, a, mode, st);
+    case 424: return pass_a_rows_mode<4, 2, 4, true>(g, b, a, mode, st);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 static hipError_t pass_a_rows_dispatch(const Geometry& g, const Bufs& b, const StepArgs& a, int finish,
@@ -2381,6 +1834,7 @@ static hipError_t pass_a_rows_dispatch(const Geometry& g, const Bufs& b, const S
       hipLaunchKernelGGL((k_rows_narrow<kPassRows>), dim3(g.GA), dim3(kThreads), 0, st, g, b, a);
     return hipGetLastError();
   }
+  if (g.a_un) return pass_a_un_dispatch(g, b, a, finish, st);
   const int key = g.a_fv * 100 + g.a_ngf * 10 + g.a_cv;
   switch (key) {
     case 111: return pass_a_rows_launch<1, 1, 1>(g, b, a, finish, st);
@@ -2412,16 +1866,9 @@ hipError_t launch_pass_u(const Geometry& g, const Bufs& b, const StepArgs& a, hi
 
 hipError_t launch_pass_a(const Geometry& g, const Bufs& b, const StepArgs& a, bool finish, hipStream_t st) {
   if (g.a_rows) return pass_a_rows_dispatch(g, b, a, finish ? kPassFinish : kPassIter, st);
-  if (finish) return pass_a_nbg<4, kAFinish>(g, b, a, st);
-  if (pass_a_split(g)) {
-    // wide factors: the row work (all columns staged) and the product (own columns only)
-    const hipError_t e = launch_rows_wide(g, b, a, st);
-    if (e != hipSuccess) return e;
-    // 16-byte rows: the product with the next tile prefetched into registers
-    if (g.vec_x && g.vec_u && (g.NBG == 4 || g.NBG == 5 || g.NBG == 7)) return launch_theta_wide(g, b, st);
-    return pass_a_mbg<kATheta>(g, b, a, st);
-  }
-  return pass_a_mbg<kAIter>(g, b, a, st);
+  if (finish) return launch_rows_wide<true>(g, b, a, st);
+  const hipError_t e = launch_rows_wide<false>(g, b, a, st);
+  return e != hipSuccess ? e : launch_theta_wide(g, b, st);
 }
 
 hipError_t launch_seg_theta(const Geometry& g, const Bufs& b, int64_t rows, int nseg, hipStream_t st) {
@@ -2461,10 +1908,8 @@ hipError_t launch_seg_a_rows(const Geometry& g, const Bufs& b, int64_t rows, boo
 }
 
 hipError_t launch_seg_a(const Geometry& g, const Bufs& b, bool finish, hipStream_t st) {
-  // the register-resident finish runs on the pass-A grid; the generic one, and the
-  // row-work launch of the split generic pass A, on GAF
-  const int64_t rows = ((finish && !g.a_rows) || (!finish && pass_a_split(g))) ? g.GAF : g.GA;
-  return launch_seg_a_rows(g, b, rows, finish, st);
+  // the register-resident forms run on the pass-A grid, the row launches on GAF
+  return launch_seg_a_rows(g, b, g.a_rows ? g.GA : g.GAF, finish, st);
 }
 
 hipError_t launch_seg_b(const Geometry& g, const Bufs& b, hipStream_t st) {
@@ -2485,31 +1930,22 @@ static hipError_t pass_b_stream_launch(const Geometry& g, const Bufs& b, const S
   // Theta buffers, the column-sum table, p, s, the reduction
   const size_t lds = (size_t)2 * 4 * CG * 256 * 4 + (size_t)4 * g.r32 * 8 + (size_t)2 * g.r32 * 4 + 4 * 8;
   if (lds > (160u << 10)) return hipErrorInvalidValue;
-  hipError_t e = allow_lds(k_pass_b_stream<CG>, lds);
+  const bool un = !(g.vec_x && g.vec_u);
+  hipError_t e = un ? allow_lds(k_pass_b_stream<CG, true>, lds) : allow_lds(k_pass_b_stream<CG, false>, lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_pass_b_stream<CG>), dim3(g.GB), dim3(kThreads), lds, st, g, b, a);
-  return hipGetLastError();
-}
-
-template <int NB>
-static hipError_t pass_b_nb(const Geometry& g, const Bufs& b, const StepArgs& a, hipStream_t st) {
-  const size_t lds = g.ldsB_bytes;
-  const dim3 grid(g.GB), blk(kThreads);
-  const bool vec = g.vec_x && g.vec_u;
-  if (lds > (64u << 10)) return hipErrorInvalidValue;  // the layout keeps pass B under 64 KiB
-  if (g.theta_lds) {
-    if (vec) hipLaunchKernelGGL((k_pass_b<NB, true, true>), grid, blk, lds, st, g, b, a);
-    else hipLaunchKernelGGL((k_pass_b<NB, true, false>), grid, blk, lds, st, g, b, a);
-  } else {
-    if (vec) hipLaunchKernelGGL((k_pass_b<NB, false, true>), grid, blk, lds, st, g, b, a);
-    else hipLaunchKernelGGL((k_pass_b<NB, false, false>), grid, blk, lds, st, g, b, a);
-  }
+  if (un)
+    hipLaunchKernelGGL((k_pass_b_stream<CG, true>), dim3(g.GB), dim3(kThreads), lds, st, g, b, a);
+  else
+    hipLaunchKernelGGL((k_pass_b_stream<CG, false>), dim3(g.GB), dim3(kThreads), lds, st, g, b, a);
   return hipGetLastError();
 }
 
 template <int NB, int NCH>
 static hipError_t pass_b_res_launch(const Geometry& g, const Bufs& b, const StepArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL((k_pass_b_res<NB, NCH>), dim3(g.GB), dim3(kThreads), g.ldsB_bytes, st, g, b, a);
+  if (g.vec_x && g.vec_u)
+    hipLaunchKernelGGL((k_pass_b_res<NB, NCH, false>), dim3(g.GB), dim3(kThreads), g.ldsB_bytes, st, g, b, a);
+  else
+    hipLaunchKernelGGL((k_pass_b_res<NB, NCH, true>), dim3(g.GB), dim3(kThreads), g.ldsB_bytes, st, g, b, a);
   return hipGetLastError();
 }
 
@@ -2527,42 +1963,14 @@ hipError_t launch_pass_b(const Geometry& g, const Bufs& b, const StepArgs& a, hi
       case 24: return pass_b_res_launch<2, 4>(g, b, a, st);
       case 41: return pass_b_res_launch<4, 1>(g, b, a, st);
       case 42: return pass_b_res_launch<4, 2>(g, b, a, st);
-      case 43: return pass_b_res_launch<4, 3>(g, b, a, st);
-      case 44: return pass_b_res_launch<4, 4>(g, b, a, st);
       default: return hipErrorInvalidValue;
     }
   }
-  if (!g.theta_lds && g.vec_x && g.vec_u) {
-    // Theta streamed through LDS in chunks, columns in groups of up to four blocks
-    switch (g.NB) {
-      case 1: return pass_b_stream_launch<1>(g, b, a, st);
-      case 2: return pass_b_stream_launch<2>(g, b, a, st);
-      case 10: return pass_b_stream_launch<2>(g, b, a, st);  // five exact groups of two
-      default: return pass_b_stream_launch<4>(g, b, a, st);  // groups of four blocks
-    }
-  }
-  if (g.NB > 8) {
-    // more than 256 columns, in pairs of column blocks
-    if (g.NB % 2 != 0 || g.NB > kMaxR / 32) return hipErrorInvalidValue;
-    const size_t lds = g.ldsB_bytes;
-    if (lds > (64u << 10)) return hipErrorInvalidValue;
-    const dim3 grid(g.GB), blk(kThreads);
-    const bool vec = g.vec_x && g.vec_u;
-    if (g.theta_lds) {
-      if (vec) hipLaunchKernelGGL((k_pass_b_wide<true, true>), grid, blk, lds, st, g, b, a);
-      else hipLaunchKernelGGL((k_pass_b_wide<true, false>), grid, blk, lds, st, g, b, a);
-    } else {
-      if (vec) hipLaunchKernelGGL((k_pass_b_wide<false, true>), grid, blk, lds, st, g, b, a);
-      else hipLaunchKernelGGL((k_pass_b_wide<false, false>), grid, blk, lds, st, g, b, a);
-    }
-    return hipGetLastError();
-  }
   switch (g.NB) {
-    case 1: return pass_b_nb<1>(g, b, a, st);
-    case 2: return pass_b_nb<2>(g, b, a, st);
-    case 4: return pass_b_nb<4>(g, b, a, st);
-    case 8: return pass_b_nb<8>(g, b, a, st);
-    default: return hipErrorInvalidValue;
+    case 1: return pass_b_stream_launch<1>(g, b, a, st);
+    case 2: return pass_b_stream_launch<2>(g, b, a, st);
+    case 10: return pass_b_stream_launch<2>(g, b, a, st);  // five exact groups of two
+    default: return pass_b_stream_launch<4>(g, b, a, st);  // groups of four blocks
   }
 }
 

@@ -36,8 +36,8 @@ Geometry make_geometry(int64_t n, int32_t d, int32_t r, int32_t K, bool aligned1
   // the two-pass kernels take in groups of two blocks
   g.NB = r <= 256 ? next_pow2((r + 31) / 32) : 2 * ((r + 63) / 64);
   g.r32 = 32 * g.NB;
-  // pass A groups: MBG in {1, 2, 4}, NBG in {1, 2, 4, 5, 7} dividing NB; 10 and 14 blocks
-  // (above 256 columns, where the product runs in a launch of its own) in two groups
+  // Theta product groups: MBG in {1, 2, 4}, NBG in {1, 2, 4, 5, 7} dividing NB; 10 and 14 blocks
+  // in two groups
   g.MBG = g.MB >= 3 ? 4 : g.MB;
   g.NBG = g.NB % 4 == 0 ? 4 : (g.NB % 2 == 0 ? 2 : 1);
   if (g.NB == 10 || g.NB == 14) g.NBG = g.NB / 2;
@@ -45,19 +45,16 @@ Geometry make_geometry(int64_t n, int32_t d, int32_t r, int32_t K, bool aligned1
   g.ngroups = (g.NB + g.NBG - 1) / g.NBG;
   g.tilesA = (n + kTPA - 1) / kTPA;
   {
-    const int64_t part_bytes = (int64_t)g.d32 * g.r32 * 4;
-    int64_t lim = (int64_t)64 << 20;
-    int64_t ga = lim / part_bytes;
-    // above 128 columns the product is a launch of its own (two workgroups per compute
-    // unit): one full round of them, without a partial second round
+    // the Theta product: above 128 columns one full round of two workgroups a compute unit, without a
+    // partial second round; else up to 1024 row chunks (64 MiB of partials): a chunk's sums are
+    // fp32, and shorter chunks keep their rounding small
+    int64_t ga = ((int64_t)64 << 20) / ((int64_t)g.d32 * g.r32 * 4);
     if (g.r32 > 128) ga = 512 / (g.mgroups * g.ngroups);
     if (ga < 16) ga = 16;
     if (ga > 1024) ga = 1024;
     if (ga > g.tilesA) ga = g.tilesA;
     g.GA = (int32_t)ga;
   }
-  g.xs_stride = g.MBG * 32;
-  g.us_stride = g.r32 + 4;
   // register-resident pass A (16x16x4 blocks): all of Theta in one wave, FV*NGF*CV <= 32
   {
     int fv = 1;
@@ -92,11 +89,10 @@ Geometry make_geometry(int64_t n, int32_t d, int32_t r, int32_t K, bool aligned1
   g.nch = g.d32 / 32;
   // Theta resident in pass B's LDS when it fits beside p, s and the reductions in 64 KiB
   g.theta_lds = ((int64_t)g.d32 * g.r32 * 4 + 2 * g.r32 * 4 + (4 * g.r32 + 8) * 8 <= (64 << 10)) ? 1 : 0;
-  // the streamed pass B (Theta from L2 through LDS, 16-byte rows): one persistent round of
-  // two workgroups per compute unit
-  if (!g.theta_lds && aligned16 && d % 4 == 0 && r % 4 == 0 && g.GB > 512) g.GB = 512;
-  g.b_res = (g.nch <= 4 && g.NB <= 4 && g.NB * g.nch <= 8 && g.theta_lds && d % 4 == 0 && r % 4 == 0 &&
-             aligned16) ? 1 : 0;
+  g.b_res = (g.nch <= 4 && g.NB <= 4 && g.NB * g.nch <= 8 && g.theta_lds) ? 1 : 0;
+  // the streamed pass B (Theta from L2 through LDS): one persistent round of two workgroups per
+  // compute unit
+  if (!g.b_res && g.GB > 512) g.GB = 512;
   g.ldsB_bytes = (int32_t)((g.theta_lds ? (int64_t)g.d32 * g.r32 * 4 : 0) + 2 * g.r32 * 4 +
                            (4 * g.r32 + 8) * 8);
   g.SB = (g.GB + 31) / 32;
@@ -152,7 +148,20 @@ Geometry make_geometry(int64_t n, int32_t d, int32_t r, int32_t K, bool aligned1
   }
   g.vec_x = (d % 4 == 0 && aligned16) ? 1 : 0;
   g.vec_u = (r % 4 == 0 && aligned16) ? 1 : 0;
-  // finish pass of the generic form: no Theta partials, so a grid for the rows alone
+  // register-resident pass A also where the rows are not whole aligned pieces (two-pass form only:
+  // which shapes take the single-pass form does not depend on it)
+  if (!g.fused && !g.a_rows && d <= 128 && r <= 64) {
+    g.a_rows = g.a_un = 1;
+    g.a_fv = d <= 16 ? 1 : (d <= 32 ? 2 : 4);
+    g.a_ngf = d <= 64 ? 1 : 2;
+    g.a_cv = r <= 16 ? 1 : (r <= 32 ? 2 : 4);
+    int64_t ga = (((n + 3) / 4) + 4 * 32 - 1) / (4 * 32);
+    g.GA = (int32_t)(ga > 1024 ? 1024 : (ga < 1 ? 1 : ga));
+    g.SA = (g.GA + 31) / 32;
+    if (g.SA > 64) g.SA = 64;
+    g.SAF = g.SA;
+  }
+  // row work and finish of the other shapes: no Theta partials, so a grid for the rows alone
   g.GAF = g.a_rows ? g.GA : (int32_t)(g.tilesA < 1024 ? g.tilesA : 1024);
   // split-fp16 panel form: the shapes the single-pass and resident kernels do not take
   g.panel = 0;

@@ -77,8 +77,8 @@ struct Geometry {
   int32_t mgroups, ngroups;
   int32_t GA;           // row-chunk workgroups per group
   int64_t tilesA;       // ceil(n / kTPA)
-  int32_t xs_stride, us_stride;
   int32_t a_rows;       // 1: register-resident pass A (k_pass_a_rows)
+  int32_t a_un;         // 1: with rows of X or U that are not whole 16-byte pieces
   int32_t a_fv, a_ngf, a_cv;  // its features per lane, feature groups, columns per lane
   // reduce theta
   int32_t RT;
@@ -190,8 +190,8 @@ Geometry make_geometry(int64_t n, int32_t d, int32_t r, int32_t K, bool aligned1
 // dynamic LDS of the fused pass B for (NB, nch, split, U moved as whole slabs)
 int fused_lds_need(int NB, int nch, bool split, bool uflat);
 bool fused8_shape(int NB, int nch, int r);
-// generic pass A above 128 columns: a row-work launch (GAF workgroups streaming rows
-// of U, storing ybar) and a Theta launch whose workgroups stage only their own columns
+// above 128 columns the row-work launch of pass A (GAF workgroups streaming rows of U) stores ybar
+// for pass B
 __host__ __device__ inline bool pass_a_split(const Geometry& g) { return !g.a_rows && g.r32 > 128; }
 constexpr int kMaxFusedLds = 160 << 10;
 size_t carve_workspace(const Geometry& g, char* base, Bufs* out);  // base may be null (size only)

@@ -223,6 +223,50 @@ def test_two_pass_wide_edges(n, d, r, K):
     assert not bad_gates
 
 
+# Two-pass fp32 form with rows that are not whole 16-byte pieces: rows shorter than a piece, one row
+# past and short of a tile (64 and 128 rows) and of the last tile, one to three columns past a piece
+# and a 32-block, the register-resident pass A and pass B (d <= 128, r <= 64), the row launch with one
+# to seven columns a lane, column groups of one, two and four blocks
+@pytest.mark.parametrize("n,d,r,K", [(5, 1, 1, 1), (4, 2, 1, 1), (129, 1, 2, 2), (130, 3, 3, 2), (128, 5, 2, 2),
+                                     (257, 17, 16, 4), (385, 51, 13, 9), (400, 33, 17, 5), (641, 97, 31, 6),
+                                     (513, 67, 33, 4), (300, 99, 63, 8), (260, 127, 61, 8), (385, 129, 5, 3),
+                                     (449, 31, 65, 5), (300, 203, 66, 4), (515, 350, 97, 7), (260, 35, 127, 6),
+                                     (259, 131, 129, 6), (401, 61, 193, 6), (450, 45, 257, 6),
+                                     (470, 130, 321, 6), (500, 77, 447, 6), (385, 50, 30, 5), (321, 64, 30, 5),
+                                     (320, 40, 99, 5), (333, 66, 128, 5)])
+@pytest.mark.parametrize("shift", [False, True])
+def test_two_pass_unaligned_rows(n, d, r, K, shift):
+    """shift: X and U start 4 bytes past a 16-byte boundary."""
+    import torch
+
+    from paper_2609_36074_amd import nlr
+    X, _, _ = gaussian_mixture(n, d, max(K, 2), 16.0, seed=n * 11 + d)
+    Z = standard_normal_factor(n, r, seed=n + 5 * r).astype(np.float64)
+    Z[0, 0] = 1.0  # a positive entry whatever the draw
+    alpha, T = onlr.default_step_size(K), 5
+
+    def dev(a):
+        flat = torch.empty(a.size + 4, dtype=torch.float32, device="cuda:0")
+        o = 1 if shift else 0
+        v = flat[o:o + a.size].view(*a.shape)
+        v.copy_(torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)))
+        return v
+
+    Xt, Ut = dev(X), dev(Z)
+    ctx = nlr.Context(Xt, K, Ut, alpha=alpha, beta=1.0, eps_d=1.0, eps_c=1e-9, T_min=T, flags=TWO_PASS)
+    other = nlr.Context(dev(X), K, dev(Z), alpha=alpha, beta=1.0, eps_d=1.0, eps_c=1e-9, T_min=T, flags=TWO_PASS)
+    ctx.run(T)
+    gates = [bool(h["dual_step"]) for h in ctx.history()]
+    Xh, _, _ = onlr.centre_and_normalise(X)
+    ref = onlr.run(Xh, Z.astype(np.float32).astype(np.float64), K, alpha, 1.0, T=T, T_min=T, gates=gates)
+    err, yerr = rel_max_err(host(ctx.U), ref.U), rel_max_err(host(ctx.y), ref.ytilde)
+    log(f"unaligned rows n={n} d={d} r={r} K={K} shift={shift}: U {err:.2e} y {yerr:.2e}")
+    assert err < U_TOL / 10 and yerr < U_TOL
+    for _ in range(T):
+        other.step(with_stats=False)
+    assert torch.equal(other.U, ctx.U) and torch.equal(other.y, ctx.y)
+
+
 def test_gmm1m_parity():
     """gmm1m over its configuration's 100 iterations with split products (the bench's
     single-Xhat-pass form) and with fp32 products, from the same start: each iterate against
