@@ -170,6 +170,53 @@ __device__ __forceinline__ float f16_range_scale(float vmax) {
   return ldexpf(1.0f, k);
 }
 
+// Sum of P[off], P[off + step], ... below `limit` (count: at least the number of such terms, uniform),
+// in order, UN loads in flight.  The partial rows of a pass were written by other XCDs, so a load
+// takes about 2 us: all of a thread's terms go in one or two batches, with 32-bit offsets (64-bit
+// products for the addresses alone took as long).
+template <typename T, int UN>
+__device__ __forceinline__ double batch_sum(const T* __restrict__ P, uint32_t off, uint32_t step, uint32_t limit,
+                                            int count) {
+  double acc = 0.0;
+  for (int s0 = 0; s0 < count; s0 += UN) {
+    T v[UN];
+#pragma unroll
+    for (int i = 0; i < UN; ++i) {
+      const uint32_t o = off + (uint32_t)i * step;
+      v[i] = P[o < limit ? o : 0];
+    }
+    __builtin_amdgcn_sched_barrier(0);  // every load is issued before the first value is used
+#pragma unroll
+    for (int i = 0; i < UN; ++i) acc += off + (uint32_t)i * step < limit ? (double)v[i] : 0.0;
+    off += UN * step;
+  }
+  return acc;
+}
+template <typename T>
+__device__ __forceinline__ double wide_sum(const T* __restrict__ P, uint32_t off, uint32_t step, uint32_t limit,
+                                           int count) {
+  return count <= 8 ? batch_sum<T, 8>(P, off, step, limit, count)
+                    : (count <= 16 ? batch_sum<T, 16>(P, off, step, limit, count)
+                                   : batch_sum<T, 32>(P, off, step, limit, count));
+}
+
+// Column sums over all rows of a partials array in one workgroup of kRedThreads: 64 consecutive
+// columns, 16 groups of threads over the rows, the groups added in order.  (rows * stride < 2^32:
+// the partials take at most 64 MiB or 255 rows of 768 x 256.)
+// Result in the threads below 64.  `red`: kRedThreads doubles of LDS.
+constexpr int kRedThreads = 1024;
+__device__ __forceinline__ double part_sum64(const float* __restrict__ P, int64_t rows, int64_t stride, int64_t col,
+                                             double* red) {
+  const uint32_t st = (uint32_t)stride, gq = threadIdx.x >> 6;
+  red[threadIdx.x] = wide_sum<float>(P, gq * st + (uint32_t)col, 16 * st, (uint32_t)rows * st, (int)((rows + 15) / 16));
+  __syncthreads();
+  double t = 0.0;
+  if (threadIdx.x < 64)
+#pragma unroll
+    for (int k = 0; k < 16; ++k) t += red[64 * k + threadIdx.x];
+  return t;
+}
+
 // FP64 matrix core v_mfma_f64_16x16x4f64, D += A B: lane l supplies A[l % 16][l / 16] and
 // B[l / 16][l % 16]; entry v of D is D[4 v + l / 16][l % 16].
 typedef double f64x4 __attribute__((ext_vector_type(4)));

@@ -619,7 +619,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(fused_
 // Row work (the end of the previous iteration): q = u.p - 1 in FP64, the pending
 // gated dual step (ytilde stored), ybar, ||q||^2 and ytilde^T q -- as the row
 // pass does, so that the row pass is not needed.  Its s = U^T ybar is instead
-// formed (by k_reduce_theta after the pass, or by k_onepass_begin at the start of
+// formed (by k_theta_sum after the pass, or by k_onepass_begin at the start of
 // a host call) from terms this kernel accumulates while W is on chip: the
 // column sums of W and of W ytilde (FP64 across tiles) and the Gram W^T W (a
 // third product on the matrix cores, from the W tile; wave w adds the block

@@ -7,7 +7,7 @@
 //                 gated dual step ytilde += (beta/n) q, ybar = ytilde + (beta/n) q,
 //                 s partials = U^T ybar, ||q||^2 and ytilde^T q partials
 //                 (eq. gpu-vectors; Appendix C call sites 2, 3, 7-11);
-//   reduce_theta  fixed-order FP64 sum of the Theta partials, ||Theta||_F^2;
+//   theta_sum     fixed-order FP64 sum of the Theta partials, ||Theta||_F^2;
 //   ctl_a         s, rho, objective fhat (eq. normalized), stopping rule (Section 4.3);
 //   pass B        G = Xhat Theta on fp32 matrix cores with the epilogue of
 //                 eq. (entrywise-fusion): w = max(u + 2 alpha G - alpha ybar p - alpha s, 0),
@@ -694,164 +694,165 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
 }
 
 // ---------------------------------------------------------------------------
-// Segmented column sums, fixed order: out[s][c] = sum over rows of segment s of
-// P[row][c] (rows [s R/S, (s+1) R/S)).  Grid (ceil(C/64), S); thread (col, sub)
-// sums rows sub, sub+4, ... of the segment, then the four subs are added in order.
+// The control kernels sum the partial rows (row statistics, column sums) themselves: a workgroup
+// takes 8 columns, its threads spread over the rows, so that the rows, which other XCDs wrote,
+// come in over several compute units (one workgroup for all columns: 7 to 13 us for 147 to
+// 440 KB; a launch of segment sums in front of a one-workgroup control: 9.5 to 14 us for the two).
+// Column c of the row layout is a statistic below 4 and column c - 4 of the factor above.
 // ---------------------------------------------------------------------------
-// sum over s < S of p[s * stride] in the order s = 0, 1, ...: the loads of eight terms
-// are issued before their additions (a clamped index, so that no load waits behind a
-// branch), which keeps the small reduction kernels from waiting on one load at a time
-template <typename T>
-__device__ __forceinline__ double seq_sum(const T* __restrict__ p, int64_t stride, int64_t S) {
-  double acc = 0.0;
-  for (int64_t s0 = 0; s0 < S; s0 += 8) {
-    double v[8];
+constexpr int kCtlCols = 8;
+static int ctl_blocks(const Geometry& g) { return (4 + g.r32 + kCtlCols - 1) / kCtlCols; }
+
+// Fixed-order sums over the R <= 1024 rows of the partial rows of a_part (HA) and b_part (HB), every
+// load issued before the first is used (one after the other they cost a load latency of about 2 us
+// each): in every thread its column of the workgroup's eight (NT / 8 threads over the rows) and the
+// array's leading statistics (a thread a row), which have the same bits in every workgroup; with th2,
+// the sum of its RT entries.  `red`: kRedDoubles of LDS.  NT = 256 threads where the launch is the
+// control's own: with 1024, the shuffles of sixteen waves on one compute unit's LDS took 3 us.
+constexpr int kRedDoubles = 2 * 128 + 7 * 16 + 23;
+struct CtlSums {
+  double col_a, col_b;  // this thread's column
+  double qq, yq;        // HA: ||q||^2, ytilde^T q
+  double a, b, h, over; // HB
+  double th2;
+};
+// sum over the wave, in every lane of its last 16 and in lanes 0..15 alike (four DPP steps, two shuffles)
+__device__ __forceinline__ double wave_sum_d(double v) {
+  v = row16_sum_d(v);
+  v += shfl_xor_d(v, 16);
+  return v + shfl_xor_d(v, 32);
+}
+template <bool HA, bool HB, int NT, int UN>
+__device__ __forceinline__ CtlSums ctl_sums_un(const double* __restrict__ pa, const double* __restrict__ pb, int rows,
+                                               int C, int blk, const double* __restrict__ th2, int RT, double* red) {
+  constexpr int PH = NT / 8, NW = NT / 64, SR = (PH * UN + NT - 1) / NT;
+  const int tid = threadIdx.x, ph = tid >> 3, w = tid >> 6;
+  int c = kCtlCols * blk + (tid & 7);
+  c = c < C ? c : C - 1;
+  double va[UN], vb[UN], s[7][SR], t2 = 0.0;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = (double)p[(s0 + i < S ? s0 + i : S - 1) * stride];
+  for (int i = 0; i < UN; ++i) {
+    const int row = ph + PH * i;
+    const uint32_t o = (uint32_t)((row < rows ? row : 0) * C + c);
+    if (HA) va[i] = pa[o];
+    if (HB) vb[i] = pb[o];
+  }
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-      if (s0 + i < S) acc += v[i];
+  for (int k = 0; k < SR; ++k) {
+    const int row = tid + NT * k;
+    const uint32_t o = (uint32_t)((row < rows ? row : 0) * C);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) s[i][k] = HA ? pa[o + i] : 0.0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s[2 + i][k] = HB ? pb[o + i] : 0.0;
   }
-  return acc;
-}
-
-template <typename T>
-__device__ __forceinline__ void seg_sum_block(const T* __restrict__ P, int64_t R, int C, double* __restrict__ out,
-                                              int S, int bx, int by, double* red) {
-  const int tid = threadIdx.x;
-  const int col = bx * 64 + (tid & 63);
-  const int sub = tid >> 6;
-  const int64_t lo = (int64_t)by * R / S;
-  const int64_t hi = (int64_t)(by + 1) * R / S;
-  double acc = 0.0;
-  if (col < C && lo + sub < hi) acc = seq_sum<T>(P + (lo + sub) * C + col, 4 * (int64_t)C, (hi - lo - sub + 3) / 4);
-  red[tid] = acc;
+  if (th2)
+    for (int k = tid; k < RT; k += NT) t2 += th2[k];
+  __builtin_amdgcn_sched_barrier(0);
+  auto col = [&](const double (&v)[UN], double* r) {
+    double t = 0.0;
+#pragma unroll
+    for (int i = 0; i < UN; ++i) t += ph + PH * i < rows ? v[i] : 0.0;
+    t += dpp_d<0x128>(t);  // row_ror 8: the row's other half
+    t += shfl_xor_d(t, 16);
+    t += shfl_xor_d(t, 32);
+    if ((tid & 63) < 8) r[8 * w + (tid & 7)] = t;
+  };
+  if (HA) col(va, red);
+  if (HB) col(vb, red + 128);
+#pragma unroll
+  for (int i = 0; i < 7; ++i) {
+    if (!(i < 2 ? HA : (i < 6 ? HB : th2 != nullptr))) continue;
+    double t = i == 6 ? t2 : 0.0;
+    if (i < 6)
+#pragma unroll
+      for (int k = 0; k < SR; ++k) t += tid + NT * k < rows ? s[i][k] : 0.0;
+    t = wave_sum_d(t);
+    if ((tid & 63) == 0) red[256 + 16 * i + w] = t;
+  }
   __syncthreads();
-  if (tid < 64 && col < C)
-    out[(int64_t)by * C + col] = ((red[tid] + red[64 + tid]) + red[128 + tid]) + red[192 + tid];
-}
-
-// mode 0: run unless broken down (after the finish pass); 1: unless halted; 2: unless
-// halted or the one-pass iteration's row pass did not run (rows_first unset)
-template <typename T>
-__global__ __launch_bounds__(kThreads) void k_seg_sum(const T* __restrict__ P, int64_t R, int C,
-                                                      double* __restrict__ out, int S, const DevCtl* ctl,
-                                                      int mode) {
-  if (mode == 0 ? (ctl->breakdown != 0) : halted(ctl)) return;
-  if (mode == 2 && !ctl->rows_first) return;
-  __shared__ double red[kThreads];
-  seg_sum_block<T>(P, R, C, out, S, blockIdx.x, blockIdx.y, red);
-}
-
-// ---------------------------------------------------------------------------
-// Theta = sum of the segment sums (fixed order, FP64), written in the pass-B
-// operand layout, plus per-workgroup ||Theta||_F^2 partials.
-// Layout: chunk ch of 32 features, quarter j (4 features), m-block mb, lane l,
-// element e  <->  Theta[32 ch + 16 (l/32) + 4 j + e][32 mb + l%32].
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ float s_from_gram(const Bufs& B, int r32, int k, double gp, float gamma_f);
-
-// gamma_f >= 0 (one-pass iteration): the extra blocks also form s for the next pass.
-__global__ __launch_bounds__(kThreads) void k_reduce_theta(Geometry g, Bufs B, int nseg, int scaled, float gamma_f) {
-  if (halted(B.ctl)) return;
-  __shared__ double red[kThreads];
-  __shared__ float mred[4];
-  if (blockIdx.x >= g.RT) {
-    // one-pass iteration: the W^T W columns of the partial rows, times P (the column
-    // sums of W, already reduced): (W^T W P)_k, each row's products added in a tree
-    const int r32 = g.r32;
-    const int e = (blockIdx.x - g.RT) * kThreads + threadIdx.x;  // entry k r32 + l
-    const int k = e / r32, l = e - k * r32;
-    const double G = seq_sum<double>(B.seg_theta + (int64_t)g.d32 * r32 + e, g.theta_cols, nseg);
-    red[threadIdx.x] = G * B.gram_vec[l];
-    __syncthreads();
-    for (int w = r32 >> 1; w >= 1; w >>= 1) {
-      if (l < w) red[threadIdx.x] = red[threadIdx.x] + red[threadIdx.x + w];
-      __syncthreads();
-    }
-    if (l == 0) {
-      const double gp = red[threadIdx.x];
-      B.gram_vec[2 * r32 + k] = gp;
-      if (gamma_f >= 0.f) {
-        const float sk = s_from_gram(B, r32, k, gp, gamma_f);
-        B.s[k] = (k < g.r) ? sk : 0.f;
-      }
-    }
-    return;
+  // the waves' sums, added by a thread each
+  if (tid < 16 + 7) {
+    const double* r = tid < 16 ? red + 128 * (tid >> 3) + (tid & 7) : red + 256 + 16 * (tid - 16);
+    const int st = tid < 16 ? 8 : 1;
+    const bool used = tid < 8 ? HA : (tid < 16 ? HB : (tid < 18 ? HA : (tid < 22 ? HB : th2 != nullptr)));
+    double t = 0.0;
+    if (used)
+#pragma unroll 4
+      for (int k = 0; k < NW; ++k) t += r[st * k];
+    red[256 + 7 * 16 + tid] = t;
   }
-  const int64_t tot = (int64_t)g.d32 * g.r32;
-  const int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  double sum = 0.0;
-  if (e < tot) {
-    sum = seq_sum<double>(B.seg_theta + e, g.theta_cols, nseg);
-    const int f = (int)(e / g.r32);
-    // partials of Xhat^T W (fused pass B) carry the scale c of U = c W
-    if (scaled) sum *= (double)B.ctl->c_f;
-    if (f >= g.d) sum = 0.0;  // padded features: zero rows of Theta
-    const int c = (int)(e - (int64_t)f * g.r32);
-    const int ch = f >> 5, fin = f & 31;
-    const int hh = fin >> 4, j = (fin & 15) >> 2, ee = fin & 3;
-    const int mbk = c >> 5, l = hh * 32 + (c & 31);
-    const int64_t idx = ((((int64_t)ch * 4 + j) * g.NB + mbk) * 64 + l) * 4 + ee;
-    B.theta[idx] = (float)sum;
-  }
-  const double t2 = block_sum_d(sum * sum, red);
-  if (threadIdx.x == 0) B.th2_part[blockIdx.x] = t2;
-  // max |Theta| of the block (the panel form scales its split Theta operand by it)
-  float m = fabsf((float)sum);
-  for (int k = 32; k >= 1; k >>= 1) m = fmaxf(m, shfl_xor_f(m, k));
-  if ((threadIdx.x & 63) == 0) mred[threadIdx.x >> 6] = m;
   __syncthreads();
-  if (threadIdx.x == 0) B.thmax_part[blockIdx.x] = fmaxf(fmaxf(mred[0], mred[1]), fmaxf(mred[2], mred[3]));
+  const double* f = red + 256 + 7 * 16;
+  const int cl = tid & 7;
+  return {f[cl], f[8 + cl], f[16], f[17], f[18], f[19], f[20], f[21], f[22]};
+}
+template <bool HA, bool HB, int NT>
+__device__ __forceinline__ CtlSums ctl_sums(const double* __restrict__ pa, const double* __restrict__ pb, int64_t R,
+                                            int C, int blk, const double* __restrict__ th2, int RT, double* red) {
+  if constexpr (NT == 1024)
+    return ctl_sums_un<HA, HB, NT, 8>(pa, pb, (int)R, C, blk, th2, RT, red);
+  else
+    return R <= 256 ? ctl_sums_un<HA, HB, NT, 8>(pa, pb, (int)R, C, blk, th2, RT, red)
+                    : (R <= 512 ? ctl_sums_un<HA, HB, NT, 16>(pa, pb, (int)R, C, blk, th2, RT, red)
+                                : ctl_sums_un<HA, HB, NT, 32>(pa, pb, (int)R, C, blk, th2, RT, red));
+}
+
+// The scale c of U = c W from a = ||W||_F^2 (FP32 of an FP64 ratio), 0 on a breakdown; `over`: W left
+// its split operand's range.
+__device__ __forceinline__ float norm_scale(double a, double over, double K) {
+  const double nu = sqrt(a);
+  if (over > 0.0 || !(nu > 1e-20) || !isfinite(a)) return 0.f;
+  return (float)(sqrt(K) / nu);
 }
 
 // ---------------------------------------------------------------------------
-// Control after pass A (one workgroup): s, rho, objective, stopping rule of the
-// previous iteration.  finish = the call after the finish pass.
+// Control after pass A or a row pass: s (workgroup b its columns), and in workgroup 0 rho, the
+// objective and the stopping rule of the previous iteration.  finish = the call after the finish
+// pass (workgroup 0 alone), which also writes the control block and the record of the latest iteration
+// to the host's mirror.  rows: the partial rows.  A stop, set here, does not keep the other
+// workgroups from their columns: after a stop the partial rows stay as they are, and so does s.
+// defer (two-pass form): ||Theta||_F^2 is formed by the same launch, so the control after pass B
+// adds it to the objective.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kThreads) void k_ctl_a(Geometry g, Bufs B, StepArgs S, int finish) {
+template <int NT>
+__device__ __forceinline__ void ctl_a_work(const Geometry& g, const Bufs& B, const StepArgs& S, int blk, int finish,
+                                           int64_t rows, int defer, double* red) {
   DevCtl* ctl = B.ctl;
   if (ctl->breakdown) return;
-  if (ctl->stop) {
+  if (blk == 0 && ctl->stop) {
     // stopped earlier in this call: the finish pass only materialised U
     if (finish && threadIdx.x == 0) ctl->c_f = 1.0f;
     return;
   }
   // one-pass iteration: after its row pass only (which runs when the stop may fire)
   if (g.fused8 && !finish && !ctl->rows_first) return;
-  __shared__ double red[8];
   const int tid = threadIdx.x;
   const int C = 4 + g.r32;
+  const int64_t t = ctl->t_done;
+  const double Delta = ctl->Delta, delta = ctl->delta;
+  const CtlSums sm =
+      ctl_sums<true, false, NT>(B.a_part, nullptr, rows, C, blk, (blk > 0 || finish || defer) ? nullptr : B.th2_part, g.RT, red);
   // (one-pass iteration with valid Gram terms, rows_first == 1: s is the Gram-derived
   // one already in place, as when the pass does the row work itself)
   if (!finish && !(g.fused8 && ctl->rows_first == 1)) {
-    for (int c = tid; c < g.r32; c += kThreads) {
-      const double t = seq_sum<double>(B.seg_a + 4 + c, C, g.SA);
-      B.s[c] = (c < g.r) ? (float)t : 0.f;
-    }
+    const int c = kCtlCols * blk + tid - 4;
+    if (tid < kCtlCols && c >= 0 && c < g.r32) B.s[c] = (c < g.r) ? (float)sm.col_a : 0.f;
   }
-  // ||q||^2 and ytilde^T q summed by two threads at the same time (past those of s)
-  __shared__ double qy[2];
-  const int tq = g.r32 + 2 <= kThreads ? g.r32 : 0;
-  if (tid == tq || tid == tq + 1) qy[tid - tq] = seq_sum<double>(B.seg_a + (tid - tq), C, g.SA);
-  double th2 = 0.0;
-  if (!finish)
-    for (int k = tid; k < g.RT; k += kThreads) th2 += B.th2_part[k];
-  th2 = block_sum_d(th2, red);  // (its barriers also publish qy)
+  if (blk > 0) return;
   if (tid == 0) {
-    const double qq = qy[0], yq = qy[1];
+    const double qq = sm.qq, yq = sm.yq, th2 = sm.th2;
     const double rho = sqrt(qq * S.inv_n);
     ctl->rho = rho;
-    const int64_t t = ctl->t_done;
+    int stop = 0;
     if (S.end_work && t > 0) {
       nlr_iter_stats* prev = &B.hist[(t - 1) % kHistCap];
-      const int stop = (ctl->Delta < S.eps_d * S.eps_d * S.K) && (ctl->delta < S.eps_c) &&
-                       (rho < S.eps_c) && (t >= S.T_min);
+      stop = (Delta < S.eps_d * S.eps_d * S.K) && (delta < S.eps_c) && (rho < S.eps_c) && (t >= S.T_min);
       prev->rho = rho;
       prev->stop = stop;
       if (stop) ctl->stop = 1;
     }
-    if (!finish && !ctl->stop) {
+    if (!finish && !stop) {
       const double obj = -th2 + yq + 0.5 * S.beta * S.inv_n * qq;
       ctl->objective = obj;
       ctl->theta_fro2 = th2;
@@ -868,6 +869,106 @@ __global__ __launch_bounds__(kThreads) void k_ctl_a(Geometry g, Bufs B, StepArgs
     }
     if (finish) ctl->c_f = 1.0f;
     if (g.fused8 && !finish) ctl->rows_run += 1;
+  }
+}
+
+__global__ __launch_bounds__(kThreads) void k_ctl_a(Geometry g, Bufs B, StepArgs S, int finish, int64_t rows,
+                                                       int defer) {
+  __shared__ double red[kRedDoubles];
+  ctl_a_work<kThreads>(g, B, S, blockIdx.x, finish, rows, defer, red);
+  if (finish && B.mirror) {  // (one workgroup)
+    __syncthreads();
+    const uint32_t* src = reinterpret_cast<const uint32_t*>(B.ctl);
+    uint32_t* dst = reinterpret_cast<uint32_t*>(B.mirror);
+    for (int i = threadIdx.x; i < (int)(sizeof(DevCtl) / 4); i += blockDim.x) dst[i] = src[i];
+    const int64_t t = B.ctl->t_done - (B.ctl->breakdown ? 0 : 1);
+    if (t >= 0) {
+      const uint32_t* rec = reinterpret_cast<const uint32_t*>(B.hist + t % kHistCap);
+      uint32_t* out = reinterpret_cast<uint32_t*>(B.mirror_rec);
+      for (int i = threadIdx.x; i < (int)(sizeof(nlr_iter_stats) / 4); i += blockDim.x) out[i] = rec[i];
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// s = U^T ybar of the one-pass iteration from the Gram terms of the pass that
+// produced U = c W.  Per row q = u.p - 1 = c^2 w.P - 1 and ybar = ytilde_prev +
+// (1 + gate) gamma q (the pending gated dual step, then the penalty term; gamma =
+// beta / n), so
+//   s = c W^T ytilde_prev + (1 + gate) gamma c (c^2 (W^T W) P - P)
+// with W^T W (the columns after Theta in the Theta partial rows, reduced with them
+// and multiplied by P in k_theta_sum), P and W^T ytilde_prev summed in a fixed
+// order (FP64).  The last term is U^T q: small near feasibility and weighted by
+// gamma, so the fp32-accumulated Gram partials carry it well below the iteration's
+// rounding.  k_theta_sum forms s right after the pass with the step arguments of
+// the call; k_onepass_begin forms it again at the start of a host call,
+// whose step arguments (beta) may differ.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ float s_from_gram(const Bufs& B, int r32, int k, double gp, float gamma_f) {
+  const double c = B.ctl->c_gram;
+  const double gmul = (1.0 + (B.ctl->gate ? 1.0 : 0.0)) * (double)gamma_f;
+  const double P = B.gram_vec[k], wy = B.gram_vec[r32 + k];
+  return (float)(c * wy + gmul * c * (c * c * gp - P));
+}
+
+// ---------------------------------------------------------------------------
+// Theta = sum of the partial rows (fixed order, FP64), written in the pass-B
+// operand layout, plus per-workgroup ||Theta||_F^2 and max |Theta| partials; 64 entries a workgroup.
+// Layout: chunk ch of 32 features, quarter j (4 features), m-block mb, lane l,
+// element e  <->  Theta[32 ch + 16 (l/32) + 4 j + e][32 mb + l%32].
+// scaled: partials of Xhat^T W (fused pass B), which carry the scale c of U = c W.
+// One-pass iteration: the workgroups after the RT of Theta take the W^T W columns of the partial
+// rows, times P (the column sums of W): (W^T W P)_k, and with gamma_f >= 0 form s for the next pass.
+// Two-pass form (ctl_rows > 0): the last ctl_blocks workgroups do the control after pass A meanwhile
+// (both only need pass A's partials); Theta is then formed whatever the control decides, since a
+// stop leaves its partials as they were.
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(kRedThreads) void k_theta_sum(Geometry g, Bufs B, StepArgs S, int64_t rows, int scaled,
+                                                           float gamma_f, int64_t ctl_rows) {
+  __shared__ double red[kRedThreads];  // (also the control's: kRedDoubles)
+  if (ctl_rows > 0) {
+    if ((int)blockIdx.x >= g.RT) {
+      ctl_a_work<kRedThreads>(g, B, S, (int)blockIdx.x - g.RT, 0, ctl_rows, 1, red);
+      return;
+    }
+  } else if (halted(B.ctl)) {
+    return;
+  }
+  const int tid = threadIdx.x, r32 = g.r32;
+  const bool gram = (int)blockIdx.x >= g.RT;
+  const int64_t e = ((int64_t)blockIdx.x - (gram ? g.RT : 0)) * 64 + (tid & 63);
+  double sum = part_sum64(B.theta_part, rows, g.theta_cols, e + (gram ? (int64_t)g.d32 * r32 : 0), red);
+  if (tid >= 64) return;
+  if (gram) {
+    const int k = (int)e / r32, l = (int)e - k * r32;  // r32 = 32 or 64 entries of a row: lanes of this wave
+    double gp = sum * B.gram_vec[l];
+    for (int m = r32 >> 1; m >= 1; m >>= 1) gp += shfl_xor_d(gp, m);
+    if (l == 0) {
+      B.gram_vec[2 * r32 + k] = gp;
+      if (gamma_f >= 0.f) {
+        const float sk = s_from_gram(B, r32, k, gp, gamma_f);
+        B.s[k] = (k < g.r) ? sk : 0.f;
+      }
+    }
+    return;
+  }
+  const int f = (int)(e / r32), c = (int)(e - (int64_t)f * r32);
+  if (scaled) sum *= (double)B.ctl->c_f;
+  if (f >= g.d) sum = 0.0;  // padded features: zero rows of Theta
+  const int ch = f >> 5, fin = f & 31;
+  const int hh = fin >> 4, j = (fin & 15) >> 2, ee = fin & 3;
+  const int mbk = c >> 5, l = hh * 32 + (c & 31);
+  const int64_t idx = ((((int64_t)ch * 4 + j) * g.NB + mbk) * 64 + l) * 4 + ee;
+  B.theta[idx] = (float)sum;
+  double t2 = sum * sum;
+  float m = fabsf((float)sum);
+  for (int k = 32; k >= 1; k >>= 1) {
+    t2 += shfl_xor_d(t2, k);
+    m = fmaxf(m, shfl_xor_f(m, k));
+  }
+  if (tid == 0) {
+    B.th2_part[blockIdx.x] = t2;
+    B.thmax_part[blockIdx.x] = m;  // (the panel form scales its split Theta operand by it)
   }
 }
 
@@ -1383,21 +1484,35 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
 // ---------------------------------------------------------------------------
 // Control after pass B (one workgroup): Algorithm 2 steps (d)-(f).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kThreads) void k_ctl_b(Geometry g, Bufs B, StepArgs S) {
+// Workgroup b writes p for its columns (each forms c from the same sums), workgroup 0 the rest.
+// (A breakdown, set by workgroup 0, may keep another from its columns, which are then not used.)
+// defer: as k_ctl_a.
+__global__ __launch_bounds__(kThreads) void k_ctl_b(Geometry g, Bufs B, StepArgs S, int defer) {
   DevCtl* ctl = B.ctl;
   if (halted(ctl)) return;
-  __shared__ double cbuf[1];
-  __shared__ double abh[4];
-  const int tid = threadIdx.x;
+  __shared__ double red[kRedDoubles];
+  const int tid = threadIdx.x, blk = blockIdx.x;
   const int C = 4 + g.r32;
-  // a, b, h and the range flag summed by threads 0..3 at the same time
-  if (tid < 4) abh[tid] = seq_sum<double>(B.seg_b + tid, C, g.SB);
-  __syncthreads();
+  const int64_t t = ctl->t_done;
+  const double obj0 = ctl->objective;
+  const CtlSums sm =
+      ctl_sums<false, true, kThreads>(nullptr, B.b_part, g.GB, C, blk, (defer && blk == 0) ? B.th2_part : nullptr, g.RT, red);
+  const float cs = norm_scale(sm.a, sm.over, S.K);
+  const int pc = kCtlCols * blk + tid - 4;
+  if (cs > 0.f && tid < kCtlCols && pc >= 0 && pc < g.r32)
+    B.p[pc] = (pc < g.r) ? (float)((double)cs * sm.col_b) : 0.f;
+  if (blk > 0) return;
   if (tid == 0) {
-    const double a = abh[0], b = abh[1], h = abh[2], over = abh[3];
+    const double a = sm.a, b = sm.b, h = sm.h, over = sm.over, th2 = sm.th2;
     const double nu = sqrt(a);
-    const int64_t t = ctl->t_done;
     nlr_iter_stats* rec = &B.hist[t % kHistCap];
+    if (defer) {
+      const double obj = obj0 - th2;
+      ctl->objective = obj;
+      ctl->theta_fro2 = th2;
+      rec->objective = obj;
+      rec->theta_fro2 = th2;
+    }
     rec->a = a;
     rec->b = b;
     rec->h = h;
@@ -1405,13 +1520,11 @@ __global__ __launch_bounds__(kThreads) void k_ctl_b(Geometry g, Bufs B, StepArgs
       // a split-fp16 operand of W left fp16's range (the fused pass's flag)
       ctl->breakdown = kRangeError;
       rec->breakdown = kRangeError;
-      cbuf[0] = 0.0;
     } else if (!(nu > 1e-20) || !isfinite(a)) {
       ctl->breakdown = 1;
       rec->breakdown = 1;
-      cbuf[0] = 0.0;
     } else {
-      const float cf = (float)(sqrt(S.K) / nu);
+      const float cf = cs;
       const double c = (double)cf;
       double D = c * c * a + b - 2.0 * c * h;
       if (D < 0.0) D = 0.0;
@@ -1428,15 +1541,6 @@ __global__ __launch_bounds__(kThreads) void k_ctl_b(Geometry g, Bufs B, StepArgs
       rec->c = cf;
       rec->delta = delta;
       rec->dual_step = gate;
-      cbuf[0] = c;
-    }
-  }
-  __syncthreads();
-  const double c = cbuf[0];
-  if (c > 0.0) {
-    for (int col = tid; col < g.r32; col += kThreads) {
-      const double t = seq_sum<double>(B.seg_b + 4 + col, C, g.SB);
-      B.p[col] = (col < g.r) ? (float)(c * t) : 0.f;
     }
   }
 }
@@ -1451,19 +1555,30 @@ __global__ __launch_bounds__(kThreads) void k_ctl_b(Geometry g, Bufs B, StepArgs
 // are recorded here.  Then as k_ctl_b, the column sums P of W and W^T ytilde for
 // the next iteration's s, and whether the next iteration's row pass runs first.
 // ---------------------------------------------------------------------------
+// Workgroup b writes p, P and W^T ytilde for its columns, workgroup 0 the rest, as k_ctl_b.
 __global__ __launch_bounds__(kThreads) void k_ctl_one(Geometry g, Bufs B, StepArgs S) {
   DevCtl* ctl = B.ctl;
   if (halted(ctl)) return;
-  __shared__ double red[8];
-  __shared__ double cbuf[1];
-  const int tid = threadIdx.x;
-  double th2 = 0.0;
-  for (int k = tid; k < g.RT; k += kThreads) th2 += B.th2_part[k];
-  th2 = block_sum_d(th2, red);
+  __shared__ double red[kRedDoubles];
+  const int tid = threadIdx.x, blk = blockIdx.x;
+  const int C = 4 + g.r32;
+  const int64_t t0 = ctl->t_done;
+  const int rows_first = ctl->rows_first;
+  const CtlSums sm =
+      ctl_sums<true, true, kThreads>(B.a_part, B.b_part, g.GB, C, blk, blk == 0 ? B.th2_part : nullptr, g.RT, red);
+  const float cs = norm_scale(sm.a, sm.over, S.K);
+  const int pc = kCtlCols * blk + tid - 4;
+  if (cs > 0.f && tid < kCtlCols && pc >= 0 && pc < g.r32) {
+    const bool ok = pc < g.r;
+    B.p[pc] = ok ? (float)((double)cs * sm.col_b) : 0.f;
+    B.gram_vec[pc] = ok ? sm.col_b : 0.0;
+    B.gram_vec[g.r32 + pc] = ok ? sm.col_a : 0.0;
+  }
+  if (blk > 0) return;
   if (tid == 0) {
-    const int64_t t = ctl->t_done;
-    if (!ctl->rows_first) {
-      const double qq = B.seg_a[0], yq = B.seg_a[1];
+    const int64_t t = t0;
+    if (!rows_first) {
+      const double qq = sm.qq, yq = sm.yq, th2 = sm.th2;
       const double rho = sqrt(qq * S.inv_n);
       ctl->rho = rho;
       if (S.end_work && t > 0) {
@@ -1481,8 +1596,7 @@ __global__ __launch_bounds__(kThreads) void k_ctl_one(Geometry g, Bufs B, StepAr
       cur->rho = 0.0;
       cur->stop = 0;
     }
-    cbuf[0] = 0.0;
-    const double a = B.seg_b[0], b = B.seg_b[1], h = B.seg_b[2];
+    const double a = sm.a, b = sm.b, h = sm.h;
     const double nu = sqrt(a);
     nlr_iter_stats* rec = &B.hist[t % kHistCap];
     rec->a = a;
@@ -1490,7 +1604,7 @@ __global__ __launch_bounds__(kThreads) void k_ctl_one(Geometry g, Bufs B, StepAr
     rec->h = h;
     rec->dual_step = 0;
     rec->breakdown = 0;
-    if (B.seg_b[3] > 0.0) {
+    if (sm.over > 0.0) {
       // the split W operand left fp16's range: stop before Theta and s use it
       ctl->breakdown = kRangeError;
       rec->breakdown = kRangeError;
@@ -1503,7 +1617,7 @@ __global__ __launch_bounds__(kThreads) void k_ctl_one(Geometry g, Bufs B, StepAr
       rec->c = 0.f;
       rec->delta = 0.0;
     } else {
-      const float cf = (float)(sqrt(S.K) / nu);
+      const float cf = cs;
       const double c = (double)cf;
       double D = c * c * a + b - 2.0 * c * h;
       if (D < 0.0) D = 0.0;
@@ -1521,95 +1635,12 @@ __global__ __launch_bounds__(kThreads) void k_ctl_one(Geometry g, Bufs B, StepAr
       rec->c = cf;
       rec->delta = delta;
       rec->dual_step = gate;
-      cbuf[0] = c;
       // the next iteration of this call has this one's end-of-iteration work pending
       StepArgs nx = S;
       nx.end_work = 1;
       ctl->rows_first = stop_possible(ctl, nx) ? 1 : 0;
     }
   }
-  __syncthreads();
-  const double c = cbuf[0];
-  if (c > 0.0) {
-    for (int col = tid; col < g.r32; col += kThreads) {
-      const double P = B.seg_b[4 + col], wy = B.seg_a[4 + col];
-      B.p[col] = (col < g.r) ? (float)(c * P) : 0.f;
-      B.gram_vec[col] = P;
-      B.gram_vec[g.r32 + col] = wy;
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Fixed-order sums over the GB rows of the one-pass iteration's per-workgroup
-// statistics, one segment each: by 0 a_part -> seg_a, 1 b_part -> seg_b.
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ void seg_ab_block(const Geometry& g, const Bufs& B, int bx, int by, double* red) {
-  const double* P = by ? B.b_part : B.a_part;
-  double* out = by ? B.seg_b : B.seg_a;
-  const int C = 4 + g.r32;
-  const int tid = threadIdx.x;
-  // 8 columns x 32 row phases per block; the phases are added in a fixed tree
-  const int col = bx * 8 + (tid & 7);
-  const int sub = tid >> 3;
-  double acc = 0.0;
-  if (col < C && sub < g.GB) acc = seq_sum<double>(P + (int64_t)sub * C + col, 32 * (int64_t)C, (g.GB - sub + 31) / 32);
-  red[tid] = acc;
-  __syncthreads();
-  for (int w = 16; w >= 1; w >>= 1) {
-    if (sub < w) red[tid] = red[tid] + red[tid + 8 * w];
-    __syncthreads();
-  }
-  if (tid < 8 && col < C) out[col] = red[tid];
-}
-
-// The segment sums after the fused pass B of the single-Xhat-pass form in one launch:
-// blockIdx.y < SAF the segments of the Theta partial rows, SAF .. SAF + SB - 1 those of
-// the statistics rows (b_part; the first (4 + r32 + 63) / 64 blocks of those rows).
-__global__ __launch_bounds__(kThreads) void k_seg_fused(Geometry g, Bufs B) {
-  if (halted(B.ctl)) return;
-  __shared__ double red[kThreads];
-  const int by = blockIdx.y;
-  if (by < g.SAF) {
-    seg_sum_block<float>(B.theta_part, g.GB, g.theta_cols, B.seg_theta, g.SAF, blockIdx.x, by, red);
-  } else if ((int)blockIdx.x < (4 + g.r32 + 63) / 64) {
-    seg_sum_block<double>(B.b_part, g.GB, 4 + g.r32, B.seg_b, g.SB, blockIdx.x, by - g.SAF, red);
-  }
-}
-
-// The segment sums after a one-pass kernel in one launch: blockIdx.y < nseg the
-// segments of the Theta and W^T W partial rows, nseg and nseg + 1 the statistics
-// (a_part, b_part; the first (4 + r32 + 7) / 8 blocks of those rows).
-__global__ __launch_bounds__(kThreads) void k_seg_onepass(Geometry g, Bufs B, int nseg) {
-  if (halted(B.ctl)) return;
-  __shared__ double red[kThreads];
-  const int by = blockIdx.y;
-  if (by < nseg) {
-    seg_sum_block<float>(B.theta_part, g.GB, g.theta_cols, B.seg_theta, nseg, blockIdx.x, by, red);
-  } else if ((int)blockIdx.x < (4 + g.r32 + 7) / 8) {
-    seg_ab_block(g, B, blockIdx.x, by - nseg, red);
-  }
-}
-
-// ---------------------------------------------------------------------------
-// s = U^T ybar of the one-pass iteration from the Gram terms of the pass that
-// produced U = c W.  Per row q = u.p - 1 = c^2 w.P - 1 and ybar = ytilde_prev +
-// (1 + gate) gamma q (the pending gated dual step, then the penalty term; gamma =
-// beta / n), so
-//   s = c W^T ytilde_prev + (1 + gate) gamma c (c^2 (W^T W) P - P)
-// with W^T W (the columns after Theta in the Theta partial rows, reduced with them
-// and multiplied by P in k_reduce_theta), P and W^T ytilde_prev summed in a fixed
-// order (FP64).  The last term is U^T q: small near feasibility and weighted by
-// gamma, so the fp32-accumulated Gram partials carry it well below the iteration's
-// rounding.  k_reduce_theta forms s right after the pass with the step arguments of
-// the call; k_s_gram (one workgroup) forms it again at the start of a host call,
-// whose step arguments (beta) may differ.
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ float s_from_gram(const Bufs& B, int r32, int k, double gp, float gamma_f) {
-  const double c = B.ctl->c_gram;
-  const double gmul = (1.0 + (B.ctl->gate ? 1.0 : 0.0)) * (double)gamma_f;
-  const double P = B.gram_vec[k], wy = B.gram_vec[r32 + k];
-  return (float)(c * wy + gmul * c * (c * c * gp - P));
 }
 
 // At the start of a host call (one workgroup): s from the stored Gram terms with the
@@ -1619,9 +1650,10 @@ __device__ __forceinline__ float s_from_gram(const Bufs& B, int r32, int k, doub
 // under this call's arguments (eps, T_min; the row pass settles the rule, s stays
 // the Gram-derived one), else 0.
 __global__ __launch_bounds__(64) void k_onepass_begin(Geometry g, Bufs B, StepArgs S, int gram_valid) {
-  if (halted(B.ctl)) return;
+  if (B.ctl->breakdown) return;
   const int r32 = g.r32;
   const int k = threadIdx.x;
+  if (k == 0) B.ctl->stop = 0;  // the stop of an earlier call
   if (k == 0) B.ctl->rows_first = !gram_valid ? 2 : (stop_possible(B.ctl, S) ? 1 : 0);
   if (!gram_valid || k >= r32) return;
   const float sk = s_from_gram(B, r32, k, B.gram_vec[2 * r32 + k], S.gamma_f);
@@ -1871,57 +1903,25 @@ hipError_t launch_pass_a(const Geometry& g, const Bufs& b, const StepArgs& a, bo
   return e != hipSuccess ? e : launch_theta_wide(g, b, st);
 }
 
-hipError_t launch_seg_theta(const Geometry& g, const Bufs& b, int64_t rows, int nseg, hipStream_t st) {
-  const int C = g.theta_cols;
-  hipLaunchKernelGGL((k_seg_sum<float>), dim3((C + 63) / 64, nseg), dim3(kThreads), 0, st,
-                     (const float*)b.theta_part, rows, C, b.seg_theta, nseg, (const DevCtl*)b.ctl, 1);
+hipError_t launch_theta_sum(const Geometry& g, const Bufs& b, const StepArgs& a, int64_t rows, bool scaled,
+                            float gamma_f, bool with_ctl_a, hipStream_t st) {
+  // one-pass iteration (partials of its pass): workgroups after the RT of Theta form (W^T W) P; two-pass
+  // form: they do the control after pass A
+  const int more = (g.fused8 && scaled) ? (g.r32 * g.r32) / 64 : (with_ctl_a ? ctl_blocks(g) : 0);
+  hipLaunchKernelGGL(k_theta_sum, dim3(g.RT + more), dim3(kRedThreads), 0, st, g, b, a, rows, scaled ? 1 : 0, gamma_f,
+                     with_ctl_a ? (int64_t)(g.a_rows ? g.GA : g.GAF) : (int64_t)0);
   return hipGetLastError();
 }
 
-hipError_t launch_reduce_theta_rows(const Geometry& g, const Bufs& b, int64_t rows, int nseg, bool scaled,
-                                    hipStream_t st) {
-  const int C = g.theta_cols;
-  hipLaunchKernelGGL((k_seg_sum<float>), dim3((C + 63) / 64, nseg), dim3(kThreads), 0, st,
-                     (const float*)b.theta_part, rows, C, b.seg_theta, nseg, (const DevCtl*)b.ctl, 1);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  // one-pass iteration (partials of its pass): blocks after the RT Theta blocks form
-  // (W^T W) P from the r32 r32 Gram entries
-  const int gb = (g.fused8 && scaled) ? (g.r32 * g.r32) / kThreads : 0;
-  hipLaunchKernelGGL(k_reduce_theta, dim3(g.RT + gb), dim3(kThreads), 0, st, g, b, nseg, scaled ? 1 : 0, -1.0f);
+hipError_t launch_ctl_a(const Geometry& g, const Bufs& b, const StepArgs& a, int64_t rows, bool finish,
+                        hipStream_t st) {
+  hipLaunchKernelGGL(k_ctl_a, dim3(finish ? 1 : ctl_blocks(g)), dim3(kThreads), 0, st, g, b, a, finish ? 1 : 0, rows,
+                     0);
   return hipGetLastError();
 }
 
-hipError_t launch_reduce_theta(const Geometry& g, const Bufs& b, bool fused_partials, hipStream_t st) {
-  return fused_partials ? launch_reduce_theta_rows(g, b, g.GB, g.SAF, true, st)
-                        : launch_reduce_theta_rows(g, b, g.GA, g.SA, false, st);
-}
-
-// a_part rows -> g.SA segment sums (the segment count k_ctl_a reads); in the one-pass
-// iteration they follow its row pass, and run when that did
-hipError_t launch_seg_a_rows(const Geometry& g, const Bufs& b, int64_t rows, bool finish, hipStream_t st) {
-  const int C = 4 + g.r32;
-  const int mode = finish ? 0 : (g.fused8 ? 2 : 1);
-  hipLaunchKernelGGL((k_seg_sum<double>), dim3((C + 63) / 64, g.SA), dim3(kThreads), 0, st,
-                     (const double*)b.a_part, rows, C, b.seg_a, g.SA, (const DevCtl*)b.ctl, mode);
-  return hipGetLastError();
-}
-
-hipError_t launch_seg_a(const Geometry& g, const Bufs& b, bool finish, hipStream_t st) {
-  // the register-resident forms run on the pass-A grid, the row launches on GAF
-  return launch_seg_a_rows(g, b, g.a_rows ? g.GA : g.GAF, finish, st);
-}
-
-hipError_t launch_seg_b(const Geometry& g, const Bufs& b, hipStream_t st) {
-  const int C = 4 + g.r32;
-  hipLaunchKernelGGL((k_seg_sum<double>), dim3((C + 63) / 64, g.SB), dim3(kThreads), 0, st,
-                     (const double*)b.b_part, (int64_t)g.GB, C, b.seg_b, g.SB, (const DevCtl*)b.ctl, 1);
-  return hipGetLastError();
-}
-
-
-hipError_t launch_ctl_a(const Geometry& g, const Bufs& b, const StepArgs& a, bool finish, hipStream_t st) {
-  hipLaunchKernelGGL(k_ctl_a, dim3(1), dim3(kThreads), 0, st, g, b, a, finish ? 1 : 0);
+hipError_t launch_ctl_b(const Geometry& g, const Bufs& b, const StepArgs& a, bool defer, hipStream_t st) {
+  hipLaunchKernelGGL(k_ctl_b, dim3(ctl_blocks(g)), dim3(kThreads), 0, st, g, b, a, defer ? 1 : 0);
   return hipGetLastError();
 }
 
@@ -1974,38 +1974,8 @@ hipError_t launch_pass_b(const Geometry& g, const Bufs& b, const StepArgs& a, hi
   }
 }
 
-hipError_t launch_ctl_b(const Geometry& g, const Bufs& b, const StepArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(k_ctl_b, dim3(1), dim3(kThreads), 0, st, g, b, a);
-  return hipGetLastError();
-}
-
 hipError_t launch_ctl_one(const Geometry& g, const Bufs& b, const StepArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(k_ctl_one, dim3(1), dim3(kThreads), 0, st, g, b, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_seg_onepass(const Geometry& g, const Bufs& b, hipStream_t st) {
-  const int cx = (g.theta_cols + 63) / 64, ax = (4 + g.r32 + 7) / 8;
-  hipLaunchKernelGGL(k_seg_onepass, dim3(cx > ax ? cx : ax, g.SAF + 2), dim3(kThreads), 0, st, g, b, g.SAF);
-  return hipGetLastError();
-}
-
-hipError_t launch_seg_fused(const Geometry& g, const Bufs& b, hipStream_t st) {
-  const int cx = (g.theta_cols + 63) / 64, bx = (4 + g.r32 + 63) / 64;
-  hipLaunchKernelGGL(k_seg_fused, dim3(cx > bx ? cx : bx, g.SAF + g.SB), dim3(kThreads), 0, st, g, b);
-  return hipGetLastError();
-}
-
-hipError_t launch_reduce_theta_fused(const Geometry& g, const Bufs& b, hipStream_t st) {
-  // the Theta segments come from k_seg_fused
-  hipLaunchKernelGGL(k_reduce_theta, dim3(g.RT), dim3(kThreads), 0, st, g, b, g.SAF, 1, -1.0f);
-  return hipGetLastError();
-}
-
-hipError_t launch_reduce_theta_onepass(const Geometry& g, const Bufs& b, const StepArgs& a, hipStream_t st) {
-  // blocks after the RT Theta blocks form (W^T W) P from the r32 r32 Gram entries, and s
-  hipLaunchKernelGGL(k_reduce_theta, dim3(g.RT + (g.r32 * g.r32) / kThreads), dim3(kThreads), 0, st, g, b, g.SAF, 1,
-                     a.gamma_f);
+  hipLaunchKernelGGL(k_ctl_one, dim3(ctl_blocks(g)), dim3(kThreads), 0, st, g, b, a);
   return hipGetLastError();
 }
 

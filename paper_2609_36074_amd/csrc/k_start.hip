@@ -34,15 +34,13 @@ __global__ void k_start_zero_xbar(Geometry g, Bufs B) {
   for (int f = threadIdx.x; f < g.d; f += blockDim.x) B.i_xbar[f] = 0.0;
 }
 
-// M[f][c] = sum of the pass-A segment sums (fixed order), FP64.
-__global__ __launch_bounds__(kThreads) void k_start_m(Geometry g, Bufs B) {
-  const int64_t tot = (int64_t)g.d32 * g.r32;
-  const int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (e >= tot) return;
-  double sum = 0.0;
-  for (int s = 0; s < g.SA; ++s) sum += B.seg_theta[(int64_t)s * g.theta_cols + e];
+// M[f][c] = sum of the Theta partials (fixed order), FP64.
+__global__ __launch_bounds__(kRedThreads) void k_start_m(Geometry g, Bufs B) {
+  __shared__ double red[kRedThreads];
+  const int64_t e = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63);  // d32 r32 is a multiple of 1024
+  const double sum = part_sum64(B.theta_part, g.GA, g.theta_cols, e, red);
   const int f = (int)(e / g.r32), c = (int)(e % g.r32);
-  if (f < g.d && c < g.r) B.s_M[(int64_t)f * g.r + c] = sum;
+  if (threadIdx.x < 64 && f < g.d && c < g.r) B.s_M[(int64_t)f * g.r + c] = sum;
 }
 
 // out = A^T Bm (A k x m, Bm k x n, row-major): 64 x 64 blocks, workgroup (column, row block).  Operands
@@ -311,9 +309,7 @@ hipError_t launch_data_start(const Geometry& g, const Bufs& b, const StepArgs& a
   if ((e = hipGetLastError()) != hipSuccess) return e;
   // M = Xhat^T Z: the pass-A product with U = Z (c_f = 1)
   if ((e = launch_pass_a(g, b, a0, false, st)) != hipSuccess) return e;
-  const int C = g.d32 * g.r32;
-  if ((e = launch_seg_theta(g, b, g.GA, g.SA, st)) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_start_m, dim3((C + kThreads - 1) / kThreads), dim3(kThreads), 0, st, g, b);
+  hipLaunchKernelGGL(k_start_m, dim3(g.RT), dim3(kRedThreads), 0, st, g, b);
   // C M (C is symmetric) and M^T (C M)
   const int rb = (g.r + 63) / 64, db = (g.d + 63) / 64;
   hipLaunchKernelGGL(k_start_gemm, dim3(rb, db), dim3(kThreads), 0, st, (const double*)b.s_C, (const double*)b.s_M,

@@ -81,11 +81,9 @@ Geometry make_geometry(int64_t n, int32_t d, int32_t r, int32_t K, bool aligned1
       g.GA = (int32_t)ga;
     }
   }
-  g.SA = (g.GA + 31) / 32;
-  if (g.SA > 64) g.SA = 64;
-  g.RT = (int32_t)(((int64_t)g.d32 * g.r32 + kThreads - 1) / kThreads);
+  g.RT = (int32_t)((int64_t)g.d32 * g.r32 / 64);
   g.tilesB = (n + kTPB - 1) / kTPB;
-  g.GB = (int32_t)(g.tilesB < 1536 ? g.tilesB : 1536);
+  g.GB = (int32_t)(g.tilesB < 1024 ? g.tilesB : 1024);  // (a control kernel takes a thread a partial row)
   g.nch = g.d32 / 32;
   // Theta resident in pass B's LDS when it fits beside p, s and the reductions in 64 KiB
   g.theta_lds = ((int64_t)g.d32 * g.r32 * 4 + 2 * g.r32 * 4 + (4 * g.r32 + 8) * 8 <= (64 << 10)) ? 1 : 0;
@@ -95,8 +93,6 @@ Geometry make_geometry(int64_t n, int32_t d, int32_t r, int32_t K, bool aligned1
   if (!g.b_res && g.GB > 512) g.GB = 512;
   g.ldsB_bytes = (int32_t)((g.theta_lds ? (int64_t)g.d32 * g.r32 * 4 : 0) + 2 * g.r32 * 4 +
                            (4 * g.r32 + 8) * 8);
-  g.SB = (g.GB + 31) / 32;
-  if (g.SB > 64) g.SB = 64;
   // init reductions
   {
     int64_t gi = (n + 255) / 256;
@@ -131,15 +127,12 @@ Geometry make_geometry(int64_t n, int32_t d, int32_t r, int32_t K, bool aligned1
   g.fused8 = (g.fused && split && fused8_shape(g.NB, g.nch, r)) ? 1 : 0;
   // the one-pass iteration's W^T W partials follow its Theta partials in one row
   g.theta_cols = g.d32 * g.r32 + (g.fused8 ? g.r32 * g.r32 : 0);
-  g.SAF = g.SA;
   if (g.fused) {
     // persistent grid: one workgroup per CU; two for the shapes whose kernel holds two
     // workgroups' waves (the four-wave form with one column block and <= 64 features; the
     // one-pass form with one column block and <= 32 features: 73 KiB of LDS, 128 VGPRs)
     const int64_t gmax = (g.NB == 1 && (g.fused8 ? g.nch == 1 : g.nch <= 2)) ? 512 : 256;
     g.GB = (int32_t)(g.tilesB < gmax ? g.tilesB : gmax);
-    g.SB = (g.GB + 31) / 32;
-    g.SAF = (g.GB + 31) / 32;
     g.split_a = g.split_b = split ? 1 : 0;  // both products live in the fused pass B
   } else {
     // two-pass form: split products in the resident pass B only
@@ -157,9 +150,6 @@ Geometry make_geometry(int64_t n, int32_t d, int32_t r, int32_t K, bool aligned1
     g.a_cv = r <= 16 ? 1 : (r <= 32 ? 2 : 4);
     int64_t ga = (((n + 3) / 4) + 4 * 32 - 1) / (4 * 32);
     g.GA = (int32_t)(ga > 1024 ? 1024 : (ga < 1 ? 1 : ga));
-    g.SA = (g.GA + 31) / 32;
-    if (g.SA > 64) g.SA = 64;
-    g.SAF = g.SA;
   }
   // row work and finish of the other shapes: no Theta partials, so a grid for the rows alone
   g.GAF = g.a_rows ? g.GA : (int32_t)(g.tilesA < 1024 ? g.tilesA : 1024);
@@ -184,7 +174,6 @@ Geometry make_geometry(int64_t n, int32_t d, int32_t r, int32_t K, bool aligned1
     const int64_t pgrid = g.pnbw == 4 ? 256 : 512;
     g.tilesP = (n + prow - 1) / prow;
     g.GB = (int32_t)(g.tilesP < pgrid ? g.tilesP : pgrid);
-    g.SB = (g.GB + 31) / 32;
     // |u| <= sqrt(K) for U in Omega (||U||_F^2 = K); 1% margin for rounding
     int e2;
     (void)std::frexp(1.01 * std::sqrt((double)K), &e2);
@@ -295,10 +284,6 @@ size_t carve_workspace(const Geometry& g, char* base, Bufs* out) {
   if (g.panel && (int64_t)g.PS * g.pfb > arows) arows = (int64_t)g.PS * g.pfb;  // one row per pass-A workgroup
   if (g.fused8 && (int64_t)g.GB > arows) arows = g.GB;  // the one-pass iteration's row statistics
   b.a_part = reinterpret_cast<double*>(take((size_t)arows * (4 + r32) * 8));
-  const size_t segs = (size_t)(g.SA > g.SAF ? g.SA : g.SAF);
-  b.seg_theta = reinterpret_cast<double*>(take(segs * (size_t)g.theta_cols * 8));
-  b.seg_a = reinterpret_cast<double*>(take((size_t)g.SA * (4 + r32) * 8));
-  b.seg_b = reinterpret_cast<double*>(take((size_t)g.SB * (4 + r32) * 8));
   b.i_xbar = reinterpret_cast<double*>(take(d * 8));
   b.dump = reinterpret_cast<float*>(take(256));
   b.thmax_part = reinterpret_cast<float*>(take((size_t)g.RT * 4));
@@ -383,9 +368,10 @@ struct nlr_ctx {
   bool failed;        // sticky failure
   bool breakdown;
   bool range_error;   // the breakdown is a split-fp16 range error (NLR_ERANGE)
-  int64_t t_host;     // last known iteration counter
+  int64_t t_host;     // last known iteration counter (t_host_valid), else a bound above it
   bool t_host_valid;
-  DevCtl* host_ctl;   // pinned mirror of the control block
+  DevCtl* host_ctl;   // mirror of the control block, pinned except for the allocation-free entry point
+  nlr_iter_stats* host_rec;  // the latest record beside it (pinned mirror only)
   // profiling
   bool prof;
   int prof_level;     // 1: every launch; 2: the row and pass kernels only
@@ -500,10 +486,10 @@ static hipError_t prof_collect(nlr_ctx* c) {
   } while (0)
 
 // first: the first iteration of a host call (nlr_step, nlr_run), whose step
-// arguments may differ from those of the pass before it.  lean (one-pass form, not the
-// first iteration): the caller knows that the previous iteration's stopping rule
-// cannot fire (t < T_min), so the row pass, its segment sums and k_ctl_a would
-// return at entry; they are not launched.
+// arguments may differ from those of the pass before it; it also clears the stop of
+// an earlier call.  lean (one-pass form): the caller knows that the previous iteration's
+// stopping rule cannot fire (t < T_min), so the row pass and k_ctl_a would return at
+// entry once there are Gram terms; they are not launched.
 static nlr_status enqueue_iteration(nlr_ctx* c, bool first, bool lean = false) {
   const StepArgs a = make_step_args(c, c->pending ? 1 : 0);
   if (c->g.fused8) {
@@ -512,34 +498,31 @@ static nlr_status enqueue_iteration(nlr_ctx* c, bool first, bool lean = false) {
     // primal step; s comes from the Gram terms of the previous pass (formed after that
     // pass with this call's step arguments, or anew at the start of a call).  When the
     // previous iteration's stopping rule may fire (decided on the device before the
-    // pass), or there is no previous pass (after init or a stop), the row pass, its
-    // segment sums and k_ctl_a run first (they return at entry otherwise) and settle
-    // the rule and s.  Then one launch of segment sums (Theta and W^T W partials, the
-    // row statistics), the control, and Theta with (W^T W) P and the next s.
+    // pass), or there is no previous pass (after init or a stop), the row pass and
+    // k_ctl_a run first (they return at entry otherwise) and settle the rule and s.
+    // Then the control (which sums the pass's row statistics), and Theta with (W^T W) P
+    // and the next s.
     if (first) LAUNCH(KK_CTL_A, launch_onepass_begin(c->g, c->b, a, c->gram_valid, c->stream));
-    if (first || !lean) {
+    if (!lean || !c->gram_valid) {
       LAUNCH(KK_PASS_U, launch_pass_u(c->g, c->b, a, c->stream));
-      LAUNCH(KK_CTL_A, launch_seg_a(c->g, c->b, false, c->stream));
-      LAUNCH(KK_CTL_A, launch_ctl_a(c->g, c->b, a, false, c->stream));
+      LAUNCH(KK_CTL_A, launch_ctl_a(c->g, c->b, a, c->g.GA, false, c->stream));
     }
     LAUNCH(KK_PASS_BF, launch_pass_bf(c->g, c->b, a, c->stream));
-    LAUNCH(KK_CTL_B, launch_seg_onepass(c->g, c->b, c->stream));
     LAUNCH(KK_CTL_B, launch_ctl_one(c->g, c->b, a, c->stream));
-    LAUNCH(KK_REDUCE_THETA, launch_reduce_theta_onepass(c->g, c->b, a, c->stream));
+    LAUNCH(KK_REDUCE_THETA, launch_theta_sum(c->g, c->b, a, c->g.GB, true, a.gamma_f, false, c->stream));
     c->gram_valid = true;
     c->pending = true;
     return NLR_OK;
   }
+  if (first) LAUNCH(KK_CTL_A, launch_clear_stop(c->b, c->stream));
   if (c->g.fused) {
     // row pass (end of the previous iteration, s, rho, objective terms), control,
     // fused pass B (W and the partials of Xhat^T W), control, Theta of the new factor
     LAUNCH(KK_PASS_U, launch_pass_u(c->g, c->b, a, c->stream));
-    LAUNCH(KK_CTL_A, launch_seg_a(c->g, c->b, false, c->stream));
-    LAUNCH(KK_CTL_A, launch_ctl_a(c->g, c->b, a, false, c->stream));
+    LAUNCH(KK_CTL_A, launch_ctl_a(c->g, c->b, a, c->g.GA, false, c->stream));
     LAUNCH(KK_PASS_BF, launch_pass_bf(c->g, c->b, a, c->stream));
-    LAUNCH(KK_CTL_B, launch_seg_fused(c->g, c->b, c->stream));  // statistics and Theta segments
-    LAUNCH(KK_CTL_B, launch_ctl_b(c->g, c->b, a, c->stream));
-    LAUNCH(KK_REDUCE_THETA, launch_reduce_theta_fused(c->g, c->b, c->stream));
+    LAUNCH(KK_CTL_B, launch_ctl_b(c->g, c->b, a, false, c->stream));
+    LAUNCH(KK_REDUCE_THETA, launch_theta_sum(c->g, c->b, a, c->g.GB, true, -1.0f, false, c->stream));
     c->pending = true;
     return NLR_OK;
   }
@@ -547,23 +530,18 @@ static nlr_status enqueue_iteration(nlr_ctx* c, bool first, bool lean = false) {
     // split-fp16 panel products (large d x r): pass A (with the row work, ybar
     // stored), Theta and its split operand, control, pass B, control
     LAUNCH(KK_PASS_A, launch_pass_a_panel(c->g, c->b, a, c->stream));
-    LAUNCH(KK_REDUCE_THETA, launch_reduce_theta_rows(c->g, c->b, c->g.PS, c->g.SA, false, c->stream));
+    LAUNCH(KK_REDUCE_THETA, launch_theta_sum(c->g, c->b, a, c->g.PS, false, -1.0f, false, c->stream));
     LAUNCH(KK_REDUCE_THETA, launch_theta_split_panel(c->g, c->b, c->stream));
-    LAUNCH(KK_CTL_A, launch_seg_a_rows(c->g, c->b, (int64_t)c->g.PS * c->g.pfb, false, c->stream));
-    LAUNCH(KK_CTL_A, launch_ctl_a(c->g, c->b, a, false, c->stream));
+    LAUNCH(KK_CTL_A, launch_ctl_a(c->g, c->b, a, (int64_t)c->g.PS * c->g.pfb, false, c->stream));
     LAUNCH(KK_PASS_B, launch_pass_b_panel(c->g, c->b, a, c->stream));
-    LAUNCH(KK_CTL_B, launch_seg_b(c->g, c->b, c->stream));
-    LAUNCH(KK_CTL_B, launch_ctl_b(c->g, c->b, a, c->stream));
+    LAUNCH(KK_CTL_B, launch_ctl_b(c->g, c->b, a, false, c->stream));
     c->pending = true;
     return NLR_OK;
   }
   LAUNCH(KK_PASS_A, launch_pass_a(c->g, c->b, a, false, c->stream));
-  LAUNCH(KK_REDUCE_THETA, launch_reduce_theta(c->g, c->b, false, c->stream));
-  LAUNCH(KK_CTL_A, launch_seg_a(c->g, c->b, false, c->stream));
-  LAUNCH(KK_CTL_A, launch_ctl_a(c->g, c->b, a, false, c->stream));
+  LAUNCH(KK_REDUCE_THETA, launch_theta_sum(c->g, c->b, a, c->g.GA, false, -1.0f, true, c->stream));
   LAUNCH(KK_PASS_B, launch_pass_b(c->g, c->b, a, c->stream));
-  LAUNCH(KK_CTL_B, launch_seg_b(c->g, c->b, c->stream));
-  LAUNCH(KK_CTL_B, launch_ctl_b(c->g, c->b, a, c->stream));
+  LAUNCH(KK_CTL_B, launch_ctl_b(c->g, c->b, a, true, c->stream));
   c->pending = true;
   return NLR_OK;
 }
@@ -633,8 +611,7 @@ static nlr_status enqueue_steady(nlr_ctx* c, int nb, bool lean) {
 static nlr_status enqueue_finish(nlr_ctx* c) {
   const StepArgs a = make_step_args(c, c->pending ? 1 : 0);
   LAUNCH(KK_FINISH, launch_pass_a(c->g, c->b, a, true, c->stream));
-  LAUNCH(KK_CTL_FINISH, launch_seg_a(c->g, c->b, true, c->stream));
-  LAUNCH(KK_CTL_FINISH, launch_ctl_a(c->g, c->b, a, true, c->stream));
+  LAUNCH(KK_CTL_FINISH, launch_ctl_a(c->g, c->b, a, c->g.a_rows ? c->g.GA : c->g.GAF, true, c->stream));
   c->pending = false;
   return NLR_OK;
 }
@@ -648,7 +625,23 @@ static nlr_status read_ctl(nlr_ctx* c) {
   return NLR_OK;
 }
 
+// The control block after a finish pass: its control kernel has copied it, with the latest
+// iteration's record, to the context's pinned mirror, if there is one (two copies by
+// hipMemcpyAsync, each waited for, took 20 us of a 77 us step).
+static nlr_status read_finish(nlr_ctx* c) {
+  if (!c->b.mirror) return read_ctl(c);
+  if (hipStreamSynchronize(c->stream) != hipSuccess) return hip_fail(c);
+  c->t_host = c->host_ctl->t_done;
+  c->t_host_valid = true;
+  return NLR_OK;
+}
+
+// The record of iteration t, the latest one, after read_finish.
 static nlr_status read_record(nlr_ctx* c, int64_t t, nlr_iter_stats* out) {
+  if (c->b.mirror) {
+    std::memcpy(out, c->host_rec, sizeof(*out));
+    return NLR_OK;
+  }
   if (hipMemcpyAsync(out, c->b.hist + (t % kHistCap), sizeof(nlr_iter_stats), hipMemcpyDeviceToHost,
                      c->stream) != hipSuccess)
     return hip_fail(c);
@@ -717,6 +710,12 @@ static nlr_status init_ctx(nlr_ctx* c, const Geometry& g0, float* X, int32_t K, 
   c->b.X = X;
   c->b.U = U;
   c->b.y = y;
+  if (c->host_rec) {  // pinned: the device writes it at its device address
+    void* dp = nullptr;
+    if (hipHostGetDevicePointer(&dp, c->host_ctl, 0) != hipSuccess || !dp) return NLR_EHIP;
+    c->b.mirror = reinterpret_cast<DevCtl*>(dp);
+    c->b.mirror_rec = reinterpret_cast<nlr_iter_stats*>(c->b.mirror + 1);
+  }
   c->stream = reinterpret_cast<hipStream_t>(stream);
   c->prm = *params;
   c->pending = false;
@@ -762,7 +761,7 @@ static nlr_status init_ctx(nlr_ctx* c, const Geometry& g0, float* X, int32_t K, 
     // Theta_0 = Xhat^T U_0: one pass A (its row partials are recomputed by the first row pass)
     const StepArgs a0 = make_step_args(c, 0);
     if (launch_pass_a(g, b, a0, false, st) != hipSuccess) return NLR_EHIP;
-    if (launch_reduce_theta(g, b, false, st) != hipSuccess) return NLR_EHIP;
+    if (launch_theta_sum(g, b, a0, g.GA, false, -1.0f, false, st) != hipSuccess) return NLR_EHIP;
     // split products: the fused pass B is then the only reader of X; store Xhat split once
     if (g.split_b)
       if (launch_split_x(g, b, st) != hipSuccess) return NLR_EHIP;
@@ -781,7 +780,7 @@ static nlr_status run_iterations(nlr_ctx* c, int32_t T, int32_t* iters_done, nlr
   if (!c->t_host_valid)
     if (read_ctl(c) != NLR_OK) return NLR_EHIP;
   const int64_t t0 = c->t_host;
-  if (launch_clear_stop(c->b, c->stream) != hipSuccess) return hip_fail(c);
+  if (T == 0 && launch_clear_stop(c->b, c->stream) != hipSuccess) return hip_fail(c);
   // no iteration of this call can stop while t < T_min: its row pass would not run
   // (one-pass form), so it is not launched
   const bool lean = t0 + T - 1 < (int64_t)c->prm.T_min;
@@ -792,7 +791,7 @@ static nlr_status run_iterations(nlr_ctx* c, int32_t T, int32_t* iters_done, nlr
       if (c->host_ctl->stop || c->host_ctl->breakdown) break;
     }
     if (k == 0) {
-      nlr_status s = enqueue_iteration(c, true);
+      nlr_status s = enqueue_iteration(c, true, t0 < (int64_t)c->prm.T_min);
       if (s != NLR_OK) return s;
       ++k;
       continue;
@@ -805,7 +804,7 @@ static nlr_status run_iterations(nlr_ctx* c, int32_t T, int32_t* iters_done, nlr
   }
   nlr_status s = enqueue_finish(c);
   if (s != NLR_OK) return s;
-  if (read_ctl(c) != NLR_OK) return NLR_EHIP;
+  if (read_finish(c) != NLR_OK) return NLR_EHIP;
   if (prof_collect(c) != hipSuccess) return hip_fail(c);
   const int64_t t1 = c->host_ctl->t_done;
   if (iters_done) *iters_done = (int32_t)(t1 - t0);
@@ -869,10 +868,14 @@ nlr_status nlr_init(nlr_ctx** ctx, float* X, int64_t n, int32_t d, int32_t K, in
   nlr_ctx* c = new (std::nothrow) nlr_ctx();
   if (!c) return NLR_EHIP;
   c->graphs_allowed = true;
-  if (hipHostMalloc(reinterpret_cast<void**>(&c->host_ctl), sizeof(DevCtl), hipHostMallocDefault) != hipSuccess) {
+  static_assert(sizeof(DevCtl) % 16 == 0, "the record follows the control block");
+  if (hipHostMalloc(reinterpret_cast<void**>(&c->host_ctl), sizeof(DevCtl) + sizeof(nlr_iter_stats),
+                    hipHostMallocDefault) != hipSuccess) {
     delete c;
     return NLR_EHIP;
   }
+  std::memset(static_cast<void*>(c->host_ctl), 0, sizeof(DevCtl) + sizeof(nlr_iter_stats));
+  c->host_rec = reinterpret_cast<nlr_iter_stats*>(c->host_ctl + 1);
   const nlr_status s = init_ctx(c, g0, X, K, U, y, params, flags, workspace, stream);
   if (s != NLR_OK) {
     nlr_destroy(c);
@@ -900,6 +903,7 @@ nlr_status nlr_solve_static(float* X, int64_t n, int32_t d, int32_t K, int32_t r
   DevCtl mirror;
   std::memset(&mirror, 0, sizeof(mirror));
   c.host_ctl = &mirror;
+  c.host_rec = nullptr;
   nlr_status s = init_ctx(&c, g0, X, K, U, y, params, flags, ws, stream);
   if (s != NLR_OK) return s;
   return run_iterations(&c, T, iters_done, last);
@@ -916,14 +920,15 @@ nlr_status nlr_set_params(nlr_ctx* c, const nlr_params* params) {
 nlr_status nlr_step(nlr_ctx* c, nlr_iter_stats* stats) {
   if (!c) return NLR_EINVAL;
   if (c->failed) return NLR_ESTATE;
-  if (launch_clear_stop(c->b, c->stream) != hipSuccess) return hip_fail(c);
-  nlr_status s = enqueue_iteration(c, true);
+  // the iteration counter is known, or bounded by the steps enqueued since it was
+  nlr_status s = enqueue_iteration(c, true, c->t_host < (int64_t)c->prm.T_min);
   if (s != NLR_OK) return s;
   s = enqueue_finish(c);
   if (s != NLR_OK) return s;
   c->t_host_valid = false;
+  ++c->t_host;
   if (stats) {
-    if (read_ctl(c) != NLR_OK) return NLR_EHIP;
+    if (read_finish(c) != NLR_OK) return NLR_EHIP;
     if (c->host_ctl->breakdown) {
       c->failed = true;
       c->breakdown = true;

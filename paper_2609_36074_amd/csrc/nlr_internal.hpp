@@ -80,9 +80,7 @@ struct Geometry {
   int32_t a_rows;       // 1: register-resident pass A (k_pass_a_rows)
   int32_t a_un;         // 1: with rows of X or U that are not whole 16-byte pieces
   int32_t a_fv, a_ngf, a_cv;  // its features per lane, feature groups, columns per lane
-  // reduce theta
-  int32_t RT;
-  int32_t SA, SB;       // segments of the two-level partial sums
+  int32_t RT;           // workgroups of the Theta sum (64 entries each)
   // pass B
   int32_t GB;
   int64_t tilesB;       // ceil(n / kTPB)
@@ -94,7 +92,6 @@ struct Geometry {
   int32_t uflat;        // 1: the fused pass B moves U as whole 32-row slabs (r % 4 != 0)
   int32_t fused8;       // 1: the fused pass B in its eight-wave form (k_pass_bf8), one-pass iteration
   int32_t theta_cols;   // floats per row of the Theta partials: d32 r32 (+ r32 r32 of W^T W, one-pass)
-  int32_t SAF;          // segments of the fused pass B Theta partials (GB rows)
   int32_t ldsB_bytes;
   // init
   int32_t GI;           // row-chunk workgroups of the init reductions
@@ -123,11 +120,10 @@ struct Bufs {
   float* s;            // r32
   float* theta_part;   // rows of theta_cols floats (GA, GB or PS rows)
   double* a_part;      // GA x (4 + r32): ||q||^2, ytilde^T q, -, -, s partials
-  double* seg_theta;   // SA x d32*r32: segment sums of theta_part
-  double* seg_a;       // SA x (4 + r32)
-  double* seg_b;       // SB x (4 + r32)
   double* th2_part;    // RT
   double* b_part;      // GB x (4 + r32): a, b, h, -, column sums
+  DevCtl* mirror;      // host memory that the control after a finish pass copies ctl to (or null)
+  nlr_iter_stats* mirror_rec;  // and the latest iteration's record
   float* dump;         // 256 bytes that masked-off lanes store to (never read)
   float* thmax_part;   // RT: per-workgroup max |Theta| of the reduction
   float* ybar;         // n: ybar of the current iteration (panel form: pass A -> pass B)
@@ -213,19 +209,20 @@ hipError_t launch_zero_y(const Geometry& g, const Bufs& b, hipStream_t st);
 hipError_t launch_pass_a(const Geometry& g, const Bufs& b, const StepArgs& a, bool finish,
                          hipStream_t st);
 hipError_t launch_pass_u(const Geometry& g, const Bufs& b, const StepArgs& a, hipStream_t st);
-// fused_partials: the partials are Xhat^T W from the fused pass B (GB rows, scaled by c_f)
-hipError_t launch_reduce_theta(const Geometry& g, const Bufs& b, bool fused_partials, hipStream_t st);
 hipError_t launch_pass_bf(const Geometry& g, const Bufs& b, const StepArgs& a, hipStream_t st);
-hipError_t launch_seg_a(const Geometry& g, const Bufs& b, bool finish, hipStream_t st);
-hipError_t launch_seg_b(const Geometry& g, const Bufs& b, hipStream_t st);
-hipError_t launch_ctl_a(const Geometry& g, const Bufs& b, const StepArgs& a, bool finish,
-                        hipStream_t st);
 hipError_t launch_pass_b(const Geometry& g, const Bufs& b, const StepArgs& a, hipStream_t st);
-hipError_t launch_ctl_b(const Geometry& g, const Bufs& b, const StepArgs& a, hipStream_t st);
+// Theta from `rows` partial rows (scaled: Xhat^T W of the fused pass B, times c_f; gamma_f >= 0: the
+// one-pass iteration's next s too), and with the control after pass A in the two-pass form
+hipError_t launch_theta_sum(const Geometry& g, const Bufs& b, const StepArgs& a, int64_t rows, bool scaled,
+                            float gamma_f, bool with_ctl_a, hipStream_t st);
+// rows: a_part rows of the latest producer (pass A grid, finish grid or panel splits)
+hipError_t launch_ctl_a(const Geometry& g, const Bufs& b, const StepArgs& a, int64_t rows, bool finish,
+                        hipStream_t st);
+// defer: ||Theta||_F^2 (formed with the control after pass A, in one launch) joins the objective here
+hipError_t launch_ctl_b(const Geometry& g, const Bufs& b, const StepArgs& a, bool defer, hipStream_t st);
 hipError_t launch_xscale(const Geometry& g, const Bufs& b, hipStream_t st);
 hipError_t launch_split_x(const Geometry& g, const Bufs& b, hipStream_t st);
 hipError_t launch_pass_b_split(const Geometry& g, const Bufs& b, const StepArgs& a, hipStream_t st);
-hipError_t launch_seg_theta(const Geometry& g, const Bufs& b, int64_t rows, int nseg, hipStream_t st);
 hipError_t launch_data_start(const Geometry& g, const Bufs& b, const StepArgs& a0, bool x_normalised,
                              hipStream_t st);
 // U^T U, `count` Jacobi sweeps from sweep `first` on (all of them up to 64 columns), the basis
@@ -240,19 +237,11 @@ hipError_t launch_pass_a_panel(const Geometry& g, const Bufs& b, const StepArgs&
 hipError_t launch_theta_split_panel(const Geometry& g, const Bufs& b, hipStream_t st);
 hipError_t launch_pass_b_panel(const Geometry& g, const Bufs& b, const StepArgs& a, hipStream_t st);
 hipError_t launch_split_x8(const Geometry& g, const Bufs& b, hipStream_t st);
-// a_part rows written by the latest producer (pass A grid, finish grid or panel splits)
-hipError_t launch_seg_a_rows(const Geometry& g, const Bufs& b, int64_t rows, bool finish, hipStream_t st);
 hipError_t launch_ctl_one(const Geometry& g, const Bufs& b, const StepArgs& a, hipStream_t st);
-hipError_t launch_seg_onepass(const Geometry& g, const Bufs& b, hipStream_t st);
-hipError_t launch_seg_fused(const Geometry& g, const Bufs& b, hipStream_t st);
-hipError_t launch_reduce_theta_fused(const Geometry& g, const Bufs& b, hipStream_t st);
-hipError_t launch_reduce_theta_onepass(const Geometry& g, const Bufs& b, const StepArgs& a, hipStream_t st);
 // start of a host call of the one-pass iteration: s from the stored Gram terms (when
 // valid) and whether the first iteration's row pass runs before its pass
 hipError_t launch_onepass_begin(const Geometry& g, const Bufs& b, const StepArgs& a, bool gram_valid,
                                 hipStream_t st);
-hipError_t launch_reduce_theta_rows(const Geometry& g, const Bufs& b, int64_t rows, int nseg, bool scaled,
-                                    hipStream_t st);
 
 // ---- device helpers ----
 typedef float f32x4 __attribute__((ext_vector_type(4)));
