@@ -9,12 +9,13 @@
 //   distances, and so the labels, unchanged);
 //   Lloyd's iteration on the rows of E from the embedded seed rows.  E is never formed:
 //   with M = P cent^T (r x K) the squared distance of row i to centroid k is
-//   |e_i|^2 + |cent_k|^2 - 2 u_i M_k, so a pass is one product U M on the fp64 matrix
-//   cores with the argmin over k in registers; rows whose two smallest values lie closer
-//   than the rounding of that form can resolve are decided by the distances themselves
-//   (FP64, lowest index on ties).  The cluster sums S_k = sum of u_i over the rows of k
-//   are taken in 64-bit integers (below), and cent_k = (S_k P) / count (a centroid
-//   without rows stays in place).
+//   |e_i|^2 + |cent_k|^2 - 2 u_i M_k, so a pass is one product U M with the argmin over k in
+//   registers.  It runs on the fp16 matrix cores with two-term operand splits, under a bound on
+//   its rounding: a row whose two smallest values lie within it is decided by the same form in
+//   FP64 over its candidates, and one whose values are too close for that by the distances
+//   themselves (FP64, lowest index on ties), so that the labels are those of FP64 distances.  The
+//   cluster sums S_k = sum of u_i over the rows of k are taken in 64-bit integers (below), and
+//   cent_k = (S_k P) / count (a centroid without rows stays in place).
 // The device notes the first pass that changes no label; passes enqueued after it return
 // at entry.
 #include "k_common.hpp"
@@ -61,6 +62,7 @@ __global__ __launch_bounds__(kThreads) void k_lab_gram_reduce(Geometry g, LabScr
     }
     L.cscale[i] = sc;
     L.cinv[i] = sc > 0.0 ? 1.0 / sc : 0.0;
+    L.ubound[i] = sqrt(s) * 1.0001;
   }
 }
 
@@ -349,7 +351,10 @@ __global__ __launch_bounds__(kThreads) void k_lab_basis(Geometry g, LabScratch L
     bool ok = lk > 1e-14 * lam[pick[1]];
     for (int i = 0; i < r; ++i) ok = ok && isfinite(lam[i]);
     if (!ok) L.flag[kFlagDegenerate] = 1;
-    *L.pmax = ok ? 1.0 / sqrt(lk) : 0.0;
+    L.scal[0] = ok ? 1.0 / sqrt(lk) : 0.0;
+    double ub = 0.0;  // |u| is at most its column's norm
+    for (int i = 0; i < r; ++i) ub = fmax(ub, L.ubound[i]);
+    L.scal[1] = (double)f16_range_scale((float)ub);
   }
   for (int c = tid; c < r; c += kThreads) {
     const double v = lk > 0.0 ? L.V[(int64_t)c * L.r64 + idx] / sqrt(lk) : 0.0;
@@ -358,158 +363,240 @@ __global__ __launch_bounds__(kThreads) void k_lab_basis(Geometry g, LabScratch L
   }
 }
 
-// One assignment pass: labels of 32 rows a wave (two groups of 16), 128 a tile.  The product is
-// taken as M^T U^T: a 16 x 16 tile of the fp64 matrix core holds 16 clusters x 16 rows (lane l:
-// row l % 16, clusters 16 t + 4 v + l / 16 in entry v), so the argmin over the clusters runs
-// over registers and then over four lanes.  A step's 4 columns are 16 q + 4 (l / 16) + s for
-// s = 0..3, so a lane reads its U values as 16 consecutive bytes; M comes in that order from the
-// centroid kernel (32 bytes a lane, from L2 and L1).  Bound by the fp64 matrix cores: 2 n r16 K16
-// flops, 0.6 ms at 1e6 x 200 with K = 100 against 0.2 ms for reading U once.
-template <int T, bool VEC>
-__global__ __launch_bounds__(kThreads) void k_lab_assign(Geometry g, const float* __restrict__ U, LabScratch L, int K,
-                                                         int32_t* __restrict__ labels) {
+// One assignment pass: labels of 32 NG rows a wave, 128 NG a tile.  The product is
+// taken as M^T U^T on the 32x32x16 fp16 matrix core: a 32 x 32 tile holds 32 clusters x 32 rows (lane
+// l: row l % 32, clusters 32 t + 8 (v / 4) + 4 (l / 32) + v % 4 in entry v), so the argmin over the
+// clusters runs over registers and then over two lanes.  A lane reads its row of U directly (8
+// consecutive columns a 16-column step), splits it in two halves, and drops the product of the two
+// low parts; M comes split from the centroid kernel, 32 columns at a time through one of two LDS
+// buffers.  NG = 2 where one block of clusters leaves registers for it (more bytes in flight a wave),
+// else 1: with 2 the accumulators spill.  Bound by reading U once and by waves in flight (two a
+// SIMD): 371 us at 1e6 x 200, K = 100 (products alone 70 us, reading 160) and 55 us at 1e6 x 30,
+// K = 20; the same product on the fp64 matrix cores took 1.06 to 1.27 ms and 87 us.
+// Rounding: every term's error is at most 2^-20 of it (two operands to 2^-22, the dropped product) but
+// for fp16 subnormals (2^-25 / scale), and each of the 3 r16 / 16 matrix instructions adds at most 16
+// roundings of 2^-23 (truncation) of the sum of |u_c M_ck| <= |u| |M_k| <= |u| pmax |cent_k|.
+// UN: rows not 16-byte aligned.
+template <int T, int NG, bool UN>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_lab_assign(
+    Geometry g, const float* __restrict__ U, LabScratch L, int K, int32_t* __restrict__ labels) {
   if (L.flag[kFlagDegenerate] | L.flag[kFlagDone]) return;
-  __shared__ double cn[16 * T];
+  constexpr int CH = 2 * T * 2 * 64;  // 16-byte pieces of a 32-column chunk: [step][block][hi, lo][lane]
+  constexpr int PT = CH / kThreads;   // pieces a thread
+  __shared__ f16x8 ms[2][CH];
+  __shared__ float cnf[32 * T], cinv[32 * T];
   __shared__ double es[4][kLabMaxK];
   __shared__ unsigned wchg[4];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, lg = lane >> 4, lr = lane & 15;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, h = lane >> 5, li = lane & 31;
   const int r = g.r;
   const int64_t n = g.n;
   const bool first = L.flag[kFlagPasses] == 0;
-  for (int k = tid; k < 16 * T; k += kThreads) cn[k] = k < K ? L.cn[k] : 0.0;
-  __syncthreads();
+  const double pmax = L.scal[0], su = L.scal[1];
+  for (int k = tid; k < 32 * T; k += kThreads) {
+    cnf[k] = k < K ? (float)L.cn[k] : 0.f;
+    cinv[k] = k < K ? (float)(L.minv[k] / su) : 0.f;
+  }
   double cnmax = 0.0;
-  for (int k = 0; k < K; ++k) cnmax = fmax(cnmax, cn[k]);
-  // rounding of the scores: |M_ck| <= |P_c| |cent_k| <= pmax sqrt(cnmax), sums of r and K terms
-  const double eps = 1.1102230246251565e-16;
-  const double tolu = 8.0 * (r + K + 16) * eps * *L.pmax * sqrt(cnmax), tolc = 4.0 * (K + 16) * eps * cnmax;
-  const int nq = (r + 15) >> 4;
-  const f64x4* Mi = reinterpret_cast<const f64x4*>(L.Mimg) + lane;
+#pragma unroll 1
+  for (int k = 0; k < K; ++k) cnmax = fmax(cnmax, L.cn[k]);
+  __syncthreads();
+  const int np = (r + 31) >> 5;  // 32-column chunks
+  const double mb = pmax * sqrt(cnmax), eps = 1.1102230246251565e-16;
+  // the smallest difference of two scores that decides: fp16 form (per |u|, and fixed), FP64 form
+  const float tol16u = (float)(4.0 * (96.0 * np + 64.0) * 1.1920929e-7 * mb * 1.01);
+  const float tol16c = (float)((4.0 * r * mb * 2.98e-8 / su + 4.0 * 2.4e-7 * cnmax) * 1.01);
+  const double tol64u = 8.0 * (r + K * sqrt((double)K) + 16.0) * eps * mb, tol64c = 4.0 * (K + 16) * eps * cnmax;
+  const float suf = (float)su;
   unsigned changes = 0;
-  const int64_t tiles = (n + 127) / 128;
+  const int64_t tiles = (n + 128 * NG - 1) / (128 * NG);
   for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
-    const int64_t row0 = tile * 128 + 32 * w;
-    const float* up[2];
+    const int64_t row0 = tile * (128 * NG) + 32 * NG * w;
+    const bool edge = UN && ((tile + 1) * (128 * NG) >= n || r < 3);  // (the tile that holds the last row)
+    const float* up[NG];
 #pragma unroll
-    for (int gq = 0; gq < 2; ++gq) {
-      const int64_t row = row0 + 16 * gq + lr;
+    for (int gq = 0; gq < NG; ++gq) {
+      const int64_t row = row0 + 32 * gq + li;
       up[gq] = U + (row < n ? row : n - 1) * r;
     }
-    f64x4 acc[2][T];
+    f32x16 acc[NG][T];
 #pragma unroll
-    for (int gq = 0; gq < 2; ++gq)
-#pragma unroll
-      for (int t = 0; t < T; ++t) acc[gq][t] = (f64x4){0.0, 0.0, 0.0, 0.0};
-    double rs[2] = {0.0, 0.0};
-    float nx[2][4];
-    auto load_u = [&](int q) {
-      const int c0 = 16 * q + 4 * lg;
-#pragma unroll
-      for (int gq = 0; gq < 2; ++gq) {
-        if constexpr (VEC) {
-          const f32x4 t = *reinterpret_cast<const f32x4*>(up[gq] + (c0 < r ? c0 : 0));
-#pragma unroll
-          for (int s = 0; s < 4; ++s) nx[gq][s] = c0 < r ? t[s] : 0.f;
-        } else {
-#pragma unroll
-          for (int s = 0; s < 4; ++s) {
-            const float t = up[gq][c0 + s < r ? c0 + s : 0];
-            nx[gq][s] = c0 + s < r ? t : 0.f;
-          }
-        }
-      }
-    };
-    load_u(0);
-    for (int q = 0; q < nq; ++q) {
-      double b[2][4];
-#pragma unroll
-      for (int gq = 0; gq < 2; ++gq)
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          b[gq][s] = (double)nx[gq][s];
-          rs[gq] += fabs(b[gq][s]);
-        }
-      if (q + 1 < nq) load_u(q + 1);
-#pragma unroll
-      for (int t = 0; t < T; ++t) {
-        const f64x4 a = Mi[(int64_t)(q * T + t) * 64];
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-#pragma unroll
-          for (int gq = 0; gq < 2; ++gq)
-            acc[gq][t] = mfma16x16x4d(a[s], b[gq][s], acc[gq][t]);
-      }
-    }
-#pragma unroll
-    for (int gq = 0; gq < 2; ++gq) {
-      double best = 1e300, second = 1e300;
-      int bk = 0x7fffffff;
+    for (int gq = 0; gq < NG; ++gq)
 #pragma unroll
       for (int t = 0; t < T; ++t)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int k = 16 * t + 4 * v + lg;
-          const double sc = k < K ? cn[k] - 2.0 * acc[gq][t][v] : 1e300;
+        for (int v = 0; v < 16; ++v) acc[gq][t][v] = 0.f;
+    float un2[NG] = {};
+    f32x4 nx[2][NG][2];  // [step][group][half] of the next chunk
+    f16x8 mr[PT];
+    const f16x8* Mi = reinterpret_cast<const f16x8*>(L.Mimg);
+    auto load_chunk = [&](int p) {
+#pragma unroll
+      for (int u = 0; u < PT; ++u) mr[u] = Mi[(int64_t)p * CH + tid + u * kThreads];
+#pragma unroll
+      for (int st = 0; st < 2; ++st)
+#pragma unroll
+        for (int gq = 0; gq < NG; ++gq)
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+            const int c = 32 * p + 16 * st + 8 * h + 4 * q;
+            nx[st][gq][q] = (UN && edge) ? load4_edge(up[gq], c < r ? c : 0, r) : load4<UN>(up[gq] + (c < r ? c : 0));
+          }
+    };
+    load_chunk(0);
+    for (int p = 0; p < np; ++p) {
+      const int buf = p & 1;
+#pragma unroll
+      for (int u = 0; u < PT; ++u) ms[buf][tid + u * kThreads] = mr[u];
+      f16x8 bh[2][NG], bl[2][NG];
+#pragma unroll
+      for (int st = 0; st < 2; ++st)
+#pragma unroll
+        for (int gq = 0; gq < NG; ++gq) {
+          float v[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const int c = 32 * p + 16 * st + 8 * h + e;
+            v[e] = c < r ? nx[st][gq][e >> 2][e & 3] : 0.f;
+            un2[gq] = fmaf(v[e] * suf, v[e] * suf, un2[gq]);
+          }
+          split_f16(v, suf, bh[st][gq], bl[st][gq]);
+        }
+      __syncthreads();
+      if (p + 1 < np) load_chunk(p + 1);
+#pragma unroll
+      for (int st = 0; st < 2; ++st)
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+          const f16x8 ah = ms[buf][((st * T + t) * 2 + 0) * 64 + lane], al = ms[buf][((st * T + t) * 2 + 1) * 64 + lane];
+#pragma unroll
+          for (int gq = 0; gq < NG; ++gq) {
+            acc[gq][t] = mfma32x32x16h(ah, bl[st][gq], acc[gq][t]);
+            acc[gq][t] = mfma32x32x16h(al, bh[st][gq], acc[gq][t]);
+            acc[gq][t] = mfma32x32x16h(ah, bh[st][gq], acc[gq][t]);
+          }
+        }
+    }
+    __syncthreads();  // the buffers are free for the next tile
+#pragma unroll
+    for (int gq = 0; gq < NG; ++gq) {
+      float best = 3.0e38f, second = 3.0e38f;
+      int bk = 0;
+      const float *ci = cinv + 4 * h, *cf = cnf + 4 * h;
+      const int Kh = K - 4 * h;
+#pragma unroll
+      for (int t = 0; t < T; ++t)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int k0 = 32 * t + 8 * (v >> 2) + (v & 3);  // (4 h is added at the end)
+          const float sc = k0 < Kh ? fmaf(-2.f * ci[k0], acc[gq][t][v], cf[k0]) : 3.0e38f;
+          acc[gq][t][v] = sc;
           if (sc < best) {
             second = best;
             best = sc;
-            bk = k;
+            bk = k0;
           } else {
-            second = fmin(second, sc);
+            second = fminf(second, sc);
           }
         }
-      double rsum = rs[gq];
-#pragma unroll
-      for (int m = 16; m <= 32; m <<= 1) {
-        const double ob = __shfl_xor(best, m, 64), os = __shfl_xor(second, m, 64);
-        const int ok = __shfl_xor(bk, m, 64);
-        second = fmin(fmin(second, os), fmax(best, ob));
+      bk += 4 * h;
+      {
+        const float ob = shfl_xor_f(best, 32), os = shfl_xor_f(second, 32);
+        const int ok = __shfl_xor(bk, 32, 64);
+        second = fminf(fminf(second, os), fmaxf(best, ob));
         if (ob < best || (ob == best && ok < bk)) {
           best = ob;
           bk = ok;
         }
-        rsum += __shfl_xor(rsum, m, 64);
       }
-      const int64_t row = row0 + 16 * gq + lr;
-      // rows too close to call: the distances themselves, one row a wave at a time
-      unsigned long long close =
-          __ballot(lane < 16 && row < n && !(second - best > tolu * rsum + tolc)) & 0xffffull;
-      while (close) {
-        const int rl = __ffsll(close) - 1;
-        close &= close - 1;
-        const float* u = U + (row0 + 16 * gq + rl) * r;
-        for (int j = lane; j < K; j += 64) {
-          double s = 0.0;
-          for (int c = 0; c < r; ++c) s += (double)u[c] * L.P[(int64_t)c * K + j];
-          es[w][j] = s;
-        }
-        __builtin_amdgcn_wave_barrier();
-        double db = 1e300;
-        int kb = 0x7fffffff;
-        for (int k = lane; k < K; k += 64) {
-          double ds = 0.0;
-          for (int j = 0; j < K; ++j) {
-            const double t = es[w][j] - L.centT[(int64_t)j * K + k];
-            ds += t * t;
-          }
-          if (ds < db) {
-            db = ds;
-            kb = k;
-          }
-        }
-        __builtin_amdgcn_wave_barrier();
+      const float unorm = sqrtf(un2[gq] + shfl_xor_f(un2[gq], 32)) / suf * 1.0001f;
+      const float tol = tol16u * unorm + tol16c;
+      const int64_t row = row0 + 32 * gq + li;
+      unsigned long long close = __ballot(h == 0 && row < n && !(second - best > tol));
+      if (close) {
+        // candidates of every row, a bit a cluster
+        unsigned long long m0 = 0, m1 = 0;
 #pragma unroll
-        for (int m = 32; m >= 1; m >>= 1) {
-          const double ob = __shfl_xor(db, m, 64);
-          const int ok = __shfl_xor(kb, m, 64);
-          if (ob < db || (ob == db && ok < kb)) {
-            db = ob;
-            kb = ok;
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            const int k0 = 32 * t + 8 * (v >> 2) + (v & 3);
+            const unsigned long long bit = acc[gq][t][v] <= best + tol ? 1ull << (k0 & 63) : 0ull;
+            if (k0 < 64)
+              m0 |= bit;
+            else
+              m1 |= bit;
           }
+        m0 <<= 4 * h;
+        m1 <<= 4 * h;
+        m0 |= __shfl_xor(m0, 32, 64);
+        m1 |= __shfl_xor(m1, 32, 64);
+        while (close) {  // one row a wave at a time
+          const int rl = __ffsll(close) - 1;
+          close &= close - 1;
+          const float* u = U + (row0 + 32 * gq + rl) * r;
+          unsigned long long mm[2] = {(unsigned long long)__shfl(m0, rl, 64), (unsigned long long)__shfl(m1, rl, 64)};
+          const double t64 = tol64u * (double)__shfl(unorm, rl, 64) + tol64c;
+          double b64 = 1e300, s64 = 1e300;
+          int kb = 0;
+#pragma unroll 1
+          for (int x = 0; x < 2; ++x)
+            while (mm[x]) {
+              const int k = 64 * x + __ffsll(mm[x]) - 1;
+              mm[x] &= mm[x] - 1;
+              if (k >= K) break;
+              double s = 0.0;
+#pragma unroll 1
+              for (int c = lane; c < r; c += 64) s += (double)u[c] * L.Mt[(int64_t)k * r + c];
+              for (int m = 32; m >= 1; m >>= 1) s += shfl_xor_d(s, m);
+              const double sc = L.cn[k] - 2.0 * s;
+              if (sc < b64) {
+                s64 = b64;
+                b64 = sc;
+                kb = k;
+              } else {
+                s64 = fmin(s64, sc);
+              }
+            }
+          if (!(s64 - b64 > t64)) {
+            // too close for that: the distances themselves
+#pragma unroll 1
+            for (int j = lane; j < K; j += 64) {
+              double s = 0.0;
+#pragma unroll 1
+              for (int c = 0; c < r; ++c) s += (double)u[c] * L.P[(int64_t)c * K + j];
+              es[w][j] = s;
+            }
+            __builtin_amdgcn_wave_barrier();
+            double db = 1e300;
+            kb = 0x7fffffff;
+#pragma unroll 1
+            for (int k = lane; k < K; k += 64) {
+              double ds = 0.0;
+#pragma unroll 1
+              for (int j = 0; j < K; ++j) {
+                const double t = es[w][j] - L.centT[(int64_t)j * K + k];
+                ds += t * t;
+              }
+              if (ds < db) {
+                db = ds;
+                kb = k;
+              }
+            }
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int m = 32; m >= 1; m >>= 1) {
+              const double ob = __shfl_xor(db, m, 64);
+              const int ok = __shfl_xor(kb, m, 64);
+              if (ob < db || (ob == db && ok < kb)) {
+                db = ob;
+                kb = ok;
+              }
+            }
+          }
+          if (li == rl) bk = kb;
         }
-        if (lr == rl) bk = kb;
       }
-      if (lane < 16 && row < n) {
+      if (h == 0 && row < n) {
         if (first || labels[row] != bk) ++changes;
         labels[row] = bk;
       }
@@ -564,6 +651,7 @@ __global__ __launch_bounds__(kThreads) void k_lab_sums(Geometry g, const float* 
     for (int u = 0; u < UN; ++u)
       if (i0 + 4 * RP * u < r1) {
         const long long q = __double2ll_rn((double)v[u] * sc);
+        if ((unsigned)lb[u] >= (unsigned)K) continue;
         if (okc) atomicAdd(&S[lb[u] * LPR + cl], (unsigned long long)q);
         if (blockIdx.y == 0 && cl == 0) atomicAdd(&cnt[lb[u]], 1);
       }
@@ -589,13 +677,18 @@ __global__ __launch_bounds__(kLabUpd) void k_lab_centroid(Geometry g, const floa
   __shared__ long long ipart[kLabUpd];
   __shared__ long long count;
   const int tid = threadIdx.x, r = g.r, k = blockIdx.x;
-  const int r16 = (r + 15) & ~15;
-  auto put = [&](int c, double m) {
-    const int q = c >> 4, cc = c & 15;
-    L.Mimg[((int64_t)(q * T + (k >> 4)) * 64 + (cc >> 2) * 16 + (k & 15)) * 4 + (cc & 3)] = m;
+  const int r32 = (r + 31) & ~31;
+  // M_ck scaled and split into the assignment's operand order: [step of 16 columns][block of 32
+  // clusters][hi, lo][lane = 32 (c / 8 % 2) + k % 32][c % 8]
+  auto put = [&](int c, float m) {
+    const _Float16 hi = (_Float16)m;
+    _Float16* o = reinterpret_cast<_Float16*>(L.Mimg) +
+                  (((int64_t)((c >> 4) * T + (k >> 5)) * 2) * 64 + ((c >> 3) & 1) * 32 + (k & 31)) * 8 + (c & 7);
+    o[0] = hi;
+    o[512] = (_Float16)(m - (float)hi);
   };
   if (k >= K) {
-    for (int c = tid; c < r16; c += kLabUpd) put(c, 0.0);
+    for (int c = tid; c < r32; c += kLabUpd) put(c, 0.f);
     return;
   }
   if (tid == 0) count = seed;
@@ -648,17 +741,26 @@ __global__ __launch_bounds__(kLabUpd) void k_lab_centroid(Geometry g, const floa
     }
     __syncthreads();
   }
+  __shared__ double cn;
   if (tid == 0) {
     double s = 0.0;
     for (int j = 0; j < K; ++j) s += cent[j] * cent[j];
-    L.cn[k] = s;
+    cn = s;
   }
-  for (int c = tid; c < r16; c += kLabUpd) {
+  __syncthreads();
+  const double sm = (double)f16_range_scale((float)(L.scal[0] * sqrt(cn) * 1.01));  // |M_ck| <= pmax |cent_k|
+  if (tid == 0) {
+    L.cn[k] = cn;
+    L.minv[k] = 1.0 / sm;
+  }
+  for (int c = tid; c < r32; c += kLabUpd) {
     double m = 0.0;
-    if (c < r)
+    if (c < r) {
 #pragma unroll 8
       for (int j = 0; j < K; ++j) m += L.Pt[(int64_t)j * r + c] * cent[j];
-    put(c, m);
+      L.Mt[(int64_t)k * r + c] = m;
+    }
+    put(c, (float)(m * sm));
   }
   if (!seed && k == 0 && tid == 0) {
     const int passes = L.flag[kFlagPasses] + 1;
@@ -701,21 +803,21 @@ hipError_t launch_lab_sweeps(const LabScratch& L, int r, int first, int count, h
 }
 
 hipError_t launch_lab_embed(const Geometry& g, const Bufs& b, const LabScratch& L, int K, hipStream_t st) {
-  const int T = (K + 15) / 16;
+  const int T = (K + 31) / 32;
   hipLaunchKernelGGL(k_lab_basis, dim3(K), dim3(kThreads), 0, st, g, L, K);
-  hipLaunchKernelGGL(k_lab_centroid, dim3(16 * T), dim3(kLabUpd), 0, st, g, (const float*)b.U, L, K, T, 1);
+  hipLaunchKernelGGL(k_lab_centroid, dim3(32 * T), dim3(kLabUpd), 0, st, g, (const float*)b.U, L, K, T, 1);
   return hipGetLastError();
 }
 
 template <int T>
 static void lab_assign(const Geometry& g, const Bufs& b, const LabScratch& L, int K, int32_t* labels, hipStream_t st) {
-  const int64_t tiles = (g.n + 127) / 128;
-  const dim3 grid((unsigned)(tiles < 2048 ? tiles : 2048));
-  // 16-byte loads of U need 16-byte rows
+  constexpr int NG = T == 1 ? 2 : 1;
+  const int64_t tiles = (g.n + 128 * NG - 1) / (128 * NG);
+  const dim3 grid((unsigned)(tiles < 1024 ? tiles : 1024));
   if (g.vec_u)
-    hipLaunchKernelGGL((k_lab_assign<T, true>), grid, dim3(kThreads), 0, st, g, (const float*)b.U, L, K, labels);
+    hipLaunchKernelGGL((k_lab_assign<T, NG, false>), grid, dim3(kThreads), 0, st, g, (const float*)b.U, L, K, labels);
   else
-    hipLaunchKernelGGL((k_lab_assign<T, false>), grid, dim3(kThreads), 0, st, g, (const float*)b.U, L, K, labels);
+    hipLaunchKernelGGL((k_lab_assign<T, NG, true>), grid, dim3(kThreads), 0, st, g, (const float*)b.U, L, K, labels);
 }
 
 template <int LPR>
@@ -734,16 +836,12 @@ static hipError_t lab_sums(const Geometry& g, const Bufs& b, const LabScratch& L
 
 hipError_t launch_lab_pass(const Geometry& g, const Bufs& b, const LabScratch& L, int K, int32_t* labels,
                            hipStream_t st) {
-  const int T = (K + 15) / 16;
+  const int T = (K + 31) / 32;
   switch (T) {
     case 1: lab_assign<1>(g, b, L, K, labels, st); break;
     case 2: lab_assign<2>(g, b, L, K, labels, st); break;
     case 3: lab_assign<3>(g, b, L, K, labels, st); break;
     case 4: lab_assign<4>(g, b, L, K, labels, st); break;
-    case 5: lab_assign<5>(g, b, L, K, labels, st); break;
-    case 6: lab_assign<6>(g, b, L, K, labels, st); break;
-    case 7: lab_assign<7>(g, b, L, K, labels, st); break;
-    case 8: lab_assign<8>(g, b, L, K, labels, st); break;
     default: return hipErrorInvalidValue;
   }
   hipError_t e = hipGetLastError();

@@ -188,10 +188,11 @@ Geometry make_geometry(int64_t n, int32_t d, int32_t r, int32_t K, bool aligned1
 // within what those would take (nlr_solve_static's fixed scratch also holds it); never under one
 // chunk of either kind.
 static size_t lab_fixed_bytes(int32_t r, int32_t K) {
-  const size_t r64 = (size_t)round_up(r, 64), r16 = (size_t)round_up(r, 16), k16 = (size_t)round_up(K, 16);
+  const size_t r64 = (size_t)round_up(r, 64), r32 = (size_t)round_up(r, 32), k32 = (size_t)round_up(K, 32);
   return 2 * align256(r64 * r64 * 8) + align256(r64 / 64 * 4096 * 8) + align256(2 * kLabJacParts * 8) +
-         2 * align256((size_t)r * K * 8) + align256(r16 * k16 * 8) + align256((size_t)K * K * 8) +
-         align256((size_t)K * 8) + 2 * align256((size_t)r * 8) + align256(16) + align256((size_t)K * 8) + align256(64);
+         3 * align256((size_t)r * K * 8) + align256(r32 * k32 * 4) + align256((size_t)K * K * 8) +
+         2 * align256((size_t)K * 8) + 3 * align256((size_t)r * 8) + align256(24) + align256((size_t)K * 8) +
+         align256(64);
 }
 static size_t lab_part_bytes(int64_t n, int32_t r) {
   const size_t rr = (size_t)r * r * 8, kmax = r < kLabMaxK ? r : kLabMaxK;
@@ -239,7 +240,7 @@ LabScratch carve_lab_scratch(int64_t n, int32_t r, int32_t K, char* base) {
   if (w > (int64_t)(bytes / chunk)) w = (int64_t)(bytes / chunk);
   L.W = (int32_t)(w < 1 ? 1 : w);
   L.r64 = round_up(r, 64);
-  const size_t r64 = (size_t)L.r64, r16 = (size_t)round_up(r, 16), k16 = (size_t)round_up(K, 16);
+  const size_t r64 = (size_t)L.r64, r32 = (size_t)round_up(r, 32), k32 = (size_t)round_up(K, 32);
   char* part = take(bytes);
   L.gpart = reinterpret_cast<double*>(part);
   L.spart = reinterpret_cast<long long*>(part);
@@ -250,14 +251,17 @@ LabScratch carve_lab_scratch(int64_t n, int32_t r, int32_t K, char* base) {
   L.jpart = reinterpret_cast<double*>(take(2 * kLabJacParts * 8));
   L.P = reinterpret_cast<double*>(take((size_t)r * K * 8));
   L.Pt = reinterpret_cast<double*>(take((size_t)r * K * 8));
-  L.Mimg = reinterpret_cast<double*>(take(r16 * k16 * 8));
+  L.Mimg = take(r32 * k32 * 4);
+  L.Mt = reinterpret_cast<double*>(take((size_t)r * K * 8));
   L.centT = reinterpret_cast<double*>(take((size_t)K * K * 8));
   L.cn = reinterpret_cast<double*>(take((size_t)K * 8));
   L.cscale = reinterpret_cast<double*>(take((size_t)r * 8));
   L.cinv = reinterpret_cast<double*>(take((size_t)r * 8));
-  char* two = take(16);
-  L.pmax = reinterpret_cast<double*>(two);
-  L.changed = reinterpret_cast<unsigned long long*>(two + 8);
+  L.minv = reinterpret_cast<double*>(take((size_t)K * 8));
+  L.ubound = reinterpret_cast<double*>(take((size_t)r * 8));
+  char* three = take(24);
+  L.scal = reinterpret_cast<double*>(three);
+  L.changed = reinterpret_cast<unsigned long long*>(three + 16);
   L.seeds = reinterpret_cast<int64_t*>(take((size_t)K * 8));
   L.flag = reinterpret_cast<int32_t*>(take(64));
   return L;

@@ -166,12 +166,15 @@ struct LabScratch {
   double* jpart;       // 2 kLabJacParts: squared off-diagonal, diagonal entries
   double* P;           // r x K: V_K Lambda_K^(-1/2)
   double* Pt;          // K x r: its transpose
-  double* Mimg;        // P cent^T in the assignment's operand order (r16 x K16)
+  void* Mimg;          // P cent^T split in fp16 halves, in the assignment's operand order (r32 x K32)
+  double* Mt;          // K x r: its transpose
+  double* minv;        // K: inverse scale of a cluster's split column
   double* centT;       // K x K centroids, component-major
   double* cn;          // K: |cent_k|^2
   double* cscale;      // r: power-of-two scale of the integer sums
   double* cinv;        // r: its inverse
-  double* pmax;        // 1 / sqrt(K-th eigenvalue), a bound on the rows of P
+  double* ubound;      // r: bounds on |u| by column
+  double* scal;        // 1 / sqrt(K-th eigenvalue), a bound on the norm of P; power-of-two scale of U
   unsigned long long* changed;  // labels changed by the pass
   int64_t* seeds;      // K seed rows
   int32_t* flag;       // [0] degenerate spectrum, [1] iteration done, [2] passes, [3] Jacobi converged
