@@ -611,52 +611,123 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
   }
 }
 
-// Cluster sums of the rows of U over row chunk blockIdx.x, columns 64 blockIdx.y .. + 63: a lane
-// holds column c and adds llrint(u 2^(61 - e_c)) to its cluster's entry in LDS.  Integer sums do
-// not depend on the order, so LDS atomics stay reproducible bit for bit; every term keeps
-// 61 - log2(sqrt(n G_cc)) binary places, so a fp32 u above 2^-37 of that bound is summed exactly
-// and the sum's error is n 2^-62 of it at most (FP64 sums: n 2^-53).  LPR lanes a row (16, 32 or
-// 64): narrow factors take several rows an instruction.  Bound by reading U once (0.8 GB at 1e6 x
-// 200); a one-hot product on the fp64 matrix cores would take as long as the assignment.
-template <int LPR>
+// Cluster sums of the rows of U over row chunk blockIdx.x, columns 64 blockIdx.y .. + 63: the sum
+// of llrint(u 2^(61 - e_c)).  Integer sums do not depend on the order, so they are reproducible
+// bit for bit; every term keeps 61 - log2(sqrt(n G_cc)) binary places, so a fp32 u above 2^-37 of
+// that bound is summed exactly and the sum's error is n 2^-62 of it at most (FP64 sums: n 2^-53).
+// The rows of a piece of the chunk are sorted by label in LDS (counting sort); G lanes take a row,
+// four columns each, and a group of them the same number of consecutive sorted rows, summed in
+// registers: the LDS atomics into the cluster's entry come once a run of equal labels.  (One atomic
+// an element ran at the LDS unit's one 64-bit atomic a clock: 386 us at 1e6 x 200 with K = 100 and
+// 69 us at 1e6 x 30 with K = 20; this way 180 and 36 us.)  Bound by reading U once (4.4 and 3.3 TB/s).
+// SMALL: fewer than four columns.  UN: rows not 16-byte aligned; the last quad of a row then starts
+// at column r - 4 and leaves out the columns of the quad before.
+constexpr int kLabPiece = 2048;  // rows sorted at a time
+template <int G, bool UN, bool SMALL>
 __global__ __launch_bounds__(kThreads) void k_lab_sums(Geometry g, const float* __restrict__ U, LabScratch L, int K,
                                                        const int32_t* __restrict__ labels) {
   if (L.flag[kFlagDegenerate] | L.flag[kFlagDone]) return;
   extern __shared__ __align__(16) unsigned char smem_raw[];
+  constexpr int LPR = 4 * G, SUBS = kThreads / G, UNR = 8, RT = kLabPiece / kThreads;
   unsigned long long* S = reinterpret_cast<unsigned long long*>(smem_raw);  // K x LPR
   int* cnt = reinterpret_cast<int*>(S + K * LPR);                           // K
-  constexpr int RP = 64 / LPR, UN = 8;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  __shared__ unsigned order[kLabPiece];                                     // row | label << 16, by label
+  __shared__ int hist[kLabMaxK], base[kLabMaxK + 1];
+  const int tid = threadIdx.x, lane = tid & 63;
   const int r = g.r;
   const int64_t n = g.n;
   for (int e = tid; e < K * LPR; e += kThreads) S[e] = 0;
   for (int e = tid; e < K; e += kThreads) cnt[e] = 0;
-  __syncthreads();
   const int64_t r0 = (int64_t)blockIdx.x * n / L.W, r1 = (int64_t)(blockIdx.x + 1) * n / L.W;
-  const int cl = lane & (LPR - 1), sub = lane / LPR;
-  const int c = 64 * blockIdx.y + cl;
-  const bool okc = c < r;
-  const double sc = okc ? L.cscale[c] : 0.0;
-  const float* up = U + (okc ? c : 0);
-  for (int64_t i0 = r0 + w * RP + sub; i0 < r1; i0 += 4 * RP * UN) {
-    float v[UN];
-    int lb[UN];
+  const int sub = tid / G, ql = 4 * (tid & (G - 1));  // this lane's columns in the group
+  const int c0 = 64 * blockIdx.y + ql;
+  const int cb = SMALL ? 0 : (c0 + 4 <= r ? c0 : r - 4);  // first column loaded
+  int ex[4], sl[4];                                       // exponent of the first word's scale; slot
 #pragma unroll
-    for (int u = 0; u < UN; ++u) {
-      const int64_t i = i0 + 4 * RP * u, ic = i < r1 ? i : r0;
-      v[u] = up[ic * r];
-      lb[u] = labels[ic];
+  for (int e = 0; e < 4; ++e) {
+    const int c = cb + e;
+    const bool on = c0 < r && c >= c0 && c < r;
+    const double sc = on ? L.cscale[c] : 0.0;
+    ex[e] = sc > 0.0 ? ilogb(sc) - 31 : -4000;
+    sl[e] = on ? c - 64 * (int)blockIdx.y : -1;
+  }
+  for (int64_t s0 = r0; s0 < r1; s0 += kLabPiece) {
+    const int m = (int)(r1 - s0 < kLabPiece ? r1 - s0 : kLabPiece);
+    for (int k = tid; k < kLabMaxK; k += kThreads) hist[k] = 0;
+    __syncthreads();
+    int lb[RT], rk[RT];
+#pragma unroll
+    for (int u = 0; u < RT; ++u) {
+      const int i = tid + u * kThreads;
+      lb[u] = i < m ? labels[s0 + i] : -1;
     }
 #pragma unroll
-    for (int u = 0; u < UN; ++u)
-      if (i0 + 4 * RP * u < r1) {
-        const long long q = __double2ll_rn((double)v[u] * sc);
-        if ((unsigned)lb[u] >= (unsigned)K) continue;
-        if (okc) atomicAdd(&S[lb[u] * LPR + cl], (unsigned long long)q);
-        if (blockIdx.y == 0 && cl == 0) atomicAdd(&cnt[lb[u]], 1);
+    for (int u = 0; u < RT; ++u) rk[u] = (unsigned)lb[u] < (unsigned)K ? atomicAdd(&hist[lb[u]], 1) : 0;
+    __syncthreads();
+    if (tid < 64) {
+      const int h0 = hist[2 * lane], h1 = hist[2 * lane + 1];
+      int x = h0 + h1;
+      for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(x, o, 64);
+        if (lane >= o) x += y;
       }
+      base[2 * lane] = x - h0 - h1;
+      base[2 * lane + 1] = x - h1;
+      if (lane == 63) base[kLabMaxK] = x;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < RT; ++u)
+      if ((unsigned)lb[u] < (unsigned)K)
+        order[base[lb[u]] + rk[u]] = (unsigned)(tid + u * kThreads) | (unsigned)lb[u] << 16;
+    if (tid < K) cnt[tid] += hist[tid];
+    __syncthreads();
+    const int mt = base[kLabMaxK];
+    const int p0 = sub * mt / SUBS, p1 = (sub + 1) * mt / SUBS;
+    long long acc[4] = {0, 0, 0, 0};
+    int cur = -1;
+    auto flush = [&]() {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if (cur >= 0 && sl[e] >= 0) atomicAdd(&S[cur * LPR + sl[e]], (unsigned long long)acc[e]);
+        acc[e] = 0;
+      }
+    };
+    for (int p = p0; p < p1; p += UNR) {
+      unsigned o[UNR];
+      f32x4 v[UNR];
+#pragma unroll
+      for (int u = 0; u < UNR; ++u) o[u] = order[p + u < p1 ? p + u : p];
+#pragma unroll
+      for (int u = 0; u < UNR; ++u) {
+        const float* row = U + (s0 + (o[u] & 0xffff)) * r + cb;
+        if constexpr (SMALL) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[u][e] = row[e < r ? e : 0];
+        } else {
+          v[u] = load4<UN>(row);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < UNR; ++u)
+        if (p + u < p1) {
+          const int k = (int)(o[u] >> 16);
+          if (k != cur) {
+            flush();
+            cur = k;
+          }
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            // v 2^(ex + 31), |.| < 2^61, as hi 2^31 + lo: both steps are exact but for lo's rounding
+            const float t = ldexpf(v[u][e], ex[e]);
+            const float hi = truncf(t), lo = rintf((t - hi) * 2147483648.f);
+            acc[e] += (long long)(int)hi * 2147483648ll + (int)lo;
+          }
+        }
+    }
+    flush();
+    __syncthreads();
   }
-  __syncthreads();
   for (int e = tid; e < K * LPR; e += kThreads) {
     const int k = e / LPR, cc = 64 * blockIdx.y + (e & (LPR - 1));
     if (cc < r) L.spart[((int64_t)blockIdx.x * K + k) * r + cc] = (long long)S[e];
@@ -820,17 +891,17 @@ static void lab_assign(const Geometry& g, const Bufs& b, const LabScratch& L, in
     hipLaunchKernelGGL((k_lab_assign<T, NG, true>), grid, dim3(kThreads), 0, st, g, (const float*)b.U, L, K, labels);
 }
 
-template <int LPR>
+template <int G, bool UN, bool SMALL>
 static hipError_t lab_sums(const Geometry& g, const Bufs& b, const LabScratch& L, int K, const int32_t* labels,
                            hipStream_t st) {
-  const size_t lds = (size_t)K * LPR * 8 + (size_t)K * 4;
-  if (lds > (64u << 10)) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_lab_sums<LPR>),
+  const size_t lds = (size_t)K * 4 * G * 8 + (size_t)K * 4;
+  if (lds > (48u << 10)) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_lab_sums<G, UN, SMALL>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((k_lab_sums<LPR>), dim3(L.W, (g.r + 63) / 64), dim3(kThreads), lds, st, g, (const float*)b.U, L,
-                     K, labels);
+  hipLaunchKernelGGL((k_lab_sums<G, UN, SMALL>), dim3(L.W, (g.r + 63) / 64), dim3(kThreads), lds, st, g,
+                     (const float*)b.U, L, K, labels);
   return hipGetLastError();
 }
 
@@ -846,8 +917,11 @@ hipError_t launch_lab_pass(const Geometry& g, const Bufs& b, const LabScratch& L
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  e = g.r <= 16 ? lab_sums<16>(g, b, L, K, labels, st)
-                : (g.r <= 32 ? lab_sums<32>(g, b, L, K, labels, st) : lab_sums<64>(g, b, L, K, labels, st));
+  const bool v = g.vec_u;
+  e = g.r < 4    ? lab_sums<4, true, true>(g, b, L, K, labels, st)
+      : g.r <= 16 ? (v ? lab_sums<4, false, false>(g, b, L, K, labels, st) : lab_sums<4, true, false>(g, b, L, K, labels, st))
+      : g.r <= 32 ? (v ? lab_sums<8, false, false>(g, b, L, K, labels, st) : lab_sums<8, true, false>(g, b, L, K, labels, st))
+                  : (v ? lab_sums<16, false, false>(g, b, L, K, labels, st) : lab_sums<16, true, false>(g, b, L, K, labels, st));
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_lab_centroid, dim3(K), dim3(kLabUpd), 0, st, g, (const float*)b.U, L, K, T, 0);
   return hipGetLastError();

@@ -132,6 +132,17 @@ def test_labels_spectral_shapes(n, r, K):
     _check(ctx, K, seeds, max_iter=12)
 
 
+def test_labels_spectral_long_chunks():
+    """Row chunks of the cluster sums longer than the 2048 rows sorted at a time (128 chunks of
+    2055 rows at r = 193): labels and pass counts identical to the oracle's."""
+    n, r, K = 263_000, 193, 5
+    U, _ = _pattern_factor(n, K, r, seed=11)
+    X, _, _ = gaussian_mixture(n, 4, 1, 1.0, seed=3)
+    ctx = make_ctx(X, U, K, 0.01, flags=4)  # NLR_INIT_X_NORMALISED: only the factor matters here
+    seeds = np.random.default_rng(7).choice(n, size=K, replace=False).tolist()
+    _check(ctx, K, seeds, max_iter=4)
+
+
 def test_labels_spectral_equal_rows():
     """Every row of a cluster equal and two seeds in one cluster: two equal centroids, the lower
     index takes all of that cluster's rows and the other keeps its place without any."""
