@@ -15,7 +15,7 @@
 //   FP64 over its candidates, and one whose values are too close for that by the distances
 //   themselves (FP64, lowest index on ties), so that the labels are those of FP64 distances.  The
 //   cluster sums S_k = sum of u_i over the rows of k are taken in 64-bit integers (below), and
-//   cent_k = (S_k P) / count (a centroid without rows stays in place).
+//   cent_k = (S_k / count) P (a centroid without rows stays in place).
 // The device notes the first pass that changes no label; passes enqueued after it return
 // at entry.
 #include "k_common.hpp"
@@ -392,9 +392,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
   const int64_t n = g.n;
   const bool first = L.flag[kFlagPasses] == 0;
   const double pmax = L.scal[0], su = L.scal[1];
+  // (a centroid that equals an earlier one takes no row, see k_lab_centroid)
   for (int k = tid; k < 32 * T; k += kThreads) {
-    cnf[k] = k < K ? (float)L.cn[k] : 0.f;
-    cinv[k] = k < K ? (float)(L.minv[k] / su) : 0.f;
+    const bool on = k < K && L.lead[k] == k;
+    cnf[k] = on ? (float)L.cn[k] : 3.0e38f;
+    cinv[k] = on ? (float)(L.minv[k] / su) : 0.f;
   }
   double cnmax = 0.0;
 #pragma unroll 1
@@ -538,8 +540,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
           const double t64 = tol64u * (double)__shfl(unorm, rl, 64) + tol64c;
           double b64 = 1e300, s64 = 1e300;
           int kb = 0;
+          // (a candidate costs a sum over the wave; with many of them the distances are cheaper)
+          const bool few = __popcll(mm[0]) + __popcll(mm[1]) <= 4;
 #pragma unroll 1
-          for (int x = 0; x < 2; ++x)
+          for (int x = 0; few && x < 2; ++x)
             while (mm[x]) {
               const int k = 64 * x + __ffsll(mm[x]) - 1;
               mm[x] &= mm[x] - 1;
@@ -741,12 +745,19 @@ __global__ __launch_bounds__(kThreads) void k_lab_sums(Geometry g, const float* 
 // launch only: zeros).  Workgroup 0 settles the pass: the first one that changed no label ends
 // the iteration.  One workgroup a centroid; the sums over chunks, columns and components are each
 // shared by groups of threads (a single workgroup for all centroids: 2.7 ms at K = 100).
+// Equal centroids: a centroid equal to an earlier one, bit for bit, takes no row (its distances are
+// equal too, and the lowest index wins), so the assignment masks it; found tied row by row, a pass
+// over 1e6 x 16 with one seed for all 16 clusters took 5.7 ms, masked 0.17 ms.  Equal seed rows give
+// them.  grp: the first cluster with this seed row; lead: the first of those whose centroid is still
+// the seed's (the others have no rows and keep theirs).  A cluster that is not its own lead forms
+// the lead's new centroid instead of one, and passes to the next of the group when that has left.
 __global__ __launch_bounds__(kLabUpd) void k_lab_centroid(Geometry g, const float* __restrict__ U, LabScratch L, int K,
                                                           int T, int seed) {
   if (L.flag[kFlagDegenerate] | L.flag[kFlagDone]) return;
   __shared__ double sums[kMaxR], cent[kLabMaxK], part[kLabUpd];
   __shared__ long long ipart[kLabUpd];
   __shared__ long long count;
+  __shared__ int eq;
   const int tid = threadIdx.x, r = g.r, k = blockIdx.x;
   const int r32 = (r + 31) & ~31;
   // M_ck scaled and split into the assignment's operand order: [step of 16 columns][block of 32
@@ -762,21 +773,37 @@ __global__ __launch_bounds__(kLabUpd) void k_lab_centroid(Geometry g, const floa
     for (int c = tid; c < r32; c += kLabUpd) put(c, 0.f);
     return;
   }
-  if (tid == 0) count = seed;
+  const int src = seed ? k : L.lead[k];  // the cluster whose centroid is formed
+  if (tid == 0) {
+    count = seed;
+    eq = k;
+  }
   __syncthreads();
   if (seed) {
     const float* u = U + L.seeds[k] * r;
     for (int c = tid; c < r; c += kLabUpd) sums[c] = (double)u[c];
+    if (tid < k) {  // (K <= kLabUpd)
+      const float* v = U + L.seeds[tid] * r;
+      int differ = 0;
+      for (int c = 0; c < r && !differ; c += 8)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const int ce = c + e < r ? c + e : c;
+          differ |= u[ce] != v[ce];
+        }
+      if (!differ) atomicMin(&eq, tid);
+    }
     __syncthreads();
+    if (tid == 0) L.grp[k] = L.lead[k] = eq;
   } else {
     long long nc = 0;
-    for (int w = tid; w < L.W; w += kLabUpd) nc += L.cpart[w * K + k];
+    for (int w = tid; w < L.W; w += kLabUpd) nc += L.cpart[w * K + src];
     if (nc) atomicAdd(reinterpret_cast<unsigned long long*>(&count), (unsigned long long)nc);
     const int cw = (r + 63) & ~63;            // r <= 448: one to eight groups of threads
     const int ng = kLabUpd / cw, gq = tid / cw, c = tid - gq * cw;
     long long s = 0;
     if (gq < ng && c < r) {
-      const long long* p = L.spart + (int64_t)k * r + c;
+      const long long* p = L.spart + (int64_t)src * r + c;
       const int64_t st = (int64_t)K * r;
       int w = gq;
       for (; w + 7 * ng < L.W; w += 8 * ng) {
@@ -792,11 +819,13 @@ __global__ __launch_bounds__(kLabUpd) void k_lab_centroid(Geometry g, const floa
     __syncthreads();
     if (gq == 0 && c < r) {
       for (int h = 1; h < ng; ++h) s += ipart[tid + h * cw];
-      sums[c] = (double)s * L.cinv[c];
+      // the mean row: that of equal rows is the row itself (their sum is exact), so its embedding
+      // is that of the row as a seed, bit for bit
+      sums[c] = (double)s * L.cinv[c] / (double)count;
     }
     __syncthreads();
   }
-  {  // cent_j = sum_c sums[c] P[c][j] / count, the terms c = gq, gq + 4, ... by thread group gq
+  {  // cent_j = sum_c sums[c] P[c][j], the terms c = gq, gq + 4, ... by thread group gq
     const int j = tid & 127, gq = tid >> 7;
     double s = 0.0;
     if (j < K)
@@ -804,9 +833,19 @@ __global__ __launch_bounds__(kLabUpd) void k_lab_centroid(Geometry g, const floa
       for (int c = gq; c < r; c += 4) s += sums[c] * L.P[(int64_t)c * K + j];
     part[tid] = s;
     __syncthreads();
+    double v = 0.0;
+    if (tid < K) v = ((part[tid] + part[128 + tid]) + part[256 + tid]) + part[384 + tid];
+    if (src != k) {
+      const bool left = tid < K && count > 0 && v != L.centT[(int64_t)tid * K + k];
+      if (__syncthreads_or(left) && tid == 0) {
+        int j = src + 1;
+        while (j < k && L.grp[j] != L.grp[k]) ++j;
+        L.lead[k] = j;
+      }
+      return;
+    }
     if (tid < K) {
-      double v = ((part[tid] + part[128 + tid]) + part[256 + tid]) + part[384 + tid];
-      v = count > 0 ? v / (double)count : L.centT[(int64_t)tid * K + k];
+      if (count == 0) v = L.centT[(int64_t)tid * K + k];
       cent[tid] = v;
       L.centT[(int64_t)tid * K + k] = v;
     }

@@ -191,7 +191,7 @@ static size_t lab_fixed_bytes(int32_t r, int32_t K) {
   const size_t r64 = (size_t)round_up(r, 64), r32 = (size_t)round_up(r, 32), k32 = (size_t)round_up(K, 32);
   return 2 * align256(r64 * r64 * 8) + align256(r64 / 64 * 4096 * 8) + align256(2 * kLabJacParts * 8) +
          3 * align256((size_t)r * K * 8) + align256(r32 * k32 * 4) + align256((size_t)K * K * 8) +
-         2 * align256((size_t)K * 8) + 3 * align256((size_t)r * 8) + align256(24) + align256((size_t)K * 8) +
+         2 * align256((size_t)K * 8) + 3 * align256((size_t)r * 8) + align256(24) + 2 * align256((size_t)K * 8) +
          align256(64);
 }
 static size_t lab_part_bytes(int64_t n, int32_t r) {
@@ -263,6 +263,8 @@ LabScratch carve_lab_scratch(int64_t n, int32_t r, int32_t K, char* base) {
   L.scal = reinterpret_cast<double*>(three);
   L.changed = reinterpret_cast<unsigned long long*>(three + 16);
   L.seeds = reinterpret_cast<int64_t*>(take((size_t)K * 8));
+  L.grp = reinterpret_cast<int32_t*>(take((size_t)K * 8));
+  L.lead = L.grp + K;
   L.flag = reinterpret_cast<int32_t*>(take(64));
   return L;
 }

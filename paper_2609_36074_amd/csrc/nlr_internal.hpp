@@ -177,6 +177,8 @@ struct LabScratch {
   double* scal;        // 1 / sqrt(K-th eigenvalue), a bound on the norm of P; power-of-two scale of U
   unsigned long long* changed;  // labels changed by the pass
   int64_t* seeds;      // K seed rows
+  int32_t* grp;        // K: first cluster with the same seed row
+  int32_t* lead;       // K: first cluster whose centroid is equal by that (k itself: none before it)
   int32_t* flag;       // [0] degenerate spectrum, [1] iteration done, [2] passes, [3] Jacobi converged
 };
 size_t lab_scratch_bytes(int64_t n, int32_t r, int32_t K);

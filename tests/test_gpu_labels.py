@@ -159,3 +159,75 @@ def test_labels_spectral_equal_rows():
         assert (got[lab == k] == k).all()
     assert len(set(got[lab == 4])) == 1 and not (got == 4).any()
     assert passes == 2
+
+
+@pytest.mark.parametrize("n,r,K", [(900, 4, 4), (1200, 9, 6), (5003, 16, 16), (7000, 33, 20), (20011, 20, 20),
+                                   (4000, 70, 40), (6000, 128, 100), (60000, 5, 3)])
+def test_labels_spectral_two_seeds_in_one_cluster(n, r, K):
+    """As above at more sizes: the mean of equal rows embeds exactly as the row itself does, so the
+    two centroids stay equal and the second pass changes nothing, whatever the rounding."""
+    rng = np.random.default_rng(n)
+    own = np.arange(r) % K
+    pattern = np.zeros((K, r))
+    pattern[own, np.arange(r)] = 0.5 + rng.random(r)
+    lab = rng.integers(0, K, n)
+    lab[rng.random(n) < 0.3] = 0  # the rows without a seed of their own are nearest to the largest cluster
+    U = pattern[lab].astype(np.float32)
+    X, _, _ = gaussian_mixture(n, 4, 1, 1.0, seed=3)
+    ctx = make_ctx(X, U, K, 0.01, flags=4)
+    seeds = [int(np.flatnonzero(lab == k)[0]) for k in range(K)]
+    seeds[K - 1] = int(np.flatnonzero(lab == 1)[1])
+    got, passes = ctx.labels_spectral(K, seeds)
+    got = got.cpu().numpy()
+    log(f"  passes {passes}")
+    assert np.array_equal(got, np.where(lab == K - 1, 0, lab))
+    assert passes == 2
+
+
+@pytest.mark.parametrize("m,r", [(2, 4), (2, 20), (6, 40), (2, 70), (6, 128)])
+def test_labels_spectral_score_gaps(m, r):
+    """Rows equally far from m of the K = r seeds but for a helper column of size eps that favours
+    one of them, eps in decades from 1 to 1e-11: the differences of the scores run through the
+    bounds at which the fp16 products, then the FP64 scores, decide.  The data is the same
+    under every permutation of the m seeds (each row comes with its permuted ones), so the
+    sign of eps alone decides in exact arithmetic; the FP64 route resolves 1e-15 of a
+    score of order 1, and eps 1e-11 shifts them by some 1e-12."""
+    import torch
+    rows, want = [], []
+
+    def add(row, lab, times=1):
+        for _ in range(times):
+            rows.append(row)
+            want.append(lab)
+
+    e = np.eye(r)
+    helper = lambda k: e[m + k]
+    for k in range(m):
+        add(e[k] + 0.5 * helper(k), k, 4)
+    for k in range(m):
+        add(5.0 * helper(k), m + k, 2)
+    for k in range(2 * m, r):
+        add(5.0 * e[k], k, 2)
+    for k in range(m):  # (correlates the helpers with the seeds; not compared)
+        add(0.6 * e[k] - 0.7 * helper(k), r, 3)
+    for dec in range(12):
+        for f in (1.0, 2.7, 7.3):
+            for sign in (1.0, -1.0):
+                if f * 10.0 ** -dec > 1.0:
+                    continue
+                for j in range(m):
+                    add(e[:m].sum(axis=0) / m + sign * f * 10.0 ** -dec * helper(j), j if sign > 0 else -1 - j)
+    U, want = np.array(rows, dtype=np.float32), np.array(want)
+    n = U.shape[0]
+    seeds = [4 * k for k in range(m)] + [4 * m + 2 * k for k in range(r - m)]
+    X, _, _ = gaussian_mixture(n, 4, 1, 1.0, seed=3)
+    ctx = make_ctx(X, np.abs(U), r, 0.01, flags=4)
+    ctx.U.copy_(torch.from_numpy(U))  # (with its negative entries)
+    got = ctx.labels_spectral(r, seeds, max_iter=1)[0].cpu().numpy()
+    for j in range(m):  # a negative helper: any of the others, which are equally near
+        neg = want == -1 - j
+        assert ((got[neg] != j) & (got[neg] < m)).all()
+        if m == 2:
+            assert (got[neg] == 1 - j).all()
+    known = (want >= 0) & (want < r)
+    assert np.array_equal(got[known], want[known])
