@@ -182,11 +182,9 @@ Geometry make_geometry(int64_t n, int32_t d, int32_t r, int32_t K, bool aligned1
   return g;
 }
 
-// The label recovery's partial sums: the Gram partials of U, then the cluster sums of the
-// passes, in one region.  It is as large as 64 row chunks of r x r FP64 (16 MiB at most) and 256
-// of K x K, less what the r64 x r64 arrays take beyond r x r ones, so that the whole scratch stays
-// within what those would take (nlr_solve_static's fixed scratch also holds it); never under one
-// chunk of either kind.
+// The label recovery's scratch: fixed arrays, and one region for its partial sums, the Gram partials
+// of U and then the cluster sums of the passes.  It shares the union region of the workspace, and
+// the partial sums take all of that region beyond the fixed arrays that they have a use for.
 static size_t lab_fixed_bytes(int32_t r, int32_t K) {
   const size_t r64 = (size_t)round_up(r, 64), r32 = (size_t)round_up(r, 32), k32 = (size_t)round_up(K, 32);
   return 2 * align256(r64 * r64 * 8) + align256(r64 / 64 * 4096 * 8) + align256(2 * kLabJacParts * 8) +
@@ -194,6 +192,12 @@ static size_t lab_fixed_bytes(int32_t r, int32_t K) {
          2 * align256((size_t)K * 8) + 3 * align256((size_t)r * 8) + align256(24) + 2 * align256((size_t)K * 8) +
          align256(64);
 }
+// What the union region holds for the partial sums at least: as much as 64 row chunks of r x r FP64
+// (16 MiB at most) and 256 of K x K, less what the fixed arrays take beyond two r x r, an r x K and a
+// K x K one; never under one chunk of either kind, and up to 64 columns one per 256 rows, 48 at most.
+// (Narrow factors of more rows find what they need in the region: its Theta partials are 4 KiB or
+// more a workgroup of pass A, which has one per 512 rows.  With what the first rule leaves them, one
+// chunk, a pass over 1e6 x 4 took 21 ms; on all chunks 0.06.)
 static size_t lab_part_bytes(int64_t n, int32_t r) {
   const size_t rr = (size_t)r * r * 8, kmax = r < kLabMaxK ? r : kLabMaxK;
   size_t gu = (size_t)((n + 4095) / 4096);
@@ -206,42 +210,47 @@ static size_t lab_part_bytes(int64_t n, int32_t r) {
   size_t bytes = gu * rr + ga * (kmax * kmax + kmax + 1) * 8;
   const size_t fixed = lab_fixed_bytes(r, (int32_t)kmax), plain = 2 * rr + (size_t)r * kmax * 8 + kmax * kmax * 8;
   bytes -= fixed > plain ? (fixed - plain < bytes ? fixed - plain : bytes) : 0;
-  const size_t least = kmax * (size_t)r * 8 + kmax * 4;
-  if (bytes < rr) bytes = rr;
-  return bytes < least ? least : bytes;
+  const size_t chunk = kmax * (size_t)r * 8 + kmax * 4;
+  size_t least = chunk > rr ? chunk : rr;
+  if (r <= 64) {
+    const size_t full = (size_t)((n + 255) / 256);
+    least *= full < 48 ? full : 48;
+  }
+  return align256(bytes < least ? least : bytes);
 }
 
-size_t lab_scratch_bytes(int64_t n, int32_t r, int32_t K) {
-  return lab_fixed_bytes(r, K) + align256(lab_part_bytes(n, r));
-}
+size_t lab_scratch_bytes(int64_t n, int32_t r, int32_t K) { return lab_fixed_bytes(r, K) + lab_part_bytes(n, r); }
 
-LabScratch carve_lab_scratch(int64_t n, int32_t r, int32_t K, char* base) {
+LabScratch carve_lab_scratch(int64_t n, int32_t r, int32_t K, char* base, size_t region) {
   LabScratch L;
   size_t off = 0;
   auto take = [&](size_t bytes) -> char* {
-    char* p = base + off;
+    char* p = base ? base + off : nullptr;
     off += align256(bytes);
     return p;
   };
-  const size_t bytes = lab_part_bytes(n, r), rr = (size_t)r * r * 8;
-  const int32_t kmax = r < kLabMaxK ? r : kLabMaxK;
-  // Gram chunks: at most 256 rows' worth each, four workgroups a compute unit over all block
-  // pairs (as the initialisation's), within the region
+  const size_t rr = (size_t)r * r * 8;
+  const size_t bytes = region - lab_fixed_bytes(r, K);  // for the partial sums
+  // Gram chunks: at least 256 rows each, four workgroups a compute unit over all block pairs (as
+  // the initialisation's), within the region
   const int64_t nbk = (r + 63) / 64;
   int64_t gu = 1024 / (nbk * (nbk + 1) / 2);
   if (gu > 256) gu = 256;
   if (gu > (n + 255) / 256) gu = (n + 255) / 256;
   if (gu > (int64_t)(bytes / rr)) gu = (int64_t)(bytes / rr);
   L.GU = (int32_t)(gu < 1 ? 1 : gu);
-  // sum chunks: two workgroups a compute unit over the 64-column groups (their 64 KiB of LDS)
+  // sum chunks: two workgroups a compute unit over the 64-column groups (their 64 KiB of LDS), at
+  // least 512 rows each (with 256, the centroids' sums over the chunks of 1e5 rows take 2 us longer
+  // and the chunks no less)
   int64_t w = 512 / nbk;
-  const size_t chunk = (size_t)kmax * r * 8 + (size_t)kmax * 4;
-  if (w > (n + 255) / 256) w = (n + 255) / 256;
+  const size_t chunk = (size_t)K * r * 8 + (size_t)K * 4;
+  if (w > (n + 511) / 512) w = (n + 511) / 512;
   if (w > (int64_t)(bytes / chunk)) w = (int64_t)(bytes / chunk);
   L.W = (int32_t)(w < 1 ? 1 : w);
+  const size_t used_g = (size_t)L.GU * rr, used_s = (size_t)L.W * chunk;
   L.r64 = round_up(r, 64);
   const size_t r64 = (size_t)L.r64, r32 = (size_t)round_up(r, 32), k32 = (size_t)round_up(K, 32);
-  char* part = take(bytes);
+  char* part = take(used_g > used_s ? used_g : used_s);
   L.gpart = reinterpret_cast<double*>(part);
   L.spart = reinterpret_cast<long long*>(part);
   L.cpart = reinterpret_cast<int32_t*>(part + (size_t)L.W * K * r * 8);
@@ -323,6 +332,7 @@ size_t carve_workspace(const Geometry& g, char* base, Bufs* out) {
   size_t ubytes = u_iter > u_init ? u_iter : u_init;
   if (u_lab > ubytes) ubytes = u_lab;
   char* ub = take(ubytes);
+  b.union_bytes = ubytes;
   b.theta_part = reinterpret_cast<float*>(ub);
   if (base) {
     size_t o = 0;
@@ -970,7 +980,7 @@ nlr_status nlr_labels_spectral(nlr_ctx* c, int32_t K, const int64_t* seed_rows, 
     if (seed_rows[k] < 0 || seed_rows[k] >= c->g.n) return NLR_EINVAL;
   if (c->failed) return NLR_ESTATE;
   const Geometry& g = c->g;
-  LabScratch L = carve_lab_scratch(g.n, g.r, K, reinterpret_cast<char*>(c->b.theta_part));
+  LabScratch L = carve_lab_scratch(g.n, g.r, K, reinterpret_cast<char*>(c->b.theta_part), c->b.union_bytes);
   int32_t flags[4] = {0, 0, 0, 0};  // degenerate, done, passes, Jacobi converged
   auto read_flags = [&]() {
     return hipMemcpyAsync(flags, L.flag, sizeof(flags), hipMemcpyDeviceToHost, c->stream) == hipSuccess &&

@@ -119,6 +119,7 @@ struct Bufs {
   float* p;            // r32
   float* s;            // r32
   float* theta_part;   // rows of theta_cols floats (GA, GB or PS rows)
+  size_t union_bytes;  // bytes of the region it starts, which the init and the label recovery use too
   double* a_part;      // GA x (4 + r32): ||q||^2, ytilde^T q, -, -, s partials
   double* th2_part;    // RT
   double* b_part;      // GB x (4 + r32): a, b, h, -, column sums
@@ -182,7 +183,8 @@ struct LabScratch {
   int32_t* flag;       // [0] degenerate spectrum, [1] iteration done, [2] passes, [3] Jacobi converged
 };
 size_t lab_scratch_bytes(int64_t n, int32_t r, int32_t K);
-LabScratch carve_lab_scratch(int64_t n, int32_t r, int32_t K, char* base);
+// region: bytes at base (lab_scratch_bytes or more)
+LabScratch carve_lab_scratch(int64_t n, int32_t r, int32_t K, char* base, size_t region);
 
 // aligned16: X and U start on 16-byte boundaries (enables the vector-load kernels)
 // split: split-fp16 products requested (NLR_INIT_SPLIT_F16)
