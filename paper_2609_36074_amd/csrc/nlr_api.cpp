@@ -388,6 +388,7 @@ struct nlr_ctx {
   bool t_host_valid;
   DevCtl* host_ctl;   // mirror of the control block, pinned except for the allocation-free entry point
   nlr_iter_stats* host_rec;  // the latest record beside it (pinned mirror only)
+  bool mirror_out;    // a launch that writes the pinned mirror has not been waited for yet
   // profiling
   bool prof;
   int prof_level;     // 1: every launch; 2: the row and pass kernels only
@@ -624,10 +625,15 @@ static nlr_status enqueue_steady(nlr_ctx* c, int nb, bool lean) {
   return NLR_OK;
 }
 
-static nlr_status enqueue_finish(nlr_ctx* c) {
+// wait: the caller reads the outcome with read_finish.  Only then does the control write the pinned
+// mirror: a call that does not wait leaves nothing behind that writes the context's host memory.
+static nlr_status enqueue_finish(nlr_ctx* c, bool wait) {
   const StepArgs a = make_step_args(c, c->pending ? 1 : 0);
-  LAUNCH(KK_FINISH, launch_pass_a(c->g, c->b, a, true, c->stream));
-  LAUNCH(KK_CTL_FINISH, launch_ctl_a(c->g, c->b, a, c->g.a_rows ? c->g.GA : c->g.GAF, true, c->stream));
+  Bufs b = c->b;
+  if (!wait) b.mirror = nullptr;
+  LAUNCH(KK_FINISH, launch_pass_a(c->g, b, a, true, c->stream));
+  c->mirror_out = c->mirror_out || b.mirror;
+  LAUNCH(KK_CTL_FINISH, launch_ctl_a(c->g, b, a, c->g.a_rows ? c->g.GA : c->g.GAF, true, c->stream));
   c->pending = false;
   return NLR_OK;
 }
@@ -647,6 +653,7 @@ static nlr_status read_ctl(nlr_ctx* c) {
 static nlr_status read_finish(nlr_ctx* c) {
   if (!c->b.mirror) return read_ctl(c);
   if (hipStreamSynchronize(c->stream) != hipSuccess) return hip_fail(c);
+  c->mirror_out = false;
   c->t_host = c->host_ctl->t_done;
   c->t_host_valid = true;
   return NLR_OK;
@@ -736,6 +743,7 @@ static nlr_status init_ctx(nlr_ctx* c, const Geometry& g0, float* X, int32_t K, 
   c->prm = *params;
   c->pending = false;
   c->gram_valid = false;
+  c->mirror_out = false;
   c->failed = false;
   c->breakdown = false;
   c->range_error = false;
@@ -818,7 +826,7 @@ static nlr_status run_iterations(nlr_ctx* c, int32_t T, int32_t* iters_done, nlr
     if (s != NLR_OK) return s;
     k += nb;
   }
-  nlr_status s = enqueue_finish(c);
+  nlr_status s = enqueue_finish(c, true);
   if (s != NLR_OK) return s;
   if (read_finish(c) != NLR_OK) return NLR_EHIP;
   if (prof_collect(c) != hipSuccess) return hip_fail(c);
@@ -939,7 +947,7 @@ nlr_status nlr_step(nlr_ctx* c, nlr_iter_stats* stats) {
   // the iteration counter is known, or bounded by the steps enqueued since it was
   nlr_status s = enqueue_iteration(c, true, c->t_host < (int64_t)c->prm.T_min);
   if (s != NLR_OK) return s;
-  s = enqueue_finish(c);
+  s = enqueue_finish(c, stats != nullptr);
   if (s != NLR_OK) return s;
   c->t_host_valid = false;
   ++c->t_host;
@@ -1116,6 +1124,8 @@ nlr_status nlr_kernel_times(nlr_ctx* c, const char** names, double* total_ms, in
 
 void nlr_destroy(nlr_ctx* c) {
   if (!c) return;
+  // (a call that failed before its wait may have left a write into host_ctl behind)
+  if (c->mirror_out) (void)hipStreamSynchronize(c->stream);
   drop_graphs(c);
   if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
   for (auto e : c->ev_pool) (void)hipEventDestroy(e);
