@@ -13,6 +13,16 @@ __device__ __forceinline__ bool halted(const DevCtl* ctl) {
   return (ctl->stop | ctl->breakdown) != 0;
 }
 
+// The same for a whole workgroup, for kernels whose workgroup 0 sets breakdown at its end: the waves
+// of a workgroup that starts late would each see it set or not, and those that go on would meet the
+// barriers, and the sums in LDS, without the others.
+__device__ __forceinline__ bool halted_workgroup(const DevCtl* ctl) {
+  __shared__ int off;
+  if (threadIdx.x == 0) off = ctl->stop | ctl->breakdown;
+  __syncthreads();
+  return off != 0;
+}
+
 // Whether the stopping rule of the previous iteration (Section 4.3) can still fire
 // at this one: its movement is below min(eps_d, eps_c) and t >= T_min; only the
 // residual rho of the current factor is then missing, which the row work computes.

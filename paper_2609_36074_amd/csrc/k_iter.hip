@@ -1485,11 +1485,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
 // Control after pass B (one workgroup): Algorithm 2 steps (d)-(f).
 // ---------------------------------------------------------------------------
 // Workgroup b writes p for its columns (each forms c from the same sums), workgroup 0 the rest.
-// (A breakdown, set by workgroup 0, may keep another from its columns, which are then not used.)
+// (A breakdown, set by workgroup 0, may keep another workgroup from its columns; none are written
+// on a breakdown anyway.)
 // defer: as k_ctl_a.
 __global__ __launch_bounds__(kThreads) void k_ctl_b(Geometry g, Bufs B, StepArgs S, int defer) {
   DevCtl* ctl = B.ctl;
-  if (halted(ctl)) return;
+  if (halted_workgroup(ctl)) return;
   __shared__ double red[kRedDoubles];
   const int tid = threadIdx.x, blk = blockIdx.x;
   const int C = 4 + g.r32;
@@ -1558,7 +1559,7 @@ __global__ __launch_bounds__(kThreads) void k_ctl_b(Geometry g, Bufs B, StepArgs
 // Workgroup b writes p, P and W^T ytilde for its columns, workgroup 0 the rest, as k_ctl_b.
 __global__ __launch_bounds__(kThreads) void k_ctl_one(Geometry g, Bufs B, StepArgs S) {
   DevCtl* ctl = B.ctl;
-  if (halted(ctl)) return;
+  if (halted_workgroup(ctl)) return;
   __shared__ double red[kRedDoubles];
   const int tid = threadIdx.x, blk = blockIdx.x;
   const int C = 4 + g.r32;

@@ -753,11 +753,10 @@ __global__ __launch_bounds__(kThreads) void k_lab_sums(Geometry g, const float* 
 // the lead's new centroid instead of one, and passes to the next of the group when that has left.
 __global__ __launch_bounds__(kLabUpd) void k_lab_centroid(Geometry g, const float* __restrict__ U, LabScratch L, int K,
                                                           int T, int seed) {
-  if (L.flag[kFlagDegenerate] | L.flag[kFlagDone]) return;
   __shared__ double sums[kMaxR], cent[kLabMaxK], part[kLabUpd];
   __shared__ long long ipart[kLabUpd];
   __shared__ long long count;
-  __shared__ int eq;
+  __shared__ int eq, off;
   const int tid = threadIdx.x, r = g.r, k = blockIdx.x;
   const int r32 = (r + 31) & ~31;
   // M_ck scaled and split into the assignment's operand order: [step of 16 columns][block of 32
@@ -773,12 +772,16 @@ __global__ __launch_bounds__(kLabUpd) void k_lab_centroid(Geometry g, const floa
     for (int c = tid; c < r32; c += kLabUpd) put(c, 0.f);
     return;
   }
-  const int src = seed ? k : L.lead[k];  // the cluster whose centroid is formed
+  // Workgroup 0 ends the iteration at its end, so a workgroup that starts late may leave here (its
+  // centroid is not read again) -- as one: its waves go by what thread 0 read.
   if (tid == 0) {
     count = seed;
     eq = k;
+    off = L.flag[kFlagDegenerate] | L.flag[kFlagDone];
   }
   __syncthreads();
+  if (off) return;
+  const int src = seed ? k : L.lead[k];  // the cluster whose centroid is formed
   if (seed) {
     const float* u = U + L.seeds[k] * r;
     for (int c = tid; c < r; c += kLabUpd) sums[c] = (double)u[c];

@@ -374,6 +374,21 @@ def test_breakdown_and_sticky_state():
     assert e.value.status == nlr.NLR_ESTATE
 
 
+@pytest.mark.parametrize("n,d,r,flags", [(200, 4, 4, 8), (300, 4, 40, 0), (900, 4, 300, 0), (640, 5, 13, 0)])
+def test_breakdown_keeps_p(n, d, r, flags):
+    """A breakdown writes no column of p, whichever workgroup of the control sees it first."""
+    from paper_2609_36074_amd import nlr
+    K = 3
+    X, _, _ = gaussian_mixture(n, d, 2, 9.0, seed=10)
+    ctx = make_ctx(X, np.ones((n, r)), K, 1.0 / (2 * 1.0 * (K - 1)) * 1.5, 1.0, flags=flags)
+    p0 = ctx.inspect("p")
+    assert (p0 > 0).all()
+    with pytest.raises(nlr.NlrError) as e:
+        ctx.step()
+    assert e.value.status == nlr.NLR_EBREAKDOWN
+    assert np.array_equal(ctx.inspect("p"), p0)
+
+
 def test_degenerate_and_nonpositive_start():
     from paper_2609_36074_amd import nlr
     X = np.ones((100, 6), dtype=np.float32) * 3.0
