@@ -746,8 +746,17 @@ __device__ __forceinline__ CtlSums ctl_sums_un(const double* __restrict__ pa, co
 #pragma unroll
     for (int i = 0; i < 4; ++i) s[2 + i][k] = HB ? pb[o + i] : 0.0;
   }
-  if (th2)
-    for (int k = tid; k < RT; k += NT) t2 += th2[k];
+  if (th2 && RT <= NT) {
+    if (tid < RT) t2 = th2[tid];
+  } else if (th2) {
+    for (int k0 = tid; k0 < RT; k0 += 8 * NT) {  // eight loads in flight, added in order
+      double v[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[i] = th2[k0 + NT * i < RT ? k0 + NT * i : k0];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) t2 += k0 + NT * i < RT ? v[i] : 0.0;
+    }
+  }
   __builtin_amdgcn_sched_barrier(0);
   auto col = [&](const double (&v)[UN], double* r) {
     double t = 0.0;
@@ -923,22 +932,41 @@ __device__ __forceinline__ float s_from_gram(const Bufs& B, int r32, int k, doub
 // (both only need pass A's partials); Theta is then formed whatever the control decides, since a
 // stop leaves its partials as they were.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kRedThreads) void k_theta_sum(Geometry g, Bufs B, StepArgs S, int64_t rows, int scaled,
-                                                           float gamma_f, int64_t ctl_rows) {
-  __shared__ double red[kRedThreads];  // (also the control's: kRedDoubles)
+// WIDE: 256 entries a workgroup, one a thread (in the same order), from kThetaWide blocks of 64 on:
+// two waves a SIMD without a second thread an entry.  In sixteens the workgroups come in many rounds
+// there, with more masked loads than rows: 768 x 256 (42 partial rows) 20.5 us, wide 11.8; 4096 x 448
+// (16 rows) 140 and 31; below, 224 x 320 (128 rows) takes 13 us in sixteens.
+// After a stop of an earlier iteration (2, see k_ctl_b) there is nothing to do: formed all the same, 38
+// iterations enqueued past a stop at 60,000 x 768 x 256 took 0.55 ms more.
+constexpr int kThetaWide = 2048;
+template <bool WIDE>
+__global__ __launch_bounds__(WIDE ? kThreads : kRedThreads) void k_theta_sum(Geometry g, Bufs B, StepArgs S,
+                                                                             int64_t rows, int scaled, float gamma_f,
+                                                                             int64_t ctl_rows) {
+  constexpr int NT = WIDE ? kThreads : kRedThreads;
+  __shared__ double red[WIDE ? kRedDoubles : kRedThreads];  // (also the control's: kRedDoubles)
+  const int tb = WIDE ? g.RT >> 2 : g.RT;  // workgroups of Theta
   if (ctl_rows > 0) {
-    if ((int)blockIdx.x >= g.RT) {
-      ctl_a_work<kRedThreads>(g, B, S, (int)blockIdx.x - g.RT, 0, ctl_rows, 1, red);
+    if (B.ctl->breakdown != 0 || B.ctl->stop == 2) return;
+    if ((int)blockIdx.x >= tb) {
+      ctl_a_work<NT>(g, B, S, (int)blockIdx.x - tb, 0, ctl_rows, 1, red);
       return;
     }
   } else if (halted(B.ctl)) {
     return;
   }
   const int tid = threadIdx.x, r32 = g.r32;
-  const bool gram = (int)blockIdx.x >= g.RT;
-  const int64_t e = ((int64_t)blockIdx.x - (gram ? g.RT : 0)) * 64 + (tid & 63);
-  double sum = part_sum64(B.theta_part, rows, g.theta_cols, e + (gram ? (int64_t)g.d32 * r32 : 0), red);
-  if (tid >= 64) return;
+  const bool gram = !WIDE && (int)blockIdx.x >= g.RT;
+  int64_t e;
+  double sum;
+  if constexpr (WIDE) {
+    e = (int64_t)blockIdx.x * kThreads + tid;
+    sum = part_sum16(B.theta_part, rows, g.theta_cols, e);
+  } else {
+    e = ((int64_t)blockIdx.x - (gram ? g.RT : 0)) * 64 + (tid & 63);
+    sum = part_sum64(B.theta_part, rows, g.theta_cols, e + (gram ? (int64_t)g.d32 * r32 : 0), red);
+    if (tid >= 64) return;
+  }
   if (gram) {
     const int k = (int)e / r32, l = (int)e - k * r32;  // r32 = 32 or 64 entries of a row: lanes of this wave
     double gp = sum * B.gram_vec[l];
@@ -966,9 +994,10 @@ __global__ __launch_bounds__(kRedThreads) void k_theta_sum(Geometry g, Bufs B, S
     t2 += shfl_xor_d(t2, k);
     m = fmaxf(m, shfl_xor_f(m, k));
   }
-  if (tid == 0) {
-    B.th2_part[blockIdx.x] = t2;
-    B.thmax_part[blockIdx.x] = m;  // (the panel form scales its split Theta operand by it)
+  if ((tid & 63) == 0) {
+    const int64_t w = WIDE ? 4 * (int64_t)blockIdx.x + (tid >> 6) : blockIdx.x;
+    B.th2_part[w] = t2;
+    B.thmax_part[w] = m;  // (the panel form scales its split Theta operand by it)
   }
 }
 
@@ -1487,10 +1516,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
 // Workgroup b writes p for its columns (each forms c from the same sums), workgroup 0 the rest.
 // (A breakdown, set by workgroup 0, may keep another workgroup from its columns; none are written
 // on a breakdown anyway.)
-// defer: as k_ctl_a.
+// defer: as ctl_a_work.  A stop that this iteration's control after pass A set is marked 2 here: the
+// Theta sums of later iterations, which share their launch with that control, go by it.
 __global__ __launch_bounds__(kThreads) void k_ctl_b(Geometry g, Bufs B, StepArgs S, int defer) {
   DevCtl* ctl = B.ctl;
-  if (halted_workgroup(ctl)) return;
+  if (halted_workgroup(ctl)) {
+    if (blockIdx.x == 0 && threadIdx.x == 0 && ctl->stop == 1) ctl->stop = 2;
+    return;
+  }
   __shared__ double red[kRedDoubles];
   const int tid = threadIdx.x, blk = blockIdx.x;
   const int C = 4 + g.r32;
@@ -1909,8 +1942,13 @@ hipError_t launch_theta_sum(const Geometry& g, const Bufs& b, const StepArgs& a,
   // one-pass iteration (partials of its pass): workgroups after the RT of Theta form (W^T W) P; two-pass
   // form: they do the control after pass A
   const int more = (g.fused8 && scaled) ? (g.r32 * g.r32) / 64 : (with_ctl_a ? ctl_blocks(g) : 0);
-  hipLaunchKernelGGL(k_theta_sum, dim3(g.RT + more), dim3(kRedThreads), 0, st, g, b, a, rows, scaled ? 1 : 0, gamma_f,
-                     with_ctl_a ? (int64_t)(g.a_rows ? g.GA : g.GAF) : (int64_t)0);
+  const int64_t ctl_rows = with_ctl_a ? (int64_t)(g.a_rows ? g.GA : g.GAF) : 0;
+  if (g.RT >= kThetaWide)
+    hipLaunchKernelGGL(k_theta_sum<true>, dim3(g.RT / 4 + more), dim3(kThreads), 0, st, g, b, a, rows, scaled ? 1 : 0,
+                       gamma_f, ctl_rows);
+  else
+    hipLaunchKernelGGL(k_theta_sum<false>, dim3(g.RT + more), dim3(kRedThreads), 0, st, g, b, a, rows, scaled ? 1 : 0,
+                       gamma_f, ctl_rows);
   return hipGetLastError();
 }
 

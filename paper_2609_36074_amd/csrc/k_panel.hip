@@ -516,7 +516,13 @@ __global__ __launch_bounds__(kThreads) void k_theta_split_panel(Geometry g, Bufs
   if (halted(B.ctl)) return;
   __shared__ float red[4];
   float m = 0.f;
-  for (int k = threadIdx.x; k < g.RT; k += kThreads) m = fmaxf(m, B.thmax_part[k]);
+  for (int k0 = threadIdx.x; k0 < g.RT; k0 += 16 * kThreads) {  // sixteen loads in flight
+    float v[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = B.thmax_part[k0 + kThreads * i < g.RT ? k0 + kThreads * i : k0];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) m = fmaxf(m, v[i]);
+  }
   for (int k = 32; k >= 1; k >>= 1) m = fmaxf(m, shfl_xor_f(m, k));
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
   __syncthreads();

@@ -28,7 +28,7 @@ constexpr int32_t kRangeError = 2;
 // Device control block.  Written only by single-workgroup control kernels and
 // read uniformly by every kernel at entry.
 struct alignas(16) DevCtl {
-  int32_t stop;        // stopping rule fired during the current host call
+  int32_t stop;        // stopping rule fired during the current host call: 1, two-pass forms 2 from the next control on
   int32_t breakdown;   // sticky: kBreakdown (normalisation breakdown) or kRangeError
   int32_t gate;        // dual gate of the latest primal step
   int32_t degenerate;  // init: a = ||X_c||_2 is zero or not finite

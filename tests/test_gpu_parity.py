@@ -267,6 +267,44 @@ def test_two_pass_unaligned_rows(n, d, r, K, shift):
     assert torch.equal(other.U, ctx.U) and torch.equal(other.y, ctx.y)
 
 
+# Theta sums of one entry a thread (131072 entries of the padded Theta or more) with few and with more
+# partial rows than are in flight at once, just below that number, and in the panel form
+@pytest.mark.parametrize("n,d,r,K,flags", [(500, 500, 448, 4, TWO_PASS), (3001, 1030, 128, 6, TWO_PASS),
+                                           (2100, 990, 128, 6, TWO_PASS), (700, 300, 430, 4, TWO_PASS),
+                                           (1500, 1032, 128, 8, 8)])
+def test_large_theta(n, d, r, K, flags):
+    log(f"large theta n={n} d={d} r={r} K={K} flags={flags}")
+    X, _, _ = gaussian_mixture(n, d, K, 16.0, seed=n + d)
+    Z = standard_normal_factor(n, r, seed=n + r).astype(np.float64)
+    _, _, traj, obj, bad_gates, one, _, _ = trajectory(X, Z, K, onlr.default_step_size(K), 1.0, 4,
+                                                       one_step_tol=True, flags=flags)
+    log(f"  traj {max(traj):.2e} one {max(one):.2e} obj {max(obj):.2e}")
+    assert max(traj) < U_TOL and max(one) < U_TOL / 10 and max(obj) < OBJ_TOL
+    assert not bad_gates
+
+
+@pytest.mark.parametrize("n,d,r", [(3000, 51, 13), (2000, 200, 40), (1200, 500, 300)])
+def test_two_pass_stop_keeps_theta_and_resumes(n, d, r):
+    """Iterations enqueued after a stop change nothing: Theta stays that of the factor at the stop
+    (fp32 entries, summed in FP64 from fp32 partials: 2^-24 sqrt(n) of the largest), and the context
+    goes on from there like one that was never run past the stop."""
+    K = 4
+    X, _, _ = gaussian_mixture(n, d, K, 16.0, seed=n + d)
+    Z = standard_normal_factor(n, r, seed=n + r).astype(np.float64)
+    ctxs = [make_ctx(X, Z, K, onlr.default_step_size(K), eps_d=1e30, eps_c=1e30, T_min=3, flags=TWO_PASS)
+            for _ in range(2)]
+    done = [ctxs[0].run(40)[0], ctxs[1].run(3)[0]]
+    assert done[0] == done[1] == 3
+    U, theta = host(ctxs[0].U), ctxs[0].inspect("theta").astype(np.float64)
+    assert np.array_equal(U, host(ctxs[1].U))
+    ref = host(ctxs[0].X).T @ U
+    assert np.abs(theta - ref).max() <= 2.0 ** -24 * np.sqrt(n) * np.abs(ref).max()
+    for c in ctxs:
+        c.set_params(eps_c=1e-30)
+        c.run(5)
+    assert np.array_equal(host(ctxs[0].U), host(ctxs[1].U)) and np.array_equal(host(ctxs[0].y), host(ctxs[1].y))
+
+
 def test_gmm1m_parity():
     """gmm1m over its configuration's 100 iterations with split products (the bench's
     single-Xhat-pass form) and with fp32 products, from the same start: each iterate against
