@@ -201,25 +201,43 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NBG >=
 
 // ---------------------------------------------------------------------------
 // Row work of pass A where Theta does not fit one wave (its first launch), and the finish pass of
-// those shapes and of the panel form: no LDS staging; each wave streams whole rows of U, lane l
-// holding the columns l + 64 j (CPL = ceil(r / 64) of them), RPI rows at a time.  Per row:
-// u = fl(c_f w), q = u.p - 1 (FP64, summed over the wave by an xor butterfly, so every lane has
+// those shapes and of the panel form: no LDS staging; LPR lanes stream whole rows of U, lane l
+// holding the columns l + LPR j (CPL of them), RPI rows at a time each.  Per row:
+// u = fl(c_f w), q = u.p - 1 (FP64, summed over the row's lanes by an xor butterfly, so every lane has
 // the same bits), the gated dual step (eq. of the stored dual), ybar (stored for pass B above 128
 // columns); then s += ybar u, ||q||^2 and ytilde^T q in FP64.  FINISH: materialises u instead of
 // forming s and ybar.  Grid GAF; workgroup gx takes a contiguous range of rows, its waves every
-// fourth row of it, and writes partial row gx (qq, yq, 0, 0, s).  Bound by the row stream (the
-// finish pass as LDS-staged tiles took 1.94 ms at 1e6 x 300, 2.4 GB).
+// fourth piece of it, and writes partial row gx (qq, yq, 0, 0, s).  Bound by the row stream (the
+// finish pass as LDS-staged tiles took 1.94 ms at 1e6 x 300, 2.4 GB).  Up to 16 and 32 columns a row
+// has 16 or 32 lanes: with a whole wave a row the butterflies of mostly idle lanes bound it (row pass
+// over 1e6 x 5 and 1e6 x 30: 142 us, now 28 and 50; finish pass at 2,911,497 x 12: 0.43 ms).
 // ---------------------------------------------------------------------------
-template <int CPL, bool FINISH>
+// Sum over the LPR lanes of a row, bitwise the same in all of them: v[l] + v[l ^ m], m from LPR / 2 down
+// to 1.  (Below 16, after the step for 2 m the values repeat every 2 m lanes, so a rotation of the DPP
+// row by m brings the same value as l ^ m.)
+template <int LPR>
+__device__ __forceinline__ double lanes_sum_d(double v) {
+  if constexpr (LPR >= 64) v += shfl_xor_d(v, 32);
+  if constexpr (LPR >= 32) v += shfl_xor_d(v, 16);
+  v += dpp_d<0x128>(v);  // row_ror 8, 4, 2, 1
+  v += dpp_d<0x124>(v);
+  v += dpp_d<0x122>(v);
+  v += dpp_d<0x121>(v);
+  return v;
+}
+template <int LPR, int CPL, bool FINISH>
 __global__ __launch_bounds__(kThreads) void k_rows_wide(Geometry g, Bufs B, StepArgs S) {
   // the finish pass runs after a stop (it still materialises U) but not after a breakdown
   if (FINISH ? (B.ctl->breakdown != 0) : halted(B.ctl)) return;
   const bool stopped = FINISH && (B.ctl->stop != 0);
-  constexpr int RPI = 8;  // rows per wave and step
-  __shared__ double sred[4 * 64 * CPL];
+  static_assert(LPR == 64 || CPL == 1, "narrow rows: one column a lane");
+  constexpr int RPI = 8;           // rows per lane and step
+  constexpr int NR = 64 / LPR;     // rows of a wave at a time
+  __shared__ double sred[4 * LPR * CPL];
   __shared__ double dred[kThreads + 8];
   const int tid = threadIdx.x;
-  const int lane = tid & 63;
+  const int lane = tid & (LPR - 1);       // within the row
+  const int grp = (tid & 63) / LPR;       // row of the wave's NR
   const int wave = tid >> 6;
   const int64_t n = g.n;
   const int r = g.r;
@@ -233,7 +251,7 @@ __global__ __launch_bounds__(kThreads) void k_rows_wide(Geometry g, Bufs B, Step
   int colo[CPL];  // column read (0 for the lanes past the last column)
 #pragma unroll
   for (int j = 0; j < CPL; ++j) {
-    const int col = lane + 64 * j;
+    const int col = lane + LPR * j;
     okc[j] = col < r;
     colo[j] = okc[j] ? col : 0;
     pl[j] = okc[j] ? B.p[col] : 0.f;
@@ -245,7 +263,7 @@ __global__ __launch_bounds__(kThreads) void k_rows_wide(Geometry g, Bufs B, Step
 
   const int64_t rb = (int64_t)blockIdx.x * n / gridDim.x;
   const int64_t re = (int64_t)(blockIdx.x + 1) * n / gridDim.x;
-  for (int64_t base = rb + (int64_t)wave * RPI; base < re; base += 4 * RPI) {
+  for (int64_t base = rb + (int64_t)wave * RPI * NR + grp; base - grp < re; base += 4 * RPI * NR) {
     float u[RPI][CPL];
     float yt[RPI];
     // every load reads a valid address (row rb, column 0 in place of those out of range)
@@ -253,7 +271,7 @@ __global__ __launch_bounds__(kThreads) void k_rows_wide(Geometry g, Bufs B, Step
     // loads of the step are issued before any of their values is used
 #pragma unroll
     for (int i = 0; i < RPI; ++i) {
-      const int64_t row = base + i;
+      const int64_t row = base + i * NR;
       const float* src = B.U + (row < re ? row : rb) * r;
 #pragma unroll
       for (int j = 0; j < CPL; ++j) u[i][j] = src[colo[j]];
@@ -262,7 +280,7 @@ __global__ __launch_bounds__(kThreads) void k_rows_wide(Geometry g, Bufs B, Step
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < RPI; ++i) {
-      const bool okr = base + i < re;
+      const bool okr = base + i * NR < re;
 #pragma unroll
       for (int j = 0; j < CPL; ++j) u[i][j] = (okr && okc[j]) ? u[i][j] * cf : 0.f;
       yt[i] = okr ? yt[i] : 0.f;
@@ -275,12 +293,10 @@ __global__ __launch_bounds__(kThreads) void k_rows_wide(Geometry g, Bufs B, Step
       for (int j = 0; j < CPL; ++j) dot[i] += (double)u[i][j] * (double)pl[j];
     }
 #pragma unroll
-    for (int m = 32; m >= 1; m >>= 1)
-#pragma unroll
-      for (int i = 0; i < RPI; ++i) dot[i] += shfl_xor_d(dot[i], m);
+    for (int i = 0; i < RPI; ++i) dot[i] = lanes_sum_d<LPR>(dot[i]);
 #pragma unroll
     for (int i = 0; i < RPI; ++i) {
-      const int64_t row = base + i;
+      const int64_t row = base + i * NR;
       if (row < re) {
         const float q = (float)(dot[i] - 1.0);
         float y = yt[i];
@@ -318,16 +334,19 @@ __global__ __launch_bounds__(kThreads) void k_rows_wide(Geometry g, Bufs B, Step
     for (int c = tid; c < g.r32; c += kThreads) ap[4 + c] = 0.0;
     return;
   }
-  // s: the four waves' sums of a column, added in wave order
+  // s: the rows of a wave, then the four waves' sums of a column, added in wave order
 #pragma unroll
-  for (int j = 0; j < CPL; ++j) sred[(wave * CPL + j) * 64 + lane] = sacc[j];
+  for (int m = LPR; m < 64; m <<= 1) sacc[0] += shfl_xor_d(sacc[0], m);
+  if (grp == 0)
+#pragma unroll
+    for (int j = 0; j < CPL; ++j) sred[(wave * CPL + j) * LPR + lane] = sacc[j];
   __syncthreads();
   for (int c = tid; c < g.r32; c += kThreads) {
     double t = 0.0;
-    if (c < 64 * CPL) {
-      const int j = c >> 6, l = c & 63;
-      t = ((sred[(0 * CPL + j) * 64 + l] + sred[(1 * CPL + j) * 64 + l]) + sred[(2 * CPL + j) * 64 + l]) +
-          sred[(3 * CPL + j) * 64 + l];
+    if (c < LPR * CPL) {
+      const int j = c / LPR, l = c & (LPR - 1);
+      t = ((sred[(0 * CPL + j) * LPR + l] + sred[(1 * CPL + j) * LPR + l]) + sred[(2 * CPL + j) * LPR + l]) +
+          sred[(3 * CPL + j) * LPR + l];
     }
     ap[4 + c] = t;
   }
@@ -1839,14 +1858,22 @@ static hipError_t launch_theta_wide(const Geometry& g, const Bufs& b, hipStream_
 template <bool FINISH>
 static hipError_t launch_rows_wide(const Geometry& g, const Bufs& b, const StepArgs& a, hipStream_t st) {
   const dim3 grid(g.GAF), blk(kThreads);
+  if (g.r <= 16) {
+    hipLaunchKernelGGL((k_rows_wide<16, 1, FINISH>), grid, blk, 0, st, g, b, a);
+    return hipGetLastError();
+  }
+  if (g.r <= 32) {
+    hipLaunchKernelGGL((k_rows_wide<32, 1, FINISH>), grid, blk, 0, st, g, b, a);
+    return hipGetLastError();
+  }
   switch ((g.r + 63) / 64) {
-    case 1: hipLaunchKernelGGL((k_rows_wide<1, FINISH>), grid, blk, 0, st, g, b, a); break;
-    case 2: hipLaunchKernelGGL((k_rows_wide<2, FINISH>), grid, blk, 0, st, g, b, a); break;
-    case 3: hipLaunchKernelGGL((k_rows_wide<3, FINISH>), grid, blk, 0, st, g, b, a); break;
-    case 4: hipLaunchKernelGGL((k_rows_wide<4, FINISH>), grid, blk, 0, st, g, b, a); break;
-    case 5: hipLaunchKernelGGL((k_rows_wide<5, FINISH>), grid, blk, 0, st, g, b, a); break;
-    case 6: hipLaunchKernelGGL((k_rows_wide<6, FINISH>), grid, blk, 0, st, g, b, a); break;
-    case 7: hipLaunchKernelGGL((k_rows_wide<7, FINISH>), grid, blk, 0, st, g, b, a); break;
+    case 1: hipLaunchKernelGGL((k_rows_wide<64, 1, FINISH>), grid, blk, 0, st, g, b, a); break;
+    case 2: hipLaunchKernelGGL((k_rows_wide<64, 2, FINISH>), grid, blk, 0, st, g, b, a); break;
+    case 3: hipLaunchKernelGGL((k_rows_wide<64, 3, FINISH>), grid, blk, 0, st, g, b, a); break;
+    case 4: hipLaunchKernelGGL((k_rows_wide<64, 4, FINISH>), grid, blk, 0, st, g, b, a); break;
+    case 5: hipLaunchKernelGGL((k_rows_wide<64, 5, FINISH>), grid, blk, 0, st, g, b, a); break;
+    case 6: hipLaunchKernelGGL((k_rows_wide<64, 6, FINISH>), grid, blk, 0, st, g, b, a); break;
+    case 7: hipLaunchKernelGGL((k_rows_wide<64, 7, FINISH>), grid, blk, 0, st, g, b, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

@@ -283,6 +283,28 @@ def test_large_theta(n, d, r, K, flags):
     assert not bad_gates
 
 
+# Row work of 16 or 32 lanes a row (two-pass and panel forms beyond the register-resident shapes): the
+# edges of the lane groups, ragged last steps, fewer rows than workgroups x rows of a step
+@pytest.mark.parametrize("n,d,r,flags", [(1037, 136, 1, 0), (901, 131, 2, 0), (777, 200, 5, 0), (2049, 160, 12, 0),
+                                         (1500, 333, 16, 0), (1001, 160, 17, 0), (640, 136, 24, 0),
+                                         (3003, 131, 31, 0), (515, 264, 32, 0), (33, 136, 16, 0),
+                                         (4001, 136, 12, 8), (1999, 336, 16, 8), (2500, 264, 20, 8),
+                                         (70, 136, 32, 8)])
+def test_narrow_rows(n, d, r, flags):
+    log(f"narrow rows n={n} d={d} r={r} flags={flags}")
+    K = min(r, 3)
+    X, _, _ = gaussian_mixture(n, d, max(K, 2), 16.0, seed=n * 3 + d)
+    Z = standard_normal_factor(n, r, seed=n + 2 * r).astype(np.float64)
+    alpha = onlr.default_step_size(K)
+    _, _, traj, obj, bad_gates, one, U_gpu, _ = trajectory(X, Z, K, alpha, 1.0, 6, one_step_tol=True, flags=flags)
+    log(f"  traj {max(traj):.2e} one {max(one):.2e} obj {max(obj):.2e}")
+    assert max(traj) < U_TOL and max(one) < U_TOL / 10 and max(obj) < OBJ_TOL
+    assert not bad_gates
+    ctx = make_ctx(X, Z, K, alpha, 1.0, T_min=6, flags=flags)
+    ctx.run(6)
+    assert np.array_equal(host(ctx.U), U_gpu[-1])
+
+
 @pytest.mark.parametrize("n,d,r", [(3000, 51, 13), (2000, 200, 40), (1200, 500, 300)])
 def test_two_pass_stop_keeps_theta_and_resumes(n, d, r):
     """Iterations enqueued after a stop change nothing: Theta stays that of the factor at the stop
