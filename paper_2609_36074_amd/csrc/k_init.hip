@@ -242,7 +242,7 @@ template <int D>
 __global__ __launch_bounds__(1024) void k_power_small(Geometry g, Bufs B) {
   constexpr int LD = D + 2, NT = D / 16;
   __shared__ double C[D * LD], M[D * LD];
-  __shared__ double v[D], y[D], part[16];
+  __shared__ double v[D], y[D];
   __shared__ double sc;
   __shared__ int j0;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, d = g.d;

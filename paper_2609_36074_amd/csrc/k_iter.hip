@@ -900,10 +900,9 @@ __device__ __forceinline__ void ctl_a_work(const Geometry& g, const Bufs& B, con
   }
 }
 
-__global__ __launch_bounds__(kThreads) void k_ctl_a(Geometry g, Bufs B, StepArgs S, int finish, int64_t rows,
-                                                       int defer) {
+__global__ __launch_bounds__(kThreads) void k_ctl_a(Geometry g, Bufs B, StepArgs S, int finish, int64_t rows) {
   __shared__ double red[kRedDoubles];
-  ctl_a_work<kThreads>(g, B, S, blockIdx.x, finish, rows, defer, red);
+  ctl_a_work<kThreads>(g, B, S, blockIdx.x, finish, rows, 0, red);
   if (finish && B.mirror) {  // (one workgroup)
     __syncthreads();
     const uint32_t* src = reinterpret_cast<const uint32_t*>(B.ctl);
@@ -1834,11 +1833,15 @@ static hipError_t theta_wide_un(const Geometry& g, const Bufs& b, hipStream_t st
                               : theta_wide_launch<MBG, NBG, true>(g, b, st);
 }
 
+// (one or two blocks of columns come with more than 128 features only: narrower shapes with up to 64
+// columns are register-resident)
 template <int MBG>
 static hipError_t theta_wide_nbg(const Geometry& g, const Bufs& b, hipStream_t st) {
+  if constexpr (MBG == 4) {
+    if (g.NBG == 1) return theta_wide_un<MBG, 1>(g, b, st);
+    if (g.NBG == 2) return theta_wide_un<MBG, 2>(g, b, st);
+  }
   switch (g.NBG) {
-    case 1: return theta_wide_un<MBG, 1>(g, b, st);
-    case 2: return theta_wide_un<MBG, 2>(g, b, st);
     case 4: return theta_wide_un<MBG, 4>(g, b, st);
     case 5: return theta_wide_un<MBG, 5>(g, b, st);
     case 7: return theta_wide_un<MBG, 7>(g, b, st);
@@ -1879,21 +1882,19 @@ static hipError_t launch_rows_wide(const Geometry& g, const Bufs& b, const StepA
   return hipGetLastError();
 }
 
+// (the row pass belongs to the single-pass form, whose rows are whole aligned pieces)
 template <int FV, int NGF, int CV, bool UN>
 static hipError_t pass_a_rows_mode(const Geometry& g, const Bufs& b, const StepArgs& a, int mode, hipStream_t st) {
+  const dim3 grid(g.GA), blk(kThreads);
   if (mode == kPassFinish)
-    hipLaunchKernelGGL((k_pass_a_rows<FV, NGF, CV, kPassFinish, UN>), dim3(g.GA), dim3(kThreads), 0, st, g, b, a);
-  else if (mode == kPassRows)
-    hipLaunchKernelGGL((k_pass_a_rows<FV, NGF, CV, kPassRows, UN>), dim3(g.GA), dim3(kThreads), 0, st, g, b, a);
+    hipLaunchKernelGGL((k_pass_a_rows<FV, NGF, CV, kPassFinish, UN>), grid, blk, 0, st, g, b, a);
+  else if (mode == kPassIter)
+    hipLaunchKernelGGL((k_pass_a_rows<FV, NGF, CV, kPassIter, UN>), grid, blk, 0, st, g, b, a);
+  else if constexpr (!UN)
+    hipLaunchKernelGGL((k_pass_a_rows<FV, NGF, CV, kPassRows, UN>), grid, blk, 0, st, g, b, a);
   else
-    hipLaunchKernelGGL((k_pass_a_rows<FV, NGF, CV, kPassIter, UN>), dim3(g.GA), dim3(kThreads), 0, st, g, b, a);
+    return hipErrorInvalidValue;
   return hipGetLastError();
-}
-
-template <int FV, int NGF, int CV>
-static hipError_t pass_a_rows_launch(const Geometry& g, const Bufs& b, const StepArgs& a, int mode,
-                                     hipStream_t st) {
-  return pass_a_rows_mode<FV, NGF, CV, false>(g, b, a, mode, st);
 }
 
 // rows that are not whole aligned pieces: the fewest pieces of up to four features a lane
@@ -1930,24 +1931,24 @@ static hipError_t pass_a_rows_dispatch(const Geometry& g, const Bufs& b, const S
   if (g.a_un) return pass_a_un_dispatch(g, b, a, finish, st);
   const int key = g.a_fv * 100 + g.a_ngf * 10 + g.a_cv;
   switch (key) {
-    case 111: return pass_a_rows_launch<1, 1, 1>(g, b, a, finish, st);
-    case 112: return pass_a_rows_launch<1, 1, 2>(g, b, a, finish, st);
-    case 114: return pass_a_rows_launch<1, 1, 4>(g, b, a, finish, st);
-    case 211: return pass_a_rows_launch<2, 1, 1>(g, b, a, finish, st);
-    case 212: return pass_a_rows_launch<2, 1, 2>(g, b, a, finish, st);
-    case 214: return pass_a_rows_launch<2, 1, 4>(g, b, a, finish, st);
-    case 221: return pass_a_rows_launch<2, 2, 1>(g, b, a, finish, st);
-    case 222: return pass_a_rows_launch<2, 2, 2>(g, b, a, finish, st);
-    case 224: return pass_a_rows_launch<2, 2, 4>(g, b, a, finish, st);
-    case 241: return pass_a_rows_launch<2, 4, 1>(g, b, a, finish, st);
-    case 242: return pass_a_rows_launch<2, 4, 2>(g, b, a, finish, st);
-    case 244: return pass_a_rows_launch<2, 4, 4>(g, b, a, finish, st);
-    case 411: return pass_a_rows_launch<4, 1, 1>(g, b, a, finish, st);
-    case 412: return pass_a_rows_launch<4, 1, 2>(g, b, a, finish, st);
-    case 414: return pass_a_rows_launch<4, 1, 4>(g, b, a, finish, st);
-    case 421: return pass_a_rows_launch<4, 2, 1>(g, b, a, finish, st);
-    case 422: return pass_a_rows_launch<4, 2, 2>(g, b, a, finish, st);
-    case 424: return pass_a_rows_launch<4, 2, 4>(g, b, a, finish, st);
+    case 111: return pass_a_rows_mode<1, 1, 1, false>(g, b, a, finish, st);
+    case 112: return pass_a_rows_mode<1, 1, 2, false>(g, b, a, finish, st);
+    case 114: return pass_a_rows_mode<1, 1, 4, false>(g, b, a, finish, st);
+    case 211: return pass_a_rows_mode<2, 1, 1, false>(g, b, a, finish, st);
+    case 212: return pass_a_rows_mode<2, 1, 2, false>(g, b, a, finish, st);
+    case 214: return pass_a_rows_mode<2, 1, 4, false>(g, b, a, finish, st);
+    case 221: return pass_a_rows_mode<2, 2, 1, false>(g, b, a, finish, st);
+    case 222: return pass_a_rows_mode<2, 2, 2, false>(g, b, a, finish, st);
+    case 224: return pass_a_rows_mode<2, 2, 4, false>(g, b, a, finish, st);
+    case 241: return pass_a_rows_mode<2, 4, 1, false>(g, b, a, finish, st);
+    case 242: return pass_a_rows_mode<2, 4, 2, false>(g, b, a, finish, st);
+    case 244: return pass_a_rows_mode<2, 4, 4, false>(g, b, a, finish, st);
+    case 411: return pass_a_rows_mode<4, 1, 1, false>(g, b, a, finish, st);
+    case 412: return pass_a_rows_mode<4, 1, 2, false>(g, b, a, finish, st);
+    case 414: return pass_a_rows_mode<4, 1, 4, false>(g, b, a, finish, st);
+    case 421: return pass_a_rows_mode<4, 2, 1, false>(g, b, a, finish, st);
+    case 422: return pass_a_rows_mode<4, 2, 2, false>(g, b, a, finish, st);
+    case 424: return pass_a_rows_mode<4, 2, 4, false>(g, b, a, finish, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -1981,8 +1982,7 @@ hipError_t launch_theta_sum(const Geometry& g, const Bufs& b, const StepArgs& a,
 
 hipError_t launch_ctl_a(const Geometry& g, const Bufs& b, const StepArgs& a, int64_t rows, bool finish,
                         hipStream_t st) {
-  hipLaunchKernelGGL(k_ctl_a, dim3(finish ? 1 : ctl_blocks(g)), dim3(kThreads), 0, st, g, b, a, finish ? 1 : 0, rows,
-                     0);
+  hipLaunchKernelGGL(k_ctl_a, dim3(finish ? 1 : ctl_blocks(g)), dim3(kThreads), 0, st, g, b, a, finish ? 1 : 0, rows);
   return hipGetLastError();
 }
 
