@@ -1303,8 +1303,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
 // arithmetic and partial layout as the streamed form; each wave holds its tile's whole
 // Xhat slab (NCH chunks) and U slab in registers: the U loads of a tile are
 // issued before its matrix product and the next tile's Xhat before its epilogue.
-// UN: rows of X or U not 16-byte aligned (float by float, each tile's loads in front of its
-// products: 113 us at 700,001 x 51 x 13).
+// UN: rows of X or U not 16-byte aligned: the same in 16-byte pieces at 4-byte addresses, by elements
+// in the tile with the last row (52 us at 700,001 x 51 x 13, 4.2 TB/s of its bytes).
 // ---------------------------------------------------------------------------
 template <int NB, int NCH, bool UN>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_pass_b_res(
@@ -1529,7 +1529,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
 }
 
 // ---------------------------------------------------------------------------
-// Control after pass B (one workgroup): Algorithm 2 steps (d)-(f).
+// Control after pass B: Algorithm 2 steps (d)-(f).
 // ---------------------------------------------------------------------------
 // Workgroup b writes p for its columns (each forms c from the same sums), workgroup 0 the rest.
 // (A breakdown, set by workgroup 0, may keep another workgroup from its columns; none are written
@@ -1599,7 +1599,7 @@ __global__ __launch_bounds__(kThreads) void k_ctl_b(Geometry g, Bufs B, StepArgs
 
 // ---------------------------------------------------------------------------
 // One-pass iteration (the eight-wave fused pass B does the row work too), control
-// after the pass (one workgroup).  Unless the row pass ran first (rows_first: the
+// after the pass.  Unless the row pass ran first (rows_first: the
 // previous iteration's stopping rule could fire, and k_ctl_a has decided it and
 // written the record), the pass did the row work of this iteration -- the end of
 // the previous one: its gated dual step, q and the objective terms -- before the

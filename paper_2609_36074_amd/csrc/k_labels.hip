@@ -12,8 +12,9 @@
 //   |e_i|^2 + |cent_k|^2 - 2 u_i M_k, so a pass is one product U M with the argmin over k in
 //   registers.  It runs on the fp16 matrix cores with two-term operand splits, under a bound on
 //   its rounding: a row whose two smallest values lie within it is decided by the same form in
-//   FP64 over its candidates, and one whose values are too close for that by the distances
-//   themselves (FP64, lowest index on ties), so that the labels are those of FP64 distances.  The
+//   FP64 over its candidates, and one whose values are too close for that, or with more than four
+//   candidates, by the distances themselves (FP64, lowest index on ties), so that the labels are
+//   those of FP64 distances.  The
 //   cluster sums S_k = sum of u_i over the rows of k are taken in 64-bit integers (below), and
 //   cent_k = (S_k / count) P (a centroid without rows stays in place).
 // The device notes the first pass that changes no label; passes enqueued after it return

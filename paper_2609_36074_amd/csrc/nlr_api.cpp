@@ -196,8 +196,8 @@ static size_t lab_fixed_bytes(int32_t r, int32_t K) {
 // (16 MiB at most) and 256 of K x K, less what the fixed arrays take beyond two r x r, an r x K and a
 // K x K one; never under one chunk of either kind, and up to 64 columns one per 256 rows, 48 at most.
 // (Narrow factors of more rows find what they need in the region: its Theta partials are 4 KiB or
-// more a workgroup of pass A, which has one per 512 rows.  With what the first rule leaves them, one
-// chunk, a pass over 1e6 x 4 took 21 ms; on all chunks 0.06.)
+// more a workgroup of pass A, which has one per 512 rows.  On the one chunk that the first rule leaves
+// them, two passes over 1e6 x 4 with K = 4 took 63.8 ms a call, on all 0.49.)
 static size_t lab_part_bytes(int64_t n, int32_t r) {
   const size_t rr = (size_t)r * r * 8, kmax = r < kLabMaxK ? r : kLabMaxK;
   size_t gu = (size_t)((n + 4095) / 4096);
@@ -240,8 +240,7 @@ LabScratch carve_lab_scratch(int64_t n, int32_t r, int32_t K, char* base, size_t
   if (gu > (int64_t)(bytes / rr)) gu = (int64_t)(bytes / rr);
   L.GU = (int32_t)(gu < 1 ? 1 : gu);
   // sum chunks: two workgroups a compute unit over the 64-column groups (their 64 KiB of LDS), at
-  // least 512 rows each (with 256, the centroids' sums over the chunks of 1e5 rows take 2 us longer
-  // and the chunks no less)
+  // least 512 rows each (every centroid sums over all chunks)
   int64_t w = 512 / nbk;
   const size_t chunk = (size_t)K * r * 8 + (size_t)K * 4;
   if (w > (n + 511) / 512) w = (n + 511) / 512;

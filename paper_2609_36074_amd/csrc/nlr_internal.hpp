@@ -10,7 +10,7 @@
 
 namespace nlr {
 
-constexpr int kThreads = 256;     // every kernel uses 256-thread workgroups (4 wave64)
+constexpr int kThreads = 256;     // threads of a workgroup (4 wave64), where a kernel has no number of its own
 constexpr int kHistCap = 4096;    // per-iteration record ring
 constexpr int kTPA = 64;          // rows per pass-A tile
 constexpr int kTPB = 128;         // rows per pass-B super-tile (4 waves x 32 rows)
@@ -25,8 +25,10 @@ constexpr int kSquarings = 20;    // C -> C^(2^20) before the refinement
 constexpr int32_t kBreakdown = 1;
 constexpr int32_t kRangeError = 2;
 
-// Device control block.  Written only by single-workgroup control kernels and
-// read uniformly by every kernel at entry.
+// Device control block, read uniformly by every kernel at entry.  A launch writes it from one
+// workgroup at most: workgroup 0 of the controls (of several workgroups themselves, so what one of
+// them tests at entry and workgroup 0 sets is read once a workgroup), of the initialisation's and
+// the panel form's small kernels.
 struct alignas(16) DevCtl {
   int32_t stop;        // stopping rule fired during the current host call: 1, two-pass forms 2 from the next control on
   int32_t breakdown;   // sticky: kBreakdown (normalisation breakdown) or kRangeError

@@ -205,10 +205,10 @@ def test_two_pass_streamed_theta(n, d, r, K):
 
 
 # Two-pass fp32 form above 128 columns at its edges: about one tile per workgroup (n = 301
-# just above r, a ragged last tile and super-tile), rows not 16-byte aligned (d % 4 == 2: the
-# LDS-staged Theta product; r % 4 != 0: the pair-wise pass B), the smallest split width
-# (r = 129: three columns per lane in the row launch; its 64 x 256 Theta fills 64 KiB
-# exactly, so pass B takes it from L2)
+# just above r, a ragged last tile and super-tile), rows not 16-byte aligned (d % 4 == 2, r % 4 != 0:
+# the unaligned instances of the prefetched Theta product and the streamed pass B), the smallest
+# width with ybar stored (r = 129: three columns per lane in the row launch; its 64 x 256 Theta
+# fills 64 KiB exactly, so pass B streams it)
 @pytest.mark.parametrize("n,d,r,K", [(301, 40, 300, 6), (777, 130, 160, 8), (1500, 64, 129, 9),
                                      (2049, 132, 260, 10)])
 def test_two_pass_wide_edges(n, d, r, K):
@@ -518,6 +518,24 @@ def test_data_start_block_edges(n, d, r):
     V = Xh @ (Xh.T @ Z)
     cond = np.linalg.cond(V)
     log(f"data start n={n} d={d} r={r}: U0 err {err:.2e}, condition {cond:.1e}")
+    assert err < 2.0 ** -24 * np.sqrt(n) * cond + 1e-6
+
+
+@pytest.mark.parametrize("n,d,r", [(300, 5, 1), (999, 17, 16), (1000, 66, 33), (1025, 51, 48), (1500, 64, 63),
+                                   (2000, 131, 65), (2300, 150, 129), (4000, 300, 200), (6000, 460, 448)])
+def test_data_start_block_edges_well_conditioned(n, d, r):
+    """The same shapes with isotropic data and Z in the span of Xhat, so that the sample's condition is
+    a small number and the bound on the fp32 first product leaves no room for a wrong block."""
+    rng = np.random.default_rng(n + r)
+    X = rng.standard_normal((n, d)).astype(np.float32)
+    Xh, _, _ = onlr.centre_and_normalise(X)
+    Z = (Xh @ np.linalg.qr(rng.standard_normal((d, r)))[0]).astype(np.float32).astype(np.float64)
+    ctx = make_ctx(X, Z, r, 0.01, flags=DATA_START)
+    U0_ref, Q = onlr.data_informed_start(Xh, Z, r)
+    err = rel_max_err(host(ctx.U), U0_ref)
+    cond = np.linalg.cond(Xh @ (Xh.T @ Z))
+    log(f"data start n={n} d={d} r={r}: U0 err {err:.2e}, condition {cond:.1f}")
+    assert cond < 6.0
     assert err < 2.0 ** -24 * np.sqrt(n) * cond + 1e-6
 
 
