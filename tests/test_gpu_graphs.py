@@ -111,3 +111,34 @@ def test_graph_replay_stop_between_polls():
         b.step(with_stats=False)
     for name in ("U", "y"):
         assert np.array_equal(host(getattr(a, name)), host(getattr(b, name))), name
+
+
+@pytest.mark.parametrize("n,d,r,flags,form,T_min", [f[:5] + (5,) for f in FORMS[:4] + FORMS[7:]])
+def test_step_captured_by_the_caller(n, d, r, flags, form, T_min):
+    """nlr_step without a record, captured on the context's stream and replayed after the context is
+    closed: every replay is one iteration, below T_min and above it, bit for bit (the caller keeps
+    X, U, y and the workspace; the step leaves nothing that writes the context's host memory)."""
+    import torch
+    K, beta = 4, 2.0
+    X, _, _ = gaussian_mixture(n, d, K, 25.0, seed=1)
+    Z = standard_normal_factor(n, r, seed=2).astype(np.float64)
+    alpha = 1.8 * onlr.default_step_size(K, beta)
+    kw = dict(eps_d=3e-3, eps_c=1e-9, T_min=T_min, flags=flags)
+    log(f"captured step {form} n={n} d={d} r={r} flags={flags}")
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        a = make_ctx(X, Z, K, alpha, beta, stream=s, **kw)
+        a.step(with_stats=False)
+    b = make_ctx(X, Z, K, alpha, beta, **kw)
+    b.step(with_stats=False)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        a.step(with_stats=False)
+    held = (a.X, a.U, a.y, a.workspace)
+    a.close()
+    for k in range(12):
+        graph.replay()
+        torch.cuda.synchronize()
+        b.step(with_stats=False)
+        assert np.array_equal(host(held[1]), host(b.U)) and np.array_equal(host(held[2]), host(b.y)), k
