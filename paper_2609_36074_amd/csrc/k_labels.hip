@@ -541,7 +541,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
           const double t64 = tol64u * (double)__shfl(unorm, rl, 64) + tol64c;
           double b64 = 1e300, s64 = 1e300;
           int kb = 0;
-          // (a candidate costs a sum over the wave; with many of them the distances are cheaper)
+          // a candidate costs a sum over the wave; with more than a few the distances are cheaper (a
+          // third of 1e6 rows equally far from 60 centroids: a call 15.4 ms by scores, 3.3 so)
           const bool few = __popcll(mm[0]) + __popcll(mm[1]) <= 4;
 #pragma unroll 1
           for (int x = 0; few && x < 2; ++x)
